@@ -40,7 +40,7 @@ struct Bf16Args {
   const float* target;
   float* fitness;
   int loss;
-  int window_params, rag_at, rag_rows;  // generic kernel: see there
+  int window_params, rag_at, rag_rows, bias_at;  // generic kernel: see there
 };
 
 union Pack8 {
@@ -93,23 +93,27 @@ __device__ __forceinline__ float act_f(float v, int act) {
 // What bounds it is the weight stream (2 P bytes per member, used once) and, at a few tens of kilobytes per member,
 // the latency in front of it.  A member's parameters are one contiguous vector, W1 rows, b1, W2 rows, ..., and the
 // workgroup takes them as that: up to 48 KB at a time (a window: usually the whole member) are requested in one go,
-// sixteen bytes a lane, and left in LDS as rows (a layer's bias is one more row); a longer vector comes in several
-// windows, the next one in flight under the products of this one.  Operands are read back transposed
-// (ds_read_b64_tr_b16: four consecutive k of a column per lane).  The row stride is an odd multiple of 32 bytes, for
-// which the sixteen 32-byte row pieces of a transposed read meet all banks, and a tile is an immediate of the read.
+// sixteen bytes a lane, and left in LDS as rows; a longer vector comes in several windows, the next one in flight under
+// the products of this one.  The biases, which the sums start from, are fetched ahead of the first window into LDS of
+// their own.  Operands are read back transposed (ds_read_b64_tr_b16: four consecutive k of a column per lane); a tile is
+// an immediate of the read.
 // The activations never leave the registers.  Products are transposed (rows = neurons, columns = the wave's sixteen
 // observations); with v_mfma_f32_16x16x32_bf16 lane (j, q) of a product ends with neurons 16 t + 4 q + i of
-// observation j, and the next layer's contraction simply runs over k in the order
-//   step s, lane group q, element e:  k = 32 s + 4 q + e (e < 4),  32 s + 16 + 4 q + e - 4 (e >= 4),
-// for which the B operand of a lane is its own eight values of tiles 2 s and 2 s + 1: no LDS, no lane exchange and no
-// barrier between layers.
+// observation j.  The next layer takes them as k = 32 s + 8 q + e of lane group q, for which two lane swaps per packed
+// pair bring the eight values of a group together (no LDS, no barrier between layers).  The instruction adds its four
+// lane groups' eight products one group after the other, so with each group's k in their own order the sums are, bit for
+// bit, those of the 32x32x16 products over the same k from the same start, which the streaming and resident kernels
+// use; the order inside a group does not matter, and odd groups take their two halves in turn so that the sixteen
+// 32-byte row pieces of a transposed read (rows 8 q + (0..3) and 8 q + (4..7)) meet all banks with a row stride of an
+// odd multiple of 32 bytes.
 // Measured (get_actions, 48-144-96-12 tanh, 50 observations per member, against a kernel that gathered W element by element
-// with nothing in flight and kept activations in LDS): 1024 members 142 -> 29.5 us, 256 members 31.9 -> 11.7 us;
-// 64-256-256-32 ReLU, 1024 members 207 -> 58 us (3.6 TB/s); 48-96-12, 1024 members 58 -> 12 us.  What is left is
-// instruction issue: LDS holds two members per CU, i.e. two waves per SIMD, and a wave spends 27,000 cycles on a member,
-// 5,000 of them on leaving the window in LDS and 760 per step of 32 k.  Tried: 32 observations per wave (accumulators and
-// inputs of both groups do not fit beside the window, 50 us), the reads one group of tiles ahead of the products (no
-// change), three workgroups per CU with fewer registers (spills; LDS allows two).
+// with nothing in flight and kept activations in LDS, whose bits these are): 1024 members 141 -> 40 us, 256 members
+// 32 -> 17 us; 64-256-256-32 ReLU of 64, 1024 members 207 -> 59 us (3.5 TB/s); 48-96-12 ReLU, 1024 members 59 -> 11 us.
+// Bound by instruction issue: LDS holds two members per CU, i.e. two waves per SIMD.  9 us of the 40 are
+// tanhf against one by the hardware exponential and reciprocal (1e-6 relative), which rounded some activations
+// to the other bfloat16.  Tried: 32 observations per wave (accumulators and inputs of both groups do not fit beside the
+// window, 50 us), the reads one group of tiles ahead of the products (no change), three workgroups per CU with fewer
+// registers (spills; LDS allows two).
 __host__ __device__ constexpr int gen_pieces(int NT) { return NT == 4 ? 6 : 12; }  // 16 bytes each, per thread and window
 __host__ __device__ constexpr int gen_window(int NT) { return gen_pieces(NT) * kBf16Threads * 8; }  // elements
 
@@ -117,19 +121,13 @@ __host__ __device__ constexpr int gen_window(int NT) { return gen_pieces(NT) * k
 __host__ __device__ __forceinline__ int gen_stride(int N) { return 32 * (((N + 15) >> 4) | 1); }
 // Rows of a layer's W in LDS: a layer that ends with half a step gets sixteen rows of zeros, so that no step is special.
 __host__ __device__ __forceinline__ int gen_rows(int K) { return (K + 31) & ~31; }
+// Floats from observation to observation of the errors in LDS: up to 128 outputs, and eight more so that the rows 4 apart
+// that a read takes at once meet different banks.
+__host__ __device__ __forceinline__ int gen_error_stride(int A) { return (A > 96 ? 128 : (A + 31) & ~31) + 8; }
 // Elements of theta from row k0 of a layer (offset off) to the end of that step of 32 rows; the bias row belongs to
 // the last step.
 __host__ __device__ __forceinline__ int gen_step_end(int off, int k0, int K, int N) {
   return k0 + 32 < K ? off + (k0 + 32) * N : off + K * N + N;
-}
-
-// tanh of a value that is rounded to bfloat16 next: 1 - 2 / (e^2x + 1) on the hardware exponential and reciprocal (1e-7
-// absolute, 1e-6 relative from 1/8 on), below that the odd series up to x^5 (next term 2e-7 of the value).
-__device__ __forceinline__ float tanh_for_bf16(float x) {
-  const float t = fmaf(-2.0f, __builtin_amdgcn_rcpf(__builtin_amdgcn_exp2f(2.885390081777927f * x) + 1.0f), 1.0f);
-  const float x2 = x * x;
-  const float s = fmaf(x * x2, fmaf(x2, 2.0f / 15.0f, -1.0f / 3.0f), x);
-  return fabsf(x) < 0.125f ? s : t;
 }
 
 template <int NT>  // neuron tiles of the widest layer
@@ -160,7 +158,8 @@ __global__ __launch_bounds__(kBf16Threads, NT >= 12 ? 2 : NT == 8 ? 3 : 4) void 
   auto zero_rows = [&](int at, int stride) {   // sixteen rows
     for (int i = tid; i < stride; i += kBf16Threads) *reinterpret_cast<uint4*>(window_s + at + 16 * i) = make_uint4(0u, 0u, 0u, 0u);
   };
-  // The fetched elements [begin, end), which begin with row k0 of layer l (offset off), -> LDS rows, that row first.
+  // The fetched elements [begin, end), which begin with row k0 of layer l (offset off), -> LDS rows, that row first
+  // (the biases among them are in LDS already).
   auto store = [&](int begin, int end, int l, int k0, int off) {
     int base = 0;                              // LDS address of the window's first row of the layer
     while (l < n_layers && off + k0 * a.sh.dims[l + 1] < end) {
@@ -174,25 +173,23 @@ __global__ __launch_bounds__(kBf16Threads, NT >= 12 ? 2 : NT == 8 ? 3 : 4) void 
       const int r = static_cast<int>(floorf((static_cast<float>(x) + 0.5f) * __builtin_amdgcn_rcpf(static_cast<float>(w))));
       int c = x - r * w;
       int dst = base + r * stride + 16 * c;
-      const int bias_x = (K - k0) * w;         // the bias row goes behind the rows of zeros
-      const int bias_shift = (gen_rows(K) - K) * stride;
+      const int n_x = min(p1 - p0, (K - k0) * w);
 #pragma unroll
       for (int i = 0; i < kGenPieces; ++i) {
         if (i < i0 || i >= i1) continue;       // uniform
-        if (x >= 0 && x < p1 - p0)
-          *reinterpret_cast<u32x4v*>(window_s + dst + (x >= bias_x ? bias_shift : 0)) = piece[i];
+        if (x >= 0 && x < n_x) *reinterpret_cast<u32x4v*>(window_s + dst) = piece[i];
         x += kBf16Threads, c += dc;
         const bool wrap = c >= w;
         c -= wrap ? w : 0;
         dst += dr * stride + 16 * dc + (wrap ? stride - 16 * w : 0);
       }
       if ((K & 31) != 0 && off + K * N < end) zero_rows(base + (K - k0) * stride, stride);
-      base += (gen_rows(K) + 1 - k0) * stride;
+      base += (gen_rows(K) - k0) * stride;
       off += K * N + N, k0 = 0, ++l;
     }
   };
   // A last layer whose width is no multiple of 8 comes element by element, into LDS of its own behind the window: all of
-  // it at the start where that is little (rag_rows = K + 1), else 32 rows at a time.
+  // it at the start where that is little (rag_rows = K), else 32 rows at a time.
   constexpr int kRagged = 8;                   // elements per thread that are requested ahead
   const int rag_K = a.sh.dims[n_layers - 1], rag_N = a.sh.dims[n_layers];
   const bool ragged = a.rag_rows > 0;
@@ -200,11 +197,24 @@ __global__ __launch_bounds__(kBf16Threads, NT >= 12 ? 2 : NT == 8 ? 3 : 4) void 
   int rag_k0 = 0;                              // first row in LDS
   auto rag_put = [&](int e, uint16_t v) {      // (e below 2^14: exact, as above)
     const int r = static_cast<int>((static_cast<float>(e) + 0.5f) * rag_inv), c = e - r * rag_N;
-    const int row = r + rag_k0 < rag_K ? r : gen_rows(rag_K) - rag_k0;  // the bias row behind the rows of zeros
-    *reinterpret_cast<uint16_t*>(window_s + a.rag_at + row * gen_stride(rag_N) + 2 * c) = v;
+    *reinterpret_cast<uint16_t*>(window_s + a.rag_at + r * gen_stride(rag_N) + 2 * c) = v;
   };
-  const bool rag_ahead = ragged && a.rag_rows > rag_K && (rag_K + 1) * rag_N <= kRagged * kBf16Threads;
+  const bool rag_ahead = ragged && a.rag_rows >= rag_K && rag_K * rag_N <= kRagged * kBf16Threads;
   uint16_t rag[kRagged];
+  // the biases, one element per thread and layer, in the order of the layers (every offset but the last one's end is a
+  // multiple of 16 elements)
+  uint16_t* const bias_s = reinterpret_cast<uint16_t*>(window_s + a.bias_at);
+  uint16_t bias[EVO_MAX_LAYERS];
+  {
+    int at = 0;
+#pragma unroll
+    for (int i = 0; i < EVO_MAX_LAYERS; ++i) {
+      if (i >= n_layers) break;
+      at += a.sh.dims[i] * a.sh.dims[i + 1];
+      bias[i] = theta[at + min(tid, a.sh.dims[i + 1] - 1)];
+      at += a.sh.dims[i + 1];
+    }
+  }
   if (Pw > 0) fetch(0);
   if (rag_ahead) {
 #pragma unroll
@@ -212,41 +222,57 @@ __global__ __launch_bounds__(kBf16Threads, NT >= 12 ? 2 : NT == 8 ? 3 : 4) void 
   }
 
   // ---- this lane's observation: eight values per step, straight into operand order (widths are multiples of 16) ----
+  const int half = 4 * (q & 1);                // the half of its group's eight k that a lane takes first
   bf16x8 in[NS];
   {
     const int D = a.sh.dims[0];
     const bool live = b < B;
-    const float* row = a.obs + static_cast<size_t>(member) * a.obs_stride + static_cast<size_t>(live ? b : 0) * D + 4 * q;
+    const float* row = a.obs + static_cast<size_t>(member) * a.obs_stride + static_cast<size_t>(live ? b : 0) * D;
     // no load is predicated: what lies beyond the batch or the width is fetched from a row's start and set to zero
     float4 lo[NS], hi[NS];
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
-      lo[s] = *reinterpret_cast<const float4*>(row + (32 * s < D ? 32 * s : 0));
-      hi[s] = *reinterpret_cast<const float4*>(row + (32 * s + 16 < D ? 32 * s + 16 : 0));
+      const float* src = row + (32 * s + 8 * q < D ? 32 * s + 8 * q : 0);
+      lo[s] = *reinterpret_cast<const float4*>(src + half);
+      hi[s] = *reinterpret_cast<const float4*>(src + (half ^ 4));
     }
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
-      const uint32_t m_lo = live && 32 * s < D ? ~0u : 0u, m_hi = live && 32 * s + 16 < D ? ~0u : 0u;
-      in[s] = as_bf16x8(make_uint4(pack_bf16x2(lo[s].x, lo[s].y) & m_lo, pack_bf16x2(lo[s].z, lo[s].w) & m_lo,
-                                   pack_bf16x2(hi[s].x, hi[s].y) & m_hi, pack_bf16x2(hi[s].z, hi[s].w) & m_hi));
+      const uint32_t m = live && 32 * s + 8 * q < D ? ~0u : 0u;
+      in[s] = as_bf16x8(make_uint4(pack_bf16x2(lo[s].x, lo[s].y) & m, pack_bf16x2(lo[s].z, lo[s].w) & m,
+                                   pack_bf16x2(hi[s].x, hi[s].y) & m, pack_bf16x2(hi[s].z, hi[s].w) & m));
+    }
+  }
+  {
+    int at = 0;
+#pragma unroll
+    for (int i = 0; i < EVO_MAX_LAYERS; ++i) {
+      if (i >= n_layers) break;
+      if (tid < a.sh.dims[i + 1]) bias_s[at + tid] = bias[i];
+      at += a.sh.dims[i + 1];
     }
   }
   if (rag_ahead) {
 #pragma unroll
     for (int i = 0; i < kRagged; ++i) {
       const int e = tid + kBf16Threads * i;
-      if (e < (rag_K + 1) * rag_N) rag_put(e, rag[i]);
+      if (e < rag_K * rag_N) rag_put(e, rag[i]);
     }
     if ((rag_K & 31) != 0) zero_rows(a.rag_at + rag_K * gen_stride(rag_N), gen_stride(rag_N));
-    if (n_layers == 1) __syncthreads();        // (else the first window's barrier follows)
   }
+  __syncthreads();                             // (the first window is still on its way)
 
   floatx4v acc[NT];
-  auto clear = [&]() {
+  auto start_sums = [&](int at) {              // `at`: the layer's first bias; what lies beyond its width is dropped later
 #pragma unroll
-    for (int t = 0; t < NT; ++t) acc[t] = floatx4v{0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < NT; ++t) {
+      const uint2 v = *reinterpret_cast<const uint2*>(bias_s + at + 4 * q + 16 * t);
+      acc[t] = floatx4v{__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u), __uint_as_float(v.y << 16),
+                        __uint_as_float(v.y & 0xffff0000u)};
+    }
   };
-  clear();
+  start_sums(0);
+  int biases = 0;                              // of the layers before this one
   int l = 0, k0 = 0, off = 0;                  // the layer, its offset in theta, the step's first row
   int K = a.sh.dims[0], N = a.sh.dims[1], stride = gen_stride(N);
   // One step: rows k0 .. k0 + 31 of the layer, which lie in LDS from `at` on, against in[0].  Every tile of the class is
@@ -256,23 +282,13 @@ __global__ __launch_bounds__(kBf16Threads, NT >= 12 ? 2 : NT == 8 ? 3 : 4) void 
     const bf16x8 x = in[0];
 #pragma unroll
     for (int s = 0; s + 1 < NS; ++s) in[s] = in[s + 1];
-    const unsigned char* src = window_s + at + (4 * q + (j >> 2)) * stride + 8 * (j & 3);
-    const unsigned char* src_hi = src + 16 * stride;
+    const unsigned char* src = window_s + at + (8 * q + half + (j >> 2)) * stride + 8 * (j & 3);
+    const unsigned char* src_hi = src + (half ? -4 : 4) * stride;
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(src + 32 * t));
       const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(src_hi + 32 * t));
       acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(join_bf16(lo, hi), x, acc[t], 0, 0, 0);
-    }
-  };
-  auto add_bias = [&](int at) {                // `at`: the layer's bias row
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      const uint2 v = *reinterpret_cast<const uint2*>(window_s + at + 8 * q + 32 * t);
-      acc[t][0] += from_bf16(static_cast<uint16_t>(v.x));
-      acc[t][1] += __uint_as_float(v.x & 0xffff0000u);
-      acc[t][2] += from_bf16(static_cast<uint16_t>(v.y));
-      acc[t][3] += __uint_as_float(v.y & 0xffff0000u);
     }
   };
   // A hidden layer is complete: its activations become the next one's input.
@@ -283,18 +299,26 @@ __global__ __launch_bounds__(kBf16Threads, NT >= 12 ? 2 : NT == 8 ? 3 : 4) void 
       for (int s = 0; s < NS; ++s) {
         if (32 * s >= N) break;                // the next layer's steps end here
         const floatx4v x = acc[2 * s], y = 32 * s + 16 < N ? acc[2 * s + 1] : floatx4v{0.f, 0.f, 0.f, 0.f};
-        in[s] = as_bf16x8(make_uint4(pack_bf16x2(f(x[0]), f(x[1])), pack_bf16x2(f(x[2]), f(x[3])),
-                                     pack_bf16x2(f(y[0]), f(y[1])), pack_bf16x2(f(y[2]), f(y[3]))));
+        uint32_t first[2], second[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          // lane groups (x0 x1 x2 x3), (y0 y1 y2 y3) -> (x0 x2 y0 y2), (x1 x3 y1 y3): k 8 q + 0..3 and 8 q + 4..7
+          const auto far = __builtin_amdgcn_permlane32_swap(pack_bf16x2(f(x[2 * h]), f(x[2 * h + 1])),
+                                                            pack_bf16x2(f(y[2 * h]), f(y[2 * h + 1])), false, false);
+          const auto near = __builtin_amdgcn_permlane16_swap(far[0], far[1], false, false);
+          first[h] = half ? near[1] : near[0], second[h] = half ? near[0] : near[1];
+        }
+        in[s] = as_bf16x8(make_uint4(first[0], first[1], second[0], second[1]));
       }
     };
     if (busy) {
-      if (act == EVO_ACT_TANH) hand_on([](float v) { return tanh_for_bf16(v); });
-      else if (act == EVO_ACT_RELU) hand_on([](float v) { return __int_as_float(max(__float_as_int(v), 0)); });
+      if (act == EVO_ACT_TANH) hand_on([](float v) { return tanhf(v); });
+      else if (act == EVO_ACT_RELU) hand_on([](float v) { return fmaxf(v, 0.f); });
       else hand_on([](float v) { return v; });
     }
-    off += K * N + N;
+    off += K * N + N, biases += N;
     ++l, k0 = 0, K = N, N = a.sh.dims[l + 1], stride = gen_stride(N);
-    clear();
+    start_sums(biases);
   };
   const int n_windowed = n_layers - (ragged ? 1 : 0);  // layers that come through the windows
   for (int begin = 0; begin < Pw;) {
@@ -323,8 +347,6 @@ __global__ __launch_bounds__(kBf16Threads, NT >= 12 ? 2 : NT == 8 ? 3 : 4) void 
       at += 32 * stride;
       k0 += 32;
       if (k0 >= K) {
-        if (busy) add_bias(at);
-        at += stride;
         if (l + 1 == n_layers) break;
         next_layer();
         if (l == n_windowed) break;
@@ -335,66 +357,90 @@ __global__ __launch_bounds__(kBf16Threads, NT >= 12 ? 2 : NT == 8 ? 3 : 4) void 
   if (ragged) {
 #pragma unroll 1
     for (; k0 < K; k0 += 32) {
-      if (!rag_ahead && (k0 == 0 || a.rag_rows <= K)) {
+      if (!rag_ahead && (k0 == 0 || a.rag_rows < K)) {
         __syncthreads();                       // every wave has read the rows before
         rag_k0 = k0;
-        const int n = (a.rag_rows > K || k0 + 32 >= K ? K + 1 - k0 : 32) * N;
+        const int rows = a.rag_rows >= K ? K : min(32, K - k0);
 #pragma unroll 4
-        for (int e = tid; e < n; e += kBf16Threads) rag_put(e, theta[Pw + k0 * N + e]);
-        if ((K & 31) != 0 && (a.rag_rows > K || k0 + 32 >= K)) zero_rows(a.rag_at + (K - k0) * stride, stride);
+        for (int e = tid; e < rows * N; e += kBf16Threads) rag_put(e, theta[Pw + k0 * N + e]);
+        if ((rows & 31) != 0) zero_rows(a.rag_at + rows * stride, stride);
         __syncthreads();
       }
       if (busy) step(a.rag_at + (k0 - rag_k0) * stride);
     }
-    if (busy) add_bias(a.rag_at + (k0 - rag_k0) * stride);
   }
   // ---- outputs or their squared error ------------------------------------------------------------------
   const int A = a.sh.dims[n_layers], act = a.sh.act[n_layers - 1];
-  float loss_acc = 0.f;
-  if (b < B) {
-    const size_t base = (static_cast<size_t>(member) * B + b) * A + 4 * q;
-    // (A a multiple of 4: a lane's four outputs are 16 aligned bytes)
-    const bool quad = (A & 3) == 0;
+  const bool live = b < B;
+  const bool quad = (A & 3) == 0;              // a lane's four outputs are 16 aligned bytes
+  const size_t out_at = (static_cast<size_t>(member) * B + (live ? b : 0)) * A + 4 * q;
+  auto outputs = [&](int t, float (&v)[4]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      v[i] = act == EVO_ACT_TANH ? tanhf(acc[t][i]) : act == EVO_ACT_RELU ? fmaxf(acc[t][i], 0.f) : acc[t][i];
+  };
+  if (a.loss == LOSS_NONE) {
+    if (!live) return;
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
-      if (16 * t < A) {
-        float v[4];
-        const int n = 16 * t + 4 * q;
+      if (16 * t >= A) break;
+      float v[4];
+      outputs(t, v);
+      float* dst = a.out + out_at + 16 * t;
+      const int n = 16 * t + 4 * q;
+      if (quad) {
+        if (n < A) *reinterpret_cast<float4*>(dst) = make_float4(v[0], v[1], v[2], v[3]);
+      } else {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = act == EVO_ACT_TANH ? tanh_fast_accurate(acc[t][i])
-                                           : act == EVO_ACT_RELU ? __int_as_float(max(__float_as_int(acc[t][i]), 0)) : acc[t][i];
-        if (a.loss == LOSS_NONE) {
-          float* dst = a.out + base + 16 * t;
-          if (quad) {
-            if (n < A) *reinterpret_cast<float4*>(dst) = make_float4(v[0], v[1], v[2], v[3]);
-          } else {
+        for (int i = 0; i < 4; ++i)
+          if (n + i < A) dst[i] = v[i];
+      }
+    }
+    return;
+  }
+  // The squared errors are added as 32 x 32 tiles of the outputs hold them (rows = observations: lane 32 g + c has
+  // column c and rows 8 r + 4 g + i), the tiles of 32 outputs one per wave in turn: the errors pass through LDS, eight
+  // neuron tiles at a time.
+  float loss_acc = 0.f;
+  const int stride_e = gen_error_stride(A);
+  float* const err_s = reinterpret_cast<float*>(window_s);
+  const int c = lane & 31, g = lane >> 5;
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-              if (n + i < A) dst[i] = v[i];
-          }
-        } else {
-          const float* tg = a.target + base + 16 * t;
-          float y[4] = {v[0], v[1], v[2], v[3]};
-          if (quad) {
-            if (n < A) {
-              const float4 g = *reinterpret_cast<const float4*>(tg);
-              y[0] = g.x, y[1] = g.y, y[2] = g.z, y[3] = g.w;
-            }
-          } else {
+  for (int t0 = 0; t0 < NT; t0 += 8) {
+    if (16 * t0 >= A) break;
+    __syncthreads();                           // every wave has read its weights, or the errors before
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-              if (n + i < A) y[i] = tg[i];
-          }
+    for (int t = t0; t < t0 + 8 && t < NT; ++t) {
+      if (32 * (t >> 1) >= A) break;           // whole tiles of 32 outputs, zeros beyond the last one
+      float v[4], y[4];
+      outputs(t, v);
+      const float* tg = a.target + out_at + 16 * t;
+      const int n = 16 * t + 4 * q;
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const float d = n + i < A ? v[i] - y[i] : 0.f;
-            loss_acc = fmaf(d, d, loss_acc);
-          }
+      for (int i = 0; i < 4; ++i) y[i] = v[i];
+      if (quad) {
+        if (live && n < A) {
+          const float4 w = *reinterpret_cast<const float4*>(tg);
+          y[0] = w.x, y[1] = w.y, y[2] = w.z, y[3] = w.w;
         }
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (live && n + i < A) y[i] = tg[i];
+      }
+      *reinterpret_cast<float4*>(err_s + b * stride_e + 16 * (t - t0) + 4 * q) =
+          make_float4(live && n < A ? v[0] - y[0] : 0.f, live && n + 1 < A ? v[1] - y[1] : 0.f,
+                      live && n + 2 < A ? v[2] - y[2] : 0.f, live && n + 3 < A ? v[3] - y[3] : 0.f);
+    }
+    __syncthreads();
+    if (16 * t0 + 32 * wave < A) {
+#pragma unroll
+      for (int r = 0; r < 32; ++r) {
+        const float d = err_s[(8 * (r >> 2) + 4 * g + (r & 3)) * stride_e + 32 * wave + c];
+        loss_acc = fmaf(d, d, loss_acc);
       }
     }
   }
-  if (a.loss == LOSS_NONE) return;
   loss_acc = wave_sum(loss_acc);
   if (lane == 0) red[wave] = loss_acc;
   __syncthreads();
@@ -1186,7 +1232,8 @@ int launch_mlp_bf16(const MlpShape& sh, const uint16_t* params, const float* obs
     return check_launch("mlp_bf16_stream_kernel");
   }
   // registers follow the widest layer, in classes of 64
-  // LDS: the largest window as rows, behind it a ragged last layer (or 33 rows of it), and what a step reads beyond a row
+  // LDS: the largest window as rows, behind it a ragged last layer (or 32 rows of it), the biases, and what a read beyond
+  // the last of them takes; the errors of the outputs later take its place
   const int A = sh.dims[sh.n_layers], K_last = sh.dims[sh.n_layers - 1];
   const bool ragged = (A & 7) != 0;
   a.window_params = ragged ? sh.P - (K_last + 1) * A : sh.P;
@@ -1198,7 +1245,7 @@ int launch_mlp_bf16(const MlpShape& sh, const uint16_t* params, const float* obs
     for (int k0 = 0; k0 < K; k0 += 32) {
       const int end = gen_step_end(off, k0, K, N);
       if (end > w_end) w_end = off + k0 * N + window, rows_bytes = 0;  // this step opens a window
-      rows_bytes += static_cast<size_t>(k0 + 32 < K ? 32 : 33) * gen_stride(N);
+      rows_bytes += static_cast<size_t>(32) * gen_stride(N);
       lds = rows_bytes > lds ? rows_bytes : lds;
     }
     off += K * N + N;
@@ -1206,10 +1253,14 @@ int launch_mlp_bf16(const MlpShape& sh, const uint16_t* params, const float* obs
   a.rag_at = static_cast<int>(lds);
   a.rag_rows = 0;
   if (ragged) {
-    a.rag_rows = (gen_rows(K_last) + 1) * gen_stride(A) <= 24 * 1024 ? K_last + 1 : 32;
-    lds += static_cast<size_t>(a.rag_rows > K_last ? gen_rows(K_last) + 1 : 33) * gen_stride(A);
+    a.rag_rows = gen_rows(K_last) * gen_stride(A) <= 24 * 1024 ? K_last : 32;
+    lds += static_cast<size_t>(a.rag_rows >= K_last ? gen_rows(K_last) : 32) * gen_stride(A);
   }
-  lds += 32 * nt_class;
+  a.bias_at = static_cast<int>(lds);
+  for (int l = 0; l < sh.n_layers; ++l) lds += sizeof(uint16_t) * sh.dims[l + 1];
+  lds = ((lds + 15) & ~size_t(15)) + 32 * nt_class;
+  const size_t errors = loss == LOSS_NONE ? 0 : sizeof(float) * kMaxRows * gen_error_stride(A);
+  lds = lds > errors ? lds : errors;
   auto launch = [&](auto kern) -> int {
     if (lds > 64 * 1024) {
       hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,

@@ -336,6 +336,48 @@ def test_mlp_bf16_any_width(evo, dims, acts, pop, B):
         assert_scalar_rel(host(fit), otasks.regress_fitness(got.astype(np.float64), tgt), 1e-5, "bf16 fitness")
 
 
+def _embed(theta, dims, wide):
+    """The parameters of an MLP as part of one with wider layers: what is added has weights and biases of zero."""
+    out, at = [], 0
+    for (i, o), (wi, wo) in zip(zip(dims, dims[1:]), zip(wide, wide[1:])):
+        w, b = theta[:, at:at + i * o].reshape(-1, i, o), theta[:, at + i * o:at + i * o + o]
+        at += i * o + o
+        out += [torch.nn.functional.pad(w, (0, wo - o, 0, wi - i)).flatten(1), torch.nn.functional.pad(b, (0, wo - o))]
+    return torch.cat(out, 1).contiguous()
+
+
+@pytest.mark.parametrize("dims,acts,B", [((48, 144, 96, 12), (1, 1, 0), 50), ((16, 256, 240, 16), (1, 2, 1), 64),
+                                         ((64, 112, 16, 7), (2, 1, 1), 17), ((32, 32, 256, 1), (2, 2, 0), 3)])
+def test_mlp_bf16_sums_and_activations_are_those_of_the_streaming_kernel(evo, dims, acts, B):
+    """Zeros added to a sum of products don't change it, so a network padded with zeros to the streaming kernel's shape
+    gives the same bits if both kernels add in the same order, start from the bias and use the same activations."""
+    pop, wide = 6, (64, 256, 256, 16)
+    theta = dev(opgpe.round_to_bf16(gen.random_params(26, pop, mlp_param_count(dims), 0.3))).to(torch.bfloat16)
+    obs = torch.randn(pop, B, dims[0], generator=torch.Generator().manual_seed(27)).cuda()
+    outs = []
+    for d, th, ob in ((dims, theta, obs), (wide, _embed(theta, dims, wide), torch.nn.functional.pad(obs, (0, 64 - dims[0])).contiguous())):
+        out = torch.empty(pop, B, d[-1], device="cuda")
+        evo.pop_forward(evo.make_policy_desc(evo.EVO_POLICY_MLP, d, acts, evo.EVO_BF16), th, ob, B * d[0], out, pop, B)
+        outs.append(out[..., :dims[-1]])
+    assert torch.equal(*outs)
+
+
+def test_mlp_bf16_output_activations(evo):
+    """The last layer's result reaches the caller in fp32: its tanh is within two units in the last place (2^-22 of the
+    value) of the 64-bit one, and the ReLU of a NaN is zero."""
+    dims, B = (16, 255), 3
+    x = opgpe.round_to_bf16(np.concatenate([np.linspace(-9.0, 9.0, 254), [np.nan]]).astype(np.float32))
+    theta = np.concatenate([np.zeros(16 * 255, np.float32), x])[None]
+    obs = torch.ones(B, 16, device="cuda")
+    for act, ref in ((1, np.tanh(x.astype(np.float64))), (2, np.where(x > 0, x, 0.0))):
+        out = torch.empty(1, B, 255, device="cuda")
+        pd = evo.make_policy_desc(evo.EVO_POLICY_MLP, dims, (act,), evo.EVO_BF16)
+        evo.pop_forward(pd, dev(theta).to(torch.bfloat16), obs, 0, out, 1, B)
+        got = host(out)[0]
+        n = 254 if act == 1 else 255
+        assert (np.abs(got[:, :n] - ref[:n]) <= 2.0 ** -22 * np.abs(ref[:n])).all()
+
+
 # ---------------------------------------------------------------- sphere
 # Rows that start on any element (odd P), shorter than one 16-byte load, and around the pieces of 4096: both storage types.
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
