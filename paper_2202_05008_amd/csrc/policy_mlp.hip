@@ -930,7 +930,9 @@ int launch_mlp_f32(const MlpShape& sh, const float* params, const float* obs, in
       int kp = 32;      // widest fan-in, padded to the matrix instruction's 32
       for (int l = 0; l < sh.n_layers; ++l) kp = max(kp, (sh.dims[l] + 31) & ~31);
       a.ldw = kp;
-      const size_t lds = static_cast<size_t>(2) * kMlpTile * (kp + 8) * 2 + (kMfmaWaves + 1) * kMlpTile * sizeof(float);
+      // two fp16 terms of a layer's input and the maxima, or the network's output in their place
+      const size_t input = static_cast<size_t>(2) * kMlpTile * (kp + 8) * 2 + (kMfmaWaves + 1) * kMlpTile * sizeof(float);
+      const size_t lds = std::max(input, sh.dims[sh.n_layers] * kMlpTile * sizeof(float));
       auto launch_short = [&](auto kern) -> int {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));

@@ -85,6 +85,7 @@ def test_pop_forward_mlp_f32_matrix_cores(evo, dims, acts, pop, B, shared, scale
     ((65, 128, 9), 130, 129, True), ((64, 129, 33), 3, 128, False), ((33, 64, 257 - 1, 1), 2, 63, True),
     ((96, 31, 97, 17), 9, 193, False), ((70, 16, 70, 16, 70, 16, 70, 16, 3), 5, 66, True),
     ((64, 256, 40, 5), 9, 64, False), ((64, 256, 40, 5), 9, 65, False),
+    ((64, 64, 64, 256), 9, 64, True), ((64, 96, 64, 129), 5, 17, True), ((256, 16, 16, 256), 3, 64, False),  # outputs wider than inputs
     ((16, 32, 4), 520, 64, True), ((15, 17, 33, 64), 513, 17, False), ((63, 64, 1), 1030, 130, True),
     ((4, 8, 2), 600, 1, True), ((1, 1), 514, 1100, True), ((20, 50, 60, 5), 700, 300, False)])
 def test_mlp_f32_forms_at_their_edges(evo, dims, pop, B, shared):
