@@ -103,11 +103,13 @@ __device__ __forceinline__ void store_row4(float* row, int col, int P, const flo
 // generation takes the same); P = 300007, 250 members (300 MB): 65 and 61 us, the generation 174 and 182 us.
 template <bool STREAM>
 __device__ __forceinline__ void ask_block(unsigned xblocks, unsigned run_log2, unsigned& xb, unsigned& k) {
-  unsigned b = blockIdx.x;
-  if (!STREAM) {
-    const unsigned die = b & 7u, i = b >> 3, run = 1u << run_log2;
-    b = ((i >> run_log2) << (run_log2 + 3)) + (die << run_log2) + (i & (run - 1u));
+  if (STREAM) {  // grid (xblocks, N): the same order as one row of workgroup numbers, which has room for 128 GiB only
+    k = blockIdx.y, xb = blockIdx.x;
+    return;
   }
+  unsigned b = blockIdx.x;
+  const unsigned die = b & 7u, i = b >> 3, run = 1u << run_log2;
+  b = ((i >> run_log2) << (run_log2 + 3)) + (die << run_log2) + (i & (run - 1u));
   k = b / xblocks, xb = b - k * xblocks;
 }
 
@@ -1300,8 +1302,8 @@ extern "C" int pgpe_ask(pgpe_state* st, uint64_t seed, int32_t pop, void* params
   const size_t blocks = static_cast<size_t>(xblocks) * N;
   const unsigned run_log2 = blocks >= 32768 ? 6 : 3;
   const size_t run = size_t(8) << run_log2;
-  EVO_REQUIRE(blocks < (size_t(1) << 31) - run, EVO_ERR_UNSUPPORTED, "pgpe_ask: population too large");
-  const dim3 grid(static_cast<unsigned>(stream_stores ? blocks : (blocks + run - 1) / run * run));
+  const dim3 grid = stream_stores ? dim3(xblocks, static_cast<unsigned>(N))
+                                  : dim3(static_cast<unsigned>((blocks + run - 1) / run * run));
   hipStream_t s = as_stream(stream);
   const uint32_t k0 = static_cast<uint32_t>(seed), k1 = static_cast<uint32_t>(seed >> 32);
   const uint32_t* gen_dev = device_generation(st);

@@ -101,6 +101,25 @@ def test_ask_bf16(evo, P, pop):
     assert (np.abs(got - ref32) <= np.abs(ref32) * 2.0 ** -8 + floor).all()  # half an ulp from the fp32 value
 
 
+def test_ask_population_of_128_gib(evo):
+    """2^24 workgroups: the size from which one row of workgroups no longer fits a launch (fewer than 2^32 threads)."""
+    P, pop = 1 << 24, 2048
+    if torch.cuda.mem_get_info()[0] < (140 << 30):
+        pytest.skip("needs 140 GiB of free device memory")
+    mu0 = torch.linspace(-1.0, 1.0, P)
+    es = evo.PGPE(evo.make_pgpe_config(P=P, pop_max=pop), mu0.numpy())
+    params = torch.full((pop, P), float("nan"), device="cuda")
+    es.ask(11, pop, params)
+    mu, z = mu0.cuda(), torch.empty(P, device="cuda")
+    for k in (0, 1, 511, 1022, 1023):
+        evo.evo_philox_normal(11, 1, k, 0, P // 4, 0, z)
+        for row, sign in ((2 * k, 1.0), (2 * k + 1, -1.0)):
+            assert (params[row] - (mu + sign * es.sigma * z)).abs().max() <= 2.0 ** -22      # values up to 2: one ulp
+    assert not any(torch.isnan(row).any() for row in params)
+    del params
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("pop,kind", [(2, "plain"), (64, "plain"), (100, "ties"), (257, "specials"), (1024, "ties"),
                                       (4096, "plain"), (4096, "equal"), (3000, "specials")])
 def test_centered_rank_bit_exact(evo, pop, kind):
