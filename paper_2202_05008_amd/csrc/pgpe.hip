@@ -97,19 +97,18 @@ __device__ __forceinline__ void store_row4(float* row, int col, int P, const flo
 // which is how memory takes them best (6.5 TB/s where rows are whole cache lines).  A smaller population stays in the
 // caches for the evaluation, which reads it next: ordinary stores; and because a line at the border of two workgroups
 // is written by both, workgroups whose numbers are 8 apart, which run on the same die and share its L2, take
-// neighbouring pieces of a row, 2^run_log2 of them (64, or 8 where the grid is so small that runs of 64 leave dies
-// without one).  P = 45130, 500 members (90 MB): streaming in order 20.3 us, this 15.0 us.  P = 145674, 1024 members
+// neighbouring pieces of a row, eight of them (kAskRun; longer runs leave dies of a small grid without any).  P = 45130, 500 members (90 MB): streaming in order 20.3 us, this 15.0 us.  P = 145674, 1024 members
 // (600 MB): 127 us streaming, 110 us like this, but the evaluation behind it then pays for the write-back (the
 // generation takes the same); P = 300007, 250 members (300 MB): 65 and 61 us, the generation 174 and 182 us.
+constexpr unsigned kAskRun = 8;
 template <bool STREAM>
-__device__ __forceinline__ void ask_block(unsigned xblocks, unsigned run_log2, unsigned& xb, unsigned& k) {
+__device__ __forceinline__ void ask_block(unsigned xblocks, unsigned& xb, unsigned& k) {
   if (STREAM) {  // grid (xblocks, N): the same order as one row of workgroup numbers, which has room for 128 GiB only
     k = blockIdx.y, xb = blockIdx.x;
     return;
   }
-  unsigned b = blockIdx.x;
-  const unsigned die = b & 7u, i = b >> 3, run = 1u << run_log2;
-  b = ((i >> run_log2) << (run_log2 + 3)) + (die << run_log2) + (i & (run - 1u));
+  const unsigned die = blockIdx.x & 7u, i = blockIdx.x >> 3;
+  const unsigned b = (8 * (i / kAskRun) + die) * kAskRun + i % kAskRun;
   k = b / xblocks, xb = b - k * xblocks;
 }
 
@@ -118,11 +117,11 @@ __device__ __forceinline__ void ask_block(unsigned xblocks, unsigned run_log2, u
 template <bool STREAM>
 __global__ __launch_bounds__(256) void ask_kernel(const float* __restrict__ mu, const float* __restrict__ sigma,
                                                   float* __restrict__ params, int P, int nquads, unsigned xblocks,
-                                                  unsigned N, unsigned run_log2, uint32_t gen_host,
+                                                  unsigned N, uint32_t gen_host,
                                                   const uint32_t* __restrict__ gen_dev, uint32_t key0, uint32_t key1) {
   const uint32_t gen = gen_dev ? *gen_dev : gen_host;  // uniform: the device copy when the state keeps one
   unsigned xb, k;
-  ask_block<STREAM>(xblocks, run_log2, xb, k);
+  ask_block<STREAM>(xblocks, xb, k);
   const int q = xb * 256 + threadIdx.x;
   if (q >= nquads || k >= N) return;
   const int col = q * 4;
@@ -147,11 +146,11 @@ __global__ __launch_bounds__(256) void ask_kernel(const float* __restrict__ mu, 
 template <bool WHOLE, bool STREAM>
 __global__ __launch_bounds__(256) void ask_bf16_kernel(const float* __restrict__ mu, const float* __restrict__ sigma,
                                                        uint16_t* __restrict__ params, int P, int noct, unsigned xblocks,
-                                                       unsigned N, unsigned run_log2, uint32_t gen_host,
+                                                       unsigned N, uint32_t gen_host,
                                                        const uint32_t* __restrict__ gen_dev, uint32_t key0, uint32_t key1) {
   const uint32_t gen = gen_dev ? *gen_dev : gen_host;
   unsigned xb, k;
-  ask_block<STREAM>(xblocks, run_log2, xb, k);
+  ask_block<STREAM>(xblocks, xb, k);
   const int o = xb * 256 + threadIdx.x;
   if (o >= noct || k >= N) return;
   const int col = o * 8;
@@ -1300,8 +1299,7 @@ extern "C" int pgpe_ask(pgpe_state* st, uint64_t seed, int32_t pop, void* params
   const unsigned xblocks = static_cast<unsigned>((pieces + 255) / 256);
   const bool stream_stores = size * pop * P > (size_t(256) << 20);
   const size_t blocks = static_cast<size_t>(xblocks) * N;
-  const unsigned run_log2 = blocks >= 32768 ? 6 : 3;
-  const size_t run = size_t(8) << run_log2;
+  const size_t run = 8 * kAskRun;
   const dim3 grid = stream_stores ? dim3(xblocks, static_cast<unsigned>(N))
                                   : dim3(static_cast<unsigned>((blocks + run - 1) / run * run));
   hipStream_t s = as_stream(stream);
@@ -1309,7 +1307,7 @@ extern "C" int pgpe_ask(pgpe_state* st, uint64_t seed, int32_t pop, void* params
   const uint32_t* gen_dev = device_generation(st);
 #define EVO_ASK(KERNEL, T)                                                                                            \
   hipLaunchKernelGGL((KERNEL), grid, dim3(256), 0, s, st->mu, st->sigma, static_cast<T*>(params_dev), P, pieces, xblocks, \
-                     static_cast<unsigned>(N), run_log2, st->t, gen_dev, k0, k1)
+                     static_cast<unsigned>(N), st->t, gen_dev, k0, k1)
   if (dtype == EVO_F32) {
     if (stream_stores) EVO_ASK(ask_kernel<true>, float);
     else EVO_ASK(ask_kernel<false>, float);
