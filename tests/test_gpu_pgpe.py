@@ -101,6 +101,31 @@ def test_ask_bf16(evo, P, pop):
     assert (np.abs(got - ref32) <= np.abs(ref32) * 2.0 ** -8 + floor).all()  # half an ulp from the fp32 value
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("P,pop", [(300007, 500),              # streamed (above 256 MiB in both types), rows on any element
+                                   (86544, 2048),              # streamed, rows of whole 16-byte pieces
+                                   (45130, 500), (2051, 2050),  # kept in the caches: thousands of workgroups in the order of the dies
+                                   (9, 130)])                  # one workgroup per pair, the last eight incomplete
+def test_ask_every_row(evo, P, pop, dtype):
+    """Each row of large populations against mu + sigma z; nothing is written beyond them."""
+    mu0 = gen.initial_mu(12, P)
+    es = evo.PGPE(evo.make_pgpe_config(P=P, pop_max=pop), mu0)
+    bf16 = dtype == "bf16"
+    buf = torch.full((pop * P + 64,), float("nan"), dtype=torch.bfloat16 if bf16 else torch.float32, device="cuda")
+    params = buf[:pop * P].view(pop, P)
+    es.ask(13, pop, params, evo.EVO_BF16 if bf16 else evo.EVO_F32)
+    mu, z = dev(mu0).double(), torch.empty(-(-P // 4) * 4, device="cuda")
+    worst = torch.zeros((), dtype=torch.float64, device="cuda")
+    for k in range(pop // 2):
+        evo.evo_philox_normal(13, 1, k, 0, len(z) // 4, 0, z)
+        step = es.sigma.double() * z[:P].double()
+        for row, ref in ((2 * k, mu + step), (2 * k + 1, mu - step)):
+            # (a NaN, that is a parameter not written, counts as infinitely far)
+            worst = torch.maximum(worst, ((params[row].double() - ref).abs() / ref.abs().clamp_min(1e-30)).nan_to_num(1e9).max())
+    assert worst <= (2.0 ** -8 if bf16 else 2.0 ** -23) * 1.001          # one rounding of the 64-bit value
+    assert torch.isnan(buf[pop * P:]).all()
+
+
 def test_ask_population_of_128_gib(evo):
     """2^24 workgroups: the size from which one row of workgroups no longer fits a launch (fewer than 2^32 threads)."""
     P, pop = 1 << 24, 2048
