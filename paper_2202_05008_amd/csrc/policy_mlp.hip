@@ -12,7 +12,7 @@
 // scaled fp16 splits (mlp_f32_mfma_kernel, for deep wide networks on few samples mlp_f32_short_kernel; split16.h: three
 // v_mfma_f32_16x16x32_f16 per product, fp32 accumulation);
 // narrower networks on the fp32 matrix instruction (mlp_f32_units_kernel); what the one-launch generation takes too stays
-// on the vector ALU (mlp_f32_kernel, bound by launch latency at those sizes).
+// on the vector ALU (mlp_f32_kernel, bound by launch latency at those sizes).  The last two give the same bits.
 #include "kernels.h"
 #include "mlp_f32_body.h"
 #include "split16.h"
@@ -711,17 +711,18 @@ __global__ __launch_bounds__(64 * kMfmaWaves, 2) void mlp_f32_short_kernel(MlpAr
 
 // ---- the fp32 matrix form ------------------------------------------------------------------------------
 // Networks of widths up to 64 run on v_mfma_f32_16x16x4_f32: fp32 operands as they are, so there is
-// nothing to split or scale and the error is that of fp32 multiply-adds.  Workgroup = (member, up to 1024 samples),
-// eight waves; the member's weights go to LDS once, in operand order, and then every wave takes tiles of sixteen samples
-// through the whole network by itself: one barrier in all.  A layer is computed transposed (rows = neurons, columns =
-// samples): a lane ends up with four consecutive neurons 16 t + 4 q + i of one sample (lane group q), and a product
-// over the four k {16 t + 4 q + i : q} takes exactly the lane's value i of tile t as its B operand -- a layer's outputs
-// are the next one's operands where they are.  A unit is a 16 x 16 block of weights, one 16-byte LDS read per lane
-// for four products.
-// Bound by the fp32 matrix instruction (32 cycles for 2 kFLOP) plus the activations, which it does not overlap with:
-// 20-50-60-5, 1000 members of 300 samples 225 us on the vector form, 65 here; 60-40-8, 1000 of 500 248 -> 57 us.  Two
-// accumulators per tile: 99 -> 65 us together with the next samples' loads ahead of the layers, and errors of 1.2e-7
-// instead of 1.5e-7.
+// nothing to split or scale.  The instruction adds its four products one after the other, each as one fused
+// multiply-add, so a sum that starts from the bias and runs over k in its order has the bits of the vector form, and the
+// outputs and losses of the two forms are the same bit for bit.
+// Workgroup = (member, up to 1024 samples), eight waves; the member's weights go to LDS once, in operand order, and then
+// every wave takes tiles of sixteen samples through the whole network by itself.  A layer is computed transposed (rows =
+// neurons, columns = samples); row 4 q + i of a tile is neuron 16 t + 4 i + q, so that a lane (group q) ends up with those
+// four of one sample, and a product over the four k 16 t + 4 i + (0..3) takes exactly the lane's value i of tile t as its
+// B operand -- a layer's outputs are the next one's operands where they are.  A unit is a 16 x 16 block of weights, one
+// 16-byte LDS read per lane for four products; two neuron tiles at a time are two chains of sums.
+// Bound by the fp32 matrix instruction (32 cycles for 2 kFLOP) plus the activations, which it does not overlap with.
+// get_actions, vector form and here: 20-50-60-5 tanh, 1000 members of 300 samples 226 and 68 us; 60-40-8 ReLU, 1000 of
+// 500 245 and 54 us; 63-64-64, 1000 of 300 222 and 64 us.
 constexpr int kF32UnitB = 64 * 16;
 constexpr int kF32MaxGroup = 16;        // pieces of 64 samples per workgroup
 constexpr int kF32MaxWidth = 64;
@@ -736,9 +737,71 @@ __host__ __device__ inline int f32_out_tiles(const MlpShape& sh) {
   for (int l = 0; l < sh.n_layers; ++l) n += (sh.dims[l + 1] + 15) >> 4;
   return n;
 }
-// weights, one unit that is read ahead and not used, biases, one loss sum per sixteen samples
-inline size_t f32_lds_bytes(const MlpShape& sh) {
-  return static_cast<size_t>(f32_units(sh) + 1) * kF32UnitB + f32_out_tiles(sh) * 16 * sizeof(float) + 4 * kF32MaxGroup * sizeof(float);
+// weights, one unit that is read ahead and not used, biases, one loss per sample
+inline size_t f32_lds_bytes(const MlpShape& sh, int group) {
+  return static_cast<size_t>(f32_units(sh) + 1) * kF32UnitB + (f32_out_tiles(sh) * 16 + group * kMlpTile) * sizeof(float);
+}
+
+// v[i] of lane group q <-> v[q] of lane group i (groups of sixteen lanes).
+__device__ __forceinline__ void transpose_groups(float (&v)[4]) {
+  uint32_t u[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) u[i] = __float_as_uint(v[i]);
+  const auto a = __builtin_amdgcn_permlane32_swap(u[0], u[2], false, false), b = __builtin_amdgcn_permlane32_swap(u[1], u[3], false, false);
+  const auto c = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false), d = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
+  v[0] = __uint_as_float(c[0]), v[1] = __uint_as_float(c[1]), v[2] = __uint_as_float(d[0]), v[3] = __uint_as_float(d[1]);
+}
+// The values of the four lane groups, in every group.
+__device__ __forceinline__ void gather_groups(float v, float (&all)[4]) {
+  const uint32_t u = __float_as_uint(v);
+  const auto h = __builtin_amdgcn_permlane32_swap(u, u, false, false);            // groups (0 1 0 1), (2 3 2 3)
+  const auto a = __builtin_amdgcn_permlane16_swap(h[0], h[0], false, false), b = __builtin_amdgcn_permlane16_swap(h[1], h[1], false, false);
+  all[0] = __uint_as_float(a[0]), all[1] = __uint_as_float(a[1]), all[2] = __uint_as_float(b[0]), all[3] = __uint_as_float(b[1]);
+}
+
+// Loss of the lane's sample from its outputs, v[t][i] = neuron 16 t + 4 i + q, with the vector form's arithmetic (sums over
+// the outputs in their order); the same in all four groups.
+template <int NTM, int LOSS>
+__device__ __forceinline__ float f32_sample_loss(const MlpArgs& a, int member, int b, bool live, int A, int q, const float (&v)[NTM][4]) {
+  float sum = 0.f, mx = -__builtin_inff(), hit = 0.f;
+  const int y = LOSS == LOSS_CE && live ? min(max(static_cast<const int32_t*>(a.target)[b], 0), A - 1) : 0;  // labels outside [0, A) are clamped
+  if (LOSS == LOSS_CE) {
+#pragma unroll
+    for (int t = 0; t < NTM; ++t) {
+      if (16 * t >= A) break;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int o = 16 * t + 4 * i + q;
+        if (o < A) mx = fmaxf(mx, v[t][i]);
+        if (o == y) hit = v[t][i];
+      }
+    }
+    float all[4];
+    gather_groups(mx, all);
+    mx = fmaxf(fmaxf(all[0], all[1]), fmaxf(all[2], all[3]));
+    gather_groups(hit, all);
+    hit = (all[0] + all[1]) + (all[2] + all[3]);    // three of them are zero
+  }
+  const float* tg = static_cast<const float*>(a.target) + (LOSS == LOSS_MSE && live ? (static_cast<size_t>(member) * a.B + b) * A : 0);
+#pragma unroll
+  for (int t = 0; t < NTM; ++t) {
+    if (16 * t >= A) break;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (16 * t + 4 * i >= A) break;
+      const int o = 16 * t + 4 * i + q;
+      float all[4];
+      if (LOSS == LOSS_CE) {
+        gather_groups(o < A ? expf(v[t][i] - mx) : 0.f, all);
+        sum = (((sum + all[0]) + all[1]) + all[2]) + all[3];
+      } else {
+        gather_groups(o < A && live ? v[t][i] - tg[o] : 0.f, all);
+        sum = fmaf(all[3], all[3], fmaf(all[2], all[2], fmaf(all[1], all[1], fmaf(all[0], all[0], sum))));
+      }
+    }
+  }
+  if (LOSS == LOSS_CE) sum = (mx + logf(sum)) - hit;
+  return live ? sum : 0.f;
 }
 
 template <int LOSS>
@@ -755,7 +818,7 @@ __global__ __launch_bounds__(512, 4) void mlp_f32_units_kernel(MlpArgs a, int gr
   if (member >= a.pop) return;
   const int n_layers = a.sh.n_layers, units = f32_units(a.sh);
   float* bias_s = reinterpret_cast<float*>(lds_raw + static_cast<size_t>(units + 1) * kF32UnitB);
-  float* red_s = bias_s + 16 * f32_out_tiles(a.sh);
+  float* loss_s = bias_s + 16 * f32_out_tiles(a.sh);
   const float* theta = a.params + static_cast<size_t>(member) * a.sh.P;
   const float* obs = a.obs + static_cast<size_t>(member) * a.obs_stride;
 
@@ -771,10 +834,10 @@ __global__ __launch_bounds__(512, 4) void mlp_f32_units_kernel(MlpArgs a, int gr
         float v[4][4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int u = u0 + 8 * r, nt = u / KT, kt = u - nt * KT, n = 16 * nt + j;
-          const unsigned at = n < N ? 4u * static_cast<unsigned>((16 * kt + 4 * q) * N + n) : 0x40000000u;
+          const int u = u0 + 8 * r, nt = u / KT, kt = u - nt * KT, n = 16 * nt + 4 * (j & 3) + (j >> 2);
+          const unsigned at = n < N ? 4u * static_cast<unsigned>((16 * kt + q) * N + n) : 0x40000000u;
 #pragma unroll
-          for (int i = 0; i < 4; ++i) v[r][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(w, at + 4u * N * i, 0, 0));
+          for (int i = 0; i < 4; ++i) v[r][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(w, at + 16u * N * i, 0, 0));
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -784,7 +847,10 @@ __global__ __launch_bounds__(512, 4) void mlp_f32_units_kernel(MlpArgs a, int gr
                 make_float4(v[r][0], v[r][1], v[r][2], v[r][3]);
         }
       }
-      if (tid < 16 * NT) bias_s[16 * tile0 + tid] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(wb, 4u * tid, 0, 0));
+      if (tid < 16 * NT) {
+        const unsigned n = (tid & ~15) + 4 * (tid & 3) + ((tid >> 2) & 3);
+        bias_s[16 * tile0 + tid] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(wb, 4u * n, 0, 0));
+      }
       off += K * N + N;
       unit0 += KT * NT;
       tile0 += NT;
@@ -794,12 +860,14 @@ __global__ __launch_bounds__(512, 4) void mlp_f32_units_kernel(MlpArgs a, int gr
   const bool wide_obs = (D & 3) == 0 && (reinterpret_cast<uintptr_t>(obs) & 15u) == 0;  // then every row starts on 16 bytes
   const int pieces = min(group, a.tiles - first), s_end = min(a.B, (first + pieces) * kMlpTile);
   float x[NTM][4], ahead[NTM][4];
-  // sixteen samples from b0 on, laid out as a layer's outputs are; zeros beyond the observation and the batch
+  // sixteen samples from b0 on, laid out as a layer's outputs are (16-byte loads: once they are transposed); zeros beyond
+  // the observation and the batch
   auto observe = [&](int b0) {
     const auto rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(obs + static_cast<size_t>(b0) * D), 0,
                                                         4 * min(s_end - b0, 16) * D, 0x00020000);
 #pragma unroll
     for (int t = 0; t < NTM; ++t) {
+      if (16 * t >= D) break;
       const int d = 16 * t + 4 * q;
       if (wide_obs) {
         const auto v = __builtin_amdgcn_raw_buffer_load_b128(rows, d < D ? 4u * (j * D + d) : 0x40000000u, 0, 0);
@@ -807,8 +875,10 @@ __global__ __launch_bounds__(512, 4) void mlp_f32_units_kernel(MlpArgs a, int gr
         for (int i = 0; i < 4; ++i) ahead[t][i] = __uint_as_float(v[i]);
       } else {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-          ahead[t][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rows, d + i < D ? 4u * (j * D + d + i) : 0x40000000u, 0, 0));
+        for (int i = 0; i < 4; ++i) {
+          const int f = 16 * t + 4 * i + q;
+          ahead[t][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rows, f < D ? 4u * (j * D + f) : 0x40000000u, 0, 0));
+        }
       }
     }
   };
@@ -817,35 +887,18 @@ __global__ __launch_bounds__(512, 4) void mlp_f32_units_kernel(MlpArgs a, int gr
   __syncthreads();
   for (; b0 < s_end; b0 += 16 * 8) {
 #pragma unroll
-    for (int t = 0; t < NTM; ++t)
+    for (int t = 0; t < NTM; ++t) {
+      if (wide_obs && 16 * t < D) transpose_groups(ahead[t]);
 #pragma unroll
       for (int i = 0; i < 4; ++i) x[t][i] = ahead[t][i];
+    }
     if (b0 + 16 * 8 < s_end) observe(b0 + 16 * 8);  // the wave's next sixteen are on their way meanwhile
     const unsigned char* src = lds_raw + 16 * lane;
     const float* bias = bias_s + 4 * q;
     for (int l = 0; l < n_layers; ++l) {
       const int K = a.sh.dims[l], N = a.sh.dims[l + 1], act = a.sh.act[l], KT = (K + 15) >> 4, NT = (N + 15) >> 4;
       float y[NTM][4];
-#pragma unroll
-      for (int t = 0; t < NTM; ++t) {
-        if (t >= NT) continue;
-        const float4 b4 = *reinterpret_cast<const float4*>(bias);
-        floatx4m acc = {b4.x, b4.y, b4.z, b4.w}, odd = {0.f, 0.f, 0.f, 0.f};  // two chains: shorter sums, more in flight
-        float4 w = *reinterpret_cast<const float4*>(src);
-#pragma unroll
-        for (int kt = 0; kt < NTM; ++kt) {
-          if (kt < KT) {
-            const float4 w0 = w;
-            src += kF32UnitB;
-            w = *reinterpret_cast<const float4*>(src);  // one unit ahead
-            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w0.x, x[kt][0], acc, 0, 0, 0);
-            odd = __builtin_amdgcn_mfma_f32_16x16x4f32(w0.y, x[kt][1], odd, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w0.z, x[kt][2], acc, 0, 0, 0);
-            odd = __builtin_amdgcn_mfma_f32_16x16x4f32(w0.w, x[kt][3], odd, 0, 0, 0);
-          }
-        }
-        bias += 16;
-        acc += odd;
+      auto finish = [&](int t, const floatx4m& acc) {
         if (act == EVO_ACT_TANH) {
 #pragma unroll
           for (int i = 0; i < 4; ++i) y[t][i] = tanh_fast_accurate(acc[i]);
@@ -858,8 +911,37 @@ __global__ __launch_bounds__(512, 4) void mlp_f32_units_kernel(MlpArgs a, int gr
         }
         if (16 * t + 16 > N) {  // neurons that do not exist must not hand a NaN on (zero weights x an infinite input)
 #pragma unroll
-          for (int i = 0; i < 4; ++i) y[t][i] = 16 * t + 4 * q + i < N ? y[t][i] : 0.f;
+          for (int i = 0; i < 4; ++i) y[t][i] = 16 * t + 4 * i + q < N ? y[t][i] : 0.f;
         }
+      };
+#pragma unroll
+      for (int t = 0; t < NTM; t += 2) {
+        if (t >= NT) continue;
+        const bool two = t + 1 < NT;
+        const unsigned char* src1 = two ? src + KT * kF32UnitB : src;
+        const float4 b4 = *reinterpret_cast<const float4*>(bias), c4 = *reinterpret_cast<const float4*>(bias + (two ? 16 : 0));
+        floatx4m acc = {b4.x, b4.y, b4.z, b4.w}, acc1 = {c4.x, c4.y, c4.z, c4.w};
+        float4 w = *reinterpret_cast<const float4*>(src), w1 = *reinterpret_cast<const float4*>(src1);
+#pragma unroll
+        for (int kt = 0; kt < NTM; ++kt) {
+          if (kt < KT) {
+            const float4 v = w, v1 = w1;
+            src += kF32UnitB, src1 += kF32UnitB;
+            w = *reinterpret_cast<const float4*>(src), w1 = *reinterpret_cast<const float4*>(src1);  // one unit ahead
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(v.x, x[kt][0], acc, 0, 0, 0);
+            if (two) acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(v1.x, x[kt][0], acc1, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(v.y, x[kt][1], acc, 0, 0, 0);
+            if (two) acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(v1.y, x[kt][1], acc1, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(v.z, x[kt][2], acc, 0, 0, 0);
+            if (two) acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(v1.z, x[kt][2], acc1, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(v.w, x[kt][3], acc, 0, 0, 0);
+            if (two) acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(v1.w, x[kt][3], acc1, 0, 0, 0);
+          }
+        }
+        finish(t, acc);
+        if (two) finish(t + 1, acc1);
+        src = two ? src1 : src;
+        bias += two ? 32 : 16;
       }
 #pragma unroll
       for (int t = 0; t < NTM; ++t)
@@ -868,24 +950,33 @@ __global__ __launch_bounds__(512, 4) void mlp_f32_units_kernel(MlpArgs a, int gr
           if (t < NT) x[t][i] = y[t][i];
     }
     const int b = b0 + j;
-    const float loss = mlp_finish<NTM, LOSS>(a, member, b, b < s_end, A, q, x);
-    if (LOSS != LOSS_NONE && lane == 0) red_s[(b0 - first * kMlpTile) >> 4] = loss;
+    if (LOSS == LOSS_NONE) {
+#pragma unroll
+      for (int t = 0; t < NTM; ++t) {
+        if (16 * t >= A) break;
+        transpose_groups(x[t]);
+      }
+      mlp_finish<NTM, LOSS>(a, member, b, b < s_end, A, q, x);
+    } else {
+      const float loss = f32_sample_loss<NTM, LOSS>(a, member, b, b < s_end, A, q, x);
+      if (q == 0) loss_s[b - first * kMlpTile] = loss;
+    }
   }
   if (LOSS == LOSS_NONE) return;
   __syncthreads();
-  if (tid < pieces) {   // one partial sum per 64 samples
-    float sum = 0.f;
-    for (int k = 0; k < 4; ++k)
-      if ((first + tid) * kMlpTile + 16 * k < a.B) sum += red_s[4 * tid + k];
-    a.partial[static_cast<size_t>(member) * a.tiles + first + tid] = sum;
+  for (int piece = wave; piece < pieces; piece += 8) {   // one partial sum per 64 samples, added as the vector form does
+    const int at = piece * kMlpTile + lane;
+    const float loss = wave_sum(first * kMlpTile + at < s_end ? loss_s[at] : 0.f);
+    if (lane == 0) a.partial[static_cast<size_t>(member) * a.tiles + first + piece] = loss;
   }
 }
 
 // Any fan-in of 64 or more: the split form.  All narrower and no layer above 64: the fp32 matrix form, but for a problem
-// that the one-launch generation takes too (at most 8192 parameters, 512 members, 4096 pieces of 64 samples): that one
-// runs the vector body, and the two ways give the same bits.  (The split form is faster on narrow networks as well --
-// 20-50-60-5, 1000 members of 300 samples 64 us -- but its operands' 22 bits show there: 8-16-3 1.2e-7 from 64-bit
-// results where fp32 operands give 0.8e-7; from sums over 64 terms on the accumulation outweighs them.)
+// that the one-launch generation takes too (at most 8192 parameters, 512 members, 4096 pieces of 64 samples).  The vector
+// form gives the same bits as the fp32 matrix form, so a member's results don't depend on the population around it.  (The
+// split form is faster on narrow networks as well -- 20-50-60-5, 1000 members of 300 samples 64 us -- but its operands' 22
+// bits show there: 8-16-3 1.2e-7 from 64-bit results where fp32 operands give 0.8e-7; from sums over 64 terms on the
+// accumulation outweighs them.)
 enum MlpForm { FORM_VECTOR, FORM_SPLIT, FORM_F32 };
 static MlpForm mlp_form(const MlpShape& sh, int pop, int tiles) {
   for (int l = 0; l < sh.n_layers; ++l)
@@ -907,10 +998,10 @@ int launch_mlp_f32(const MlpShape& sh, const float* params, const float* obs, in
   const MlpForm form = mlp_form(sh, pop, a.tiles);
   if (form == FORM_F32) {
     // as large a group of samples per workgroup as leaves two workgroups per compute unit
-    const size_t lds = f32_lds_bytes(sh);
     const int64_t per = static_cast<int64_t>(pop) * a.tiles / 512;
     const int group = static_cast<int>(std::min<int64_t>(std::max<int64_t>(per, 2), std::min(a.tiles, kF32MaxGroup)));
     const int wgs = (a.tiles + group - 1) / group;
+    const size_t lds = f32_lds_bytes(sh, group);
     auto launch_units = [&](auto kern) -> int {
       if (lds > 64 * 1024) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),

@@ -107,6 +107,40 @@ def test_mlp_f32_forms_at_their_edges(evo, dims, pop, B, shared):
         assert_scalar_rel(fit[some], otasks.classify_fitness(ref, y), 1e-5, "fitness")
 
 
+@pytest.mark.parametrize("dims,acts,B,shared", [
+    ((16, 32, 4), (1, 0), 512, True), ((20, 50, 60, 5), (1, 2, 0), 300, False), ((63, 64, 64), (2, 1), 65, True),
+    ((1, 1), (0,), 1, True), ((33, 17, 64), (1, 0), 130, False), ((5, 48, 3), (2, 0), 1100, True), ((8,) * 8 + (7,), (1,) * 8, 17, True),
+    ((64, 150, 40, 5), (1, 2, 0), 300, True), ((100, 70, 9), (1, 0), 65, False)])
+def test_mlp_f32_bits_do_not_depend_on_the_population(evo, dims, acts, B, shared):
+    """A member's outputs and fitness are the same bits evaluated alone, in a few members or in a large population: which
+    kernel takes a network, and how many samples a workgroup, follows from the whole problem's size."""
+    pop = 1300
+    pd = evo.make_policy_desc(evo.EVO_POLICY_MLP, dims, acts)
+    params = dev(gen.random_params(25, pop, mlp_param_count(dims), 0.4))
+    g = torch.Generator().manual_seed(26)
+    obs = torch.randn((B, dims[0]) if shared else (pop, B, dims[0]), generator=g).cuda()
+    label = (torch.arange(B) % dims[-1]).int().cuda()
+    target = torch.randn(pop, B, dims[-1], generator=g).cuda()
+
+    def evaluate(m0, m1):
+        n, stride = m1 - m0, 0 if shared else B * dims[0]
+        p, o, t = (x[m0:m1].clone() for x in (params, obs.expand(pop, B, dims[0]), target))   # (a slice need not be aligned)
+        o = obs if shared else o
+        out, fits = torch.empty(n, B, dims[-1], device="cuda"), []
+        evo.pop_forward(pd, p, o, stride, out, n, B)
+        for kind, tg in ((evo.EVO_TASK_CLASSIFY, label), (evo.EVO_TASK_REGRESS, t)):
+            data = dict(B=B, obs=o, obs_member_stride=stride, target=tg)
+            work = torch.empty(evo.rollout_workspace_bytes(evo.make_task_desc(kind, **data), pd, n), dtype=torch.uint8, device="cuda")
+            fits.append(torch.empty(n, device="cuda"))
+            evo.rollout(evo.make_task_desc(kind, work=work, **data), pd, p, n, 1, fits[-1])
+        return out, fits[0], fits[1]
+
+    whole = evaluate(0, pop)
+    for m0, m1 in ((0, 1), (7, 39), (500, 1012), (1299, 1300)):
+        for x, y in zip(whole, evaluate(m0, m1)):
+            assert torch.equal(x[m0:m1], y)
+
+
 def test_mlp_f32_infinite_input_stays_in_its_sample(evo):
     """An infinity among the observations of one sample: the other samples, and the neurons beyond a ragged layer, see nothing of it."""
     for dims, pop in (((20, 33, 5), 513), ((70, 33, 5), 4)):
