@@ -11,8 +11,8 @@
 // Four kernels, chosen by mlp_form below: any fan-in of 64 or more runs on the matrix cores with fp32 operands as two-term
 // scaled fp16 splits (mlp_f32_mfma_kernel, for deep wide networks on few samples mlp_f32_short_kernel; split16.h: three
 // v_mfma_f32_16x16x32_f16 per product, fp32 accumulation);
-// narrower networks on the fp32 matrix instruction (mlp_f32_units_kernel); what the one-launch generation takes too stays
-// on the vector ALU (mlp_f32_kernel, bound by launch latency at those sizes).  The last two give the same bits.
+// narrower networks on the fp32 matrix instruction (mlp_f32_units_kernel) or, small ones, on the vector ALU
+// (mlp_f32_kernel).  The last two give the same bits, which are also those of the one-launch generation.
 #include "kernels.h"
 #include "mlp_f32_body.h"
 #include "split16.h"
@@ -805,16 +805,18 @@ __device__ __forceinline__ float f32_sample_loss(const MlpArgs& a, int member, i
 }
 
 template <int LOSS>
-__global__ __launch_bounds__(512, 4) void mlp_f32_units_kernel(MlpArgs a, int group) {
+__global__ __launch_bounds__(512, 4) void mlp_f32_units_kernel(MlpArgs a, int group, bool spread) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
   constexpr int NTM = kF32MaxWidth / 16;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int j = lane & 15, q = lane >> 4;
-  // consecutive workgroup numbers go to the eight dies in turn: the groups of one member, which read the same weights, 8 apart
-  const int wgs = (a.tiles + group - 1) / group;
-  const int die = blockIdx.x & 7, turn = blockIdx.x >> 3;
-  const int member = 8 * (turn / wgs) + die, first = (turn % wgs) * group;     // (in pieces of 64 samples)
+  // consecutive workgroup numbers go to the eight dies in turn: the groups of one member, which read the same weights, 8
+  // apart; fewer than 64 members (spread) have all dies work on each (20-50-60-5, one member of 100000 samples: 169 us on
+  // one die, 35 us on all)
+  const int wgs = (a.tiles + group - 1) / group, by = spread ? 1 : 8;
+  const int die = blockIdx.x % by, turn = blockIdx.x / by;
+  const int member = by * (turn / wgs) + die, first = (turn % wgs) * group;     // (in pieces of 64 samples)
   if (member >= a.pop) return;
   const int n_layers = a.sh.n_layers, units = f32_units(a.sh);
   float* bias_s = reinterpret_cast<float*>(lds_raw + static_cast<size_t>(units + 1) * kF32UnitB);
@@ -971,18 +973,30 @@ __global__ __launch_bounds__(512, 4) void mlp_f32_units_kernel(MlpArgs a, int gr
   }
 }
 
-// Any fan-in of 64 or more: the split form.  All narrower and no layer above 64: the fp32 matrix form, but for a problem
-// that the one-launch generation takes too (at most 8192 parameters, 512 members, 4096 pieces of 64 samples).  The vector
-// form gives the same bits as the fp32 matrix form, so a member's results don't depend on the population around it.  (The
-// split form is faster on narrow networks as well -- 20-50-60-5, 1000 members of 300 samples 64 us -- but its operands' 22
-// bits show there: 8-16-3 1.2e-7 from 64-bit results where fp32 operands give 0.8e-7; from sums over 64 terms on the
-// accumulation outweighs them.)
+// Any fan-in of 64 or more: the split form.  (It is fast on narrow networks as well, but its operands' 22 bits show there:
+// 8-16-3 1.2e-7 from 64-bit results where fp32 operands give 0.8e-7; from sums over 64 terms on the accumulation outweighs
+// them.)  All narrower: the fp32 matrix form where it is the faster one, else the vector form, which gives the same bits.
+// A matrix tile costs the same whether the layer fills it or not, and a wave carries sixteen samples instead of 64, so
+// small layers are the vector form's.  get_actions, vector and matrix form in us (300 sizes of 25 networks measured; the
+// rule costs at most a tenth where it misses the faster form by the vector form's measure):
+//   products per sample >= 1100: 32-32-4 (1152), 514 members of 300 samples 27 and 21, 64 of 512 11.7 and 7.8;
+//     below, 8-24-24-4 (864) 1000 of 128 17.4 and 19.5, 8-16-3 4096 of 16 13.7 and 29
+//   one piece of samples each, many members (half of a workgroup's waves have no samples) >= 1900: 16-32-32-4 (1664)
+//     2048 of 64 29 and 33 with the loss, 40-40-8 (1920) 29 and 27
+//   a width of 48 or more (the vector form keeps 512 bytes of LDS per width, few workgroups fit): 8-64-2 1000 of 128 66
+//     and 18, 60-5 514 of 64 10.3 and 7.4
+//   enough samples that set-up and latency drop out: 16-32-4 2048 of 500 (6.6e8 products) 100 and 61, 600 of 1024 (3.9e8)
+//     47 and 52 with the loss
 enum MlpForm { FORM_VECTOR, FORM_SPLIT, FORM_F32 };
-static MlpForm mlp_form(const MlpShape& sh, int pop, int tiles) {
-  for (int l = 0; l < sh.n_layers; ++l)
+static MlpForm mlp_form(const MlpShape& sh, int pop, int B) {
+  int products = 0;
+  for (int l = 0; l < sh.n_layers; ++l) {
     if (sh.dims[l] >= 64) return FORM_SPLIT;
-  const bool one_launch = sh.P <= 8192 && pop <= 512 && static_cast<int64_t>(pop) * tiles <= 4096;
-  return sh.max_width <= kF32MaxWidth && !one_launch ? FORM_F32 : FORM_VECTOR;
+    products += sh.dims[l] * sh.dims[l + 1];
+  }
+  if (sh.max_width > kF32MaxWidth) return FORM_VECTOR;
+  const bool single = B <= kMlpTile && pop > 1024;
+  return sh.max_width >= 48 || products >= (single ? 1900 : 1100) || 1.0 * products * pop * B >= 6e8 ? FORM_F32 : FORM_VECTOR;
 }
 
 int launch_mlp_f32(const MlpShape& sh, const float* params, const float* obs, int64_t obs_stride, int pop, int B,
@@ -995,13 +1009,14 @@ int launch_mlp_f32(const MlpShape& sh, const float* params, const float* obs, in
   a.tiles = (B + kMlpTile - 1) / kMlpTile;
   a.pop = pop;
   const dim3 grid(a.tiles, pop);
-  const MlpForm form = mlp_form(sh, pop, a.tiles);
+  const MlpForm form = mlp_form(sh, pop, B);
   if (form == FORM_F32) {
     // as large a group of samples per workgroup as leaves two workgroups per compute unit
     const int64_t per = static_cast<int64_t>(pop) * a.tiles / 512;
     const int group = static_cast<int>(std::min<int64_t>(std::max<int64_t>(per, 2), std::min(a.tiles, kF32MaxGroup)));
     const int wgs = (a.tiles + group - 1) / group;
     const size_t lds = f32_lds_bytes(sh, group);
+    const bool spread = pop < 64;
     auto launch_units = [&](auto kern) -> int {
       if (lds > 64 * 1024) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -1009,7 +1024,7 @@ int launch_mlp_f32(const MlpShape& sh, const float* params, const float* obs, in
         if (e != hipSuccess) (void)hipGetLastError();
         EVO_REQUIRE(e == hipSuccess, EVO_ERR_HIP, "hipFuncSetAttribute failed: %s", hipGetErrorString(e));
       }
-      hipLaunchKernelGGL(kern, dim3(8 * ((pop + 7) / 8) * wgs), dim3(512), lds, s, a, group);
+      hipLaunchKernelGGL(kern, dim3((spread ? pop : (pop + 7) / 8 * 8) * wgs), dim3(512), lds, s, a, group, spread);
       return check_launch("mlp_f32_units_kernel");
     };
     if (loss == LOSS_NONE) return launch_units(mlp_f32_units_kernel<LOSS_NONE>);
