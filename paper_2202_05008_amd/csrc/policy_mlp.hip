@@ -814,9 +814,8 @@ __global__ __launch_bounds__(512, 4) void mlp_f32_units_kernel(MlpArgs a, int gr
   // consecutive workgroup numbers go to the eight dies in turn: the groups of one member, which read the same weights, 8
   // apart; fewer than 64 members (spread) have all dies work on each (20-50-60-5, one member of 100000 samples: 169 us on
   // one die, 35 us on all)
-  const int wgs = (a.tiles + group - 1) / group, by = spread ? 1 : 8;
-  const int die = blockIdx.x % by, turn = blockIdx.x / by;
-  const int member = by * (turn / wgs) + die, first = (turn % wgs) * group;     // (in pieces of 64 samples)
+  const int by = spread ? 1 : 8;
+  const int member = by * blockIdx.y + blockIdx.x % by, first = blockIdx.x / by * group;     // (in pieces of 64 samples)
   if (member >= a.pop) return;
   const int n_layers = a.sh.n_layers, units = f32_units(a.sh);
   float* bias_s = reinterpret_cast<float*>(lds_raw + static_cast<size_t>(units + 1) * kF32UnitB);
@@ -1024,7 +1023,8 @@ int launch_mlp_f32(const MlpShape& sh, const float* params, const float* obs, in
         if (e != hipSuccess) (void)hipGetLastError();
         EVO_REQUIRE(e == hipSuccess, EVO_ERR_HIP, "hipFuncSetAttribute failed: %s", hipGetErrorString(e));
       }
-      hipLaunchKernelGGL(kern, dim3((spread ? pop : (pop + 7) / 8 * 8) * wgs), dim3(512), lds, s, a, group, spread);
+      // (in two dimensions: one has room for fewer than 2^32 threads, 8.6e9 samples of all members)
+      hipLaunchKernelGGL(kern, spread ? dim3(wgs, pop) : dim3(8 * wgs, (pop + 7) / 8), dim3(512), lds, s, a, group, spread);
       return check_launch("mlp_f32_units_kernel");
     };
     if (loss == LOSS_NONE) return launch_units(mlp_f32_units_kernel<LOSS_NONE>);

@@ -141,6 +141,33 @@ def test_mlp_f32_bits_do_not_depend_on_the_population(evo, dims, acts, B, shared
             assert torch.equal(x[m0:m1], y)
 
 
+def test_mlp_f32_more_workgroups_than_one_grid_dimension_takes(evo):
+    """65528 members of 131200 samples on the fp32 matrix form are 2^32 threads and more; the members' fitness is that of
+    a few of them evaluated by themselves."""
+    dims, pop, B = (48, 2), 65528, 131200
+    pd = evo.make_policy_desc(evo.EVO_POLICY_MLP, dims, (0,))
+    g = torch.Generator(device="cuda").manual_seed(28)
+    params = torch.randn(pop, mlp_param_count(dims), generator=g, device="cuda")
+    obs = torch.randn(B, 48, generator=g, device="cuda")
+    label = (torch.arange(B, device="cuda") % 2).int()
+
+    def fitness(p):
+        data = dict(B=B, obs=obs, target=label)
+        n = len(p)
+        work = torch.empty(evo.rollout_workspace_bytes(evo.make_task_desc(evo.EVO_TASK_CLASSIFY, **data), pd, n), dtype=torch.uint8, device="cuda")
+        fit = torch.full((n,), float("nan"), device="cuda")
+        evo.rollout(evo.make_task_desc(evo.EVO_TASK_CLASSIFY, work=work, **data), pd, p, n, 1, fit)
+        return fit
+
+    whole = fitness(params)
+    assert not torch.isnan(whole).any()
+    some = torch.tensor([0, 7, 8, 4095, 32768, 65519, 65520, 65527], device="cuda")
+    assert torch.equal(whole[some], fitness(params[some].contiguous()))
+    w, b = params[some, :96].double().view(-1, 48, 2), params[some, 96:].double()
+    ref = torch.stack([-torch.nn.functional.cross_entropy(obs.double() @ w[m] + b[m], label.long()) for m in range(len(some))])
+    assert ((whole[some].double() - ref).abs() <= 1e-5 * ref.abs()).all()
+
+
 def test_mlp_f32_infinite_input_stays_in_its_sample(evo):
     """An infinity among the observations of one sample: the other samples, and the neurons beyond a ragged layer, see nothing of it."""
     for dims, pop in (((20, 33, 5), 513), ((70, 33, 5), 4)):
