@@ -9,8 +9,8 @@
 // output neurons, whose weights W[k][o..o+3] are contiguous and wave-uniform (scalar loads).
 //
 // Four kernels, chosen by mlp_form below: any fan-in of 64 or more runs on the matrix cores with fp32 operands as two-term
-// scaled fp16 splits (mlp_f32_mfma_kernel, for deep wide networks on few samples mlp_f32_short_kernel; split16.h: three
-// v_mfma_f32_16x16x32_f16 per product, fp32 accumulation);
+// scaled fp16 splits (mlp_f32_mfma_kernel or, the same bits, mlp_f32_short_kernel for wide layers and few workgroups;
+// split16.h: three v_mfma_f32_16x16x32_f16 per product, fp32 accumulation);
 // narrower networks on the fp32 matrix instruction (mlp_f32_units_kernel) or, small ones, on the vector ALU
 // (mlp_f32_kernel).  The last two give the same bits, which are also those of the one-launch generation.
 #include "kernels.h"
@@ -54,25 +54,24 @@ constexpr int kMfmaMaxWidth = 256;             // fan-in and fan-out of a layer
 constexpr int kMfmaWaves = 8;
 constexpr int kMfmaUnitB = 2 * 64 * 16;        // two terms x 64 lanes x 16 bytes
 
-// What follows the last layer on sixteen samples of a wave: lanes j, j + 16, j + 32, j + 48 hold sample b's outputs,
-// held[t][i] = neuron 16 t + 4 q + i.  Writes them, or returns the loss sum of the wave's live samples in every lane.
-template <int NTM, int LOSS>
-__device__ __forceinline__ float mlp_finish(const MlpArgs& a, int member, int b, bool live, int A, int q,
-                                            const float (&held)[NTM][4]) {
+// What follows the last layer on sixteen samples of a wave: lanes j, j + 16, j + 32, j + 48 have sample b's outputs,
+// out(t, i) = neuron 16 t + 4 q + i.  Writes them, or returns the loss sum of the wave's live samples in every lane.
+template <int NTM, int LOSS, int UNROLL = NTM, typename OUT>
+__device__ __forceinline__ float mlp_finish(const MlpArgs& a, int member, int b, bool live, int A, int q, OUT out) {
   if (LOSS == LOSS_NONE) {
     if (!live) return 0.f;
     float* dst = a.out + (static_cast<size_t>(member) * a.B + b) * A;
     const bool wide = (A & 3) == 0 && (reinterpret_cast<uintptr_t>(a.out) & 15u) == 0;
-#pragma unroll
+#pragma unroll UNROLL
     for (int t = 0; t < NTM; ++t) {
       if (16 * t >= A) break;
       const int o = 16 * t + 4 * q;
       if (wide) {
-        if (o < A) *reinterpret_cast<float4*>(dst + o) = make_float4(held[t][0], held[t][1], held[t][2], held[t][3]);
+        if (o < A) *reinterpret_cast<float4*>(dst + o) = make_float4(out(t, 0), out(t, 1), out(t, 2), out(t, 3));
       } else {
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-          if (o + i < A) dst[o + i] = held[t][i];
+          if (o + i < A) dst[o + i] = out(t, i);
       }
     }
     return 0.f;
@@ -82,23 +81,23 @@ __device__ __forceinline__ float mlp_finish(const MlpArgs& a, int member, int b,
     if (LOSS == LOSS_CE) {
       const int y = live ? min(max(static_cast<const int32_t*>(a.target)[b], 0), A - 1) : 0;  // labels outside [0, A) are clamped
       float mx = -__builtin_inff(), se = 0.f, hit = 0.f;
-#pragma unroll
+#pragma unroll UNROLL
       for (int t = 0; t < NTM; ++t) {
         if (16 * t >= A) break;
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-          if (16 * t + 4 * q + i < A) mx = fmaxf(mx, held[t][i]);
+          if (16 * t + 4 * q + i < A) mx = fmaxf(mx, out(t, i));
       }
       mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
       mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-#pragma unroll
+#pragma unroll UNROLL
       for (int t = 0; t < NTM; ++t) {
         if (16 * t >= A) break;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int o = 16 * t + 4 * q + i;
-          if (o < A) se += expf(held[t][i] - mx);
-          if (o == y) hit = held[t][i];
+          if (o < A) se += expf(out(t, i) - mx);
+          if (o == y) hit = out(t, i);
         }
       }
       se += __shfl_xor(se, 16, 64);
@@ -106,17 +105,41 @@ __device__ __forceinline__ float mlp_finish(const MlpArgs& a, int member, int b,
       hit += __shfl_xor(hit, 16, 64);
       hit += __shfl_xor(hit, 32, 64);
       loss = live && q == 0 ? (mx + logf(se)) - hit : 0.f;
-    } else if (live) {
-      const float* tg = static_cast<const float*>(a.target) + (static_cast<size_t>(member) * a.B + b) * A;
+    } else {
+      // the targets of eight tiles are on their way together (fetched and used one tile after the other they took 5 of the
+      // 29 us of 256-256 on 64 samples)
+      constexpr int kAhead = NTM < 8 ? NTM : 8;
+      const int first = __builtin_amdgcn_readfirstlane(b), j = b - first;
+      const float* tg = static_cast<const float*>(a.target) + (static_cast<size_t>(member) * a.B + first) * A;
+      const auto rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(tg), 0, 4 * max(0, min(a.B - first, 16)) * A, 0x00020000);
+      const bool wide = (A & 3) == 0 && (reinterpret_cast<uintptr_t>(a.target) & 15u) == 0;
+#pragma unroll UNROLL
+      for (int t0 = 0; t0 < NTM; t0 += kAhead) {
+        if (16 * t0 >= A) break;
+        float y[kAhead][4];
 #pragma unroll
-      for (int t = 0; t < NTM; ++t) {
-        if (16 * t >= A) break;
+        for (int t = 0; t < kAhead; ++t) {
+          if (16 * (t0 + t) >= A) break;
+          const int o = 16 * (t0 + t) + 4 * q;
+          if (wide) {
+            const auto v = __builtin_amdgcn_raw_buffer_load_b128(rows, o < A ? 4u * (j * A + o) : 0x40000000u, 0, 0);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int o = 16 * t + 4 * q + i;
-          if (o < A) {
-            const float d = held[t][i] - tg[o];
-            loss = fmaf(d, d, loss);
+            for (int i = 0; i < 4; ++i) y[t][i] = __uint_as_float(v[i]);
+          } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              y[t][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rows, o + i < A ? 4u * (j * A + o + i) : 0x40000000u, 0, 0));
+          }
+        }
+#pragma unroll
+        for (int t = 0; t < kAhead; ++t) {
+          if (16 * (t0 + t) >= A) break;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            if (live && 16 * (t0 + t) + 4 * q + i < A) {
+              const float d = out(t0 + t, i) - y[t][i];
+              loss = fmaf(d, d, loss);
+            }
           }
         }
       }
@@ -387,7 +410,7 @@ __global__ __launch_bounds__(64 * kMfmaWaves, KSM <= 4 ? 4 : 2) void mlp_f32_mfm
     }
   }
 
-  const float loss = works ? mlp_finish<NTM, LOSS>(a, member, b, live, a.sh.dims[n_layers], q, held) : 0.f;
+  const float loss = works ? mlp_finish<NTM, LOSS>(a, member, b, live, a.sh.dims[n_layers], q, [&](int t, int i) { return held[t][i]; }) : 0.f;
   if (LOSS == LOSS_NONE) return;
   if (lane == 0) red_s[wave] = loss;
   __syncthreads();
@@ -396,25 +419,27 @@ __global__ __launch_bounds__(64 * kMfmaWaves, KSM <= 4 ? 4 : 2) void mlp_f32_mfm
         (red_s[4 * tid] + red_s[4 * tid + 1]) + (red_s[4 * tid + 2] + red_s[4 * tid + 3]);
 }
 
-// ---- the split form for up to 64 samples a member ------------------------------------------------------------------------------
-// Three layers or more, one of them wider than 128, and at most 64 samples a member: a workgroup of the form above then
-// stages more than it computes, one chunk waiting for the other, and every wave reading its own neurons' weights is the
-// faster way (64-256-256-16, samples 64: 4096 members 514 us here, 528 there, 128 members 29 and 32; 100-200-120-10,
-// 500 members 52.4 and 53.6).  With two layers (150-140-5, 300 members of 50: 44 and 37), from 65 samples on and in layers
-// up to 128 the form above wins.
-// Workgroup = (member, tile of 64 samples), eight waves (two per SIMD).  A layer is computed
-// transposed: rows of a 16 x 16 tile are neurons (A operand: the member's weights W[k][neuron], fetched one
-// tile ahead of their use and split once per neuron tile), columns are samples (B operand: the layer's input,
-// kept in LDS as two fp16 terms [term][sample][k], one 16-byte read per term and 32 k).  A lane then ends up
-// with four consecutive neurons of one sample: bias, activation, and one 8-byte LDS store per term hand them
-// to the next layer.  Wave w takes neuron tiles w, w + 8, ...; its outputs wait in registers until every wave
-// has finished reading the layer's input, which they then overwrite.
-// Scales (powers of two, so that every finite fp32 value fits fp16's range): the weights of a neuron tile from
-// their largest magnitude; the activations of a SAMPLE from the largest magnitude among that sample's outputs
-// of the layer (in-lane maxima, two lane exchanges, one LDS word per wave and sample).  The factor of a
-// pre-activation, 1 / (sample scale x tile scale), rides in the multiply-add that adds the bias.
+// ---- the split form for few workgroups ------------------------------------------------------------------------
+// The same sums, bit for bit, shared out the other way round: a wave takes neurons instead of samples.  With few
+// workgroups, or samples for half of a workgroup's waves only, the form above is a chain through every neuron tile per
+// wave, one chunk of weights waiting for the other; here the waves work on a layer's tiles side by side, each reading its
+// own neurons' weights.  It pays from layers of 192 to 192 on, whose eight waves all have tiles, and where no fan-in is
+// ragged (clamped addresses and zeroes per weight then cost more than the other form's bounds checks).  In us, that form
+// and this one: 64-256-256-16 128 members of 64 samples 31.7 and 28.9, one member of 2000 33.6 and 29.3, 4096 of 64 529 and
+// 518; 256-256-16 one of 300 24.2 and 20.6; 64-192-192-16 1000 of 64 101 and 92; against it 240-240-16 200 of 64 25.2 and
+// 27.6, 200-200-200-20 4096 of 64 609 and 649, 256-40-10 one of 300 12.0 and 13.4.
+// Workgroup = (member, tile of 64 samples), eight waves (two per SIMD).  A layer is computed transposed: rows of a
+// 16 x 16 tile are neurons (A operand: the member's weights, fetched one tile ahead of their use and split once per neuron
+// tile), columns are samples (B operand: the layer's input, kept in LDS as two fp16 terms [term][sample][k], the eight k of
+// a lane group side by side: one 16-byte read per term and 32 k).  A lane then ends up with four consecutive neurons of one
+// sample: bias, activation, and one 8-byte LDS store per term hand them to the next layer.  Wave w takes neuron tiles
+// w, w + 8, ...; its outputs wait in registers until every wave has finished reading the layer's input, which they then
+// overwrite.  Scales as above: the weights of a neuron, the activations of a sample (in-lane maxima, two lane exchanges,
+// one LDS word per wave and sample).
 constexpr int kMfmaKSteps = kMfmaMaxWidth / 32;
 constexpr int kMfmaSlots = kMfmaMaxWidth / 16 / kMfmaWaves;  // neuron tiles per wave
+// Place of a layer's input k among a sample's: lane group q of a step has k = 16 h + 4 q + e (h = 0, 1, e = 0..3).
+__device__ __forceinline__ int short_place(int k) { return (k & ~31) + 8 * ((k >> 2) & 3) + 4 * ((k >> 4) & 1) + (k & 3); }
 
 template <int LOSS>
 __global__ __launch_bounds__(64 * kMfmaWaves, 2) void mlp_f32_short_kernel(MlpArgs a) {
@@ -423,6 +448,7 @@ __global__ __launch_bounds__(64 * kMfmaWaves, 2) void mlp_f32_short_kernel(MlpAr
   static_assert(TB == 64, "four column tiles of 16 samples");
   const int kRowB = (a.ldw + 8) * 2;       // bytes of one sample's row of one term (a.ldw: widest padded fan-in)
   const int kTermB = TB * kRowB;
+  __shared__ float red_s[4];
   unsigned char* at = lds_raw;                                    // [2][64][ldw + 8] fp16
   float* smax = reinterpret_cast<float*>(lds_raw + 2 * kTermB);   // [8][64] per wave: largest |output| of a sample
   float* us_s = smax + kMfmaWaves * TB;                                    // [64] 1 / scale of the staged observations
@@ -466,8 +492,8 @@ __global__ __launch_bounds__(64 * kMfmaWaves, 2) void mlp_f32_short_kernel(MlpAr
           uint2 lead, resid;
           split2_pair_true(sc * v[c].x, sc * v[c].y, lead.x, resid.x);
           split2_pair_true(sc * v[c].z, sc * v[c].w, lead.y, resid.y);
-          *reinterpret_cast<uint2*>(at + smp * kRowB + d * 2) = lead;
-          *reinterpret_cast<uint2*>(at + kTermB + smp * kRowB + d * 2) = resid;
+          *reinterpret_cast<uint2*>(at + smp * kRowB + short_place(d) * 2) = lead;
+          *reinterpret_cast<uint2*>(at + kTermB + smp * kRowB + short_place(d) * 2) = resid;
         }
       }
     } else {
@@ -481,8 +507,8 @@ __global__ __launch_bounds__(64 * kMfmaWaves, 2) void mlp_f32_short_kernel(MlpAr
         const float x0 = (live && d < D) ? sc * row[d] : 0.f, x1 = (live && d + 1 < D) ? sc * row[d + 1] : 0.f;
         uint32_t lead, resid;
         split2_pair_true(x0, x1, lead, resid);
-        *reinterpret_cast<uint32_t*>(at + smp * kRowB + d * 2) = lead;
-        *reinterpret_cast<uint32_t*>(at + kTermB + smp * kRowB + d * 2) = resid;
+        *reinterpret_cast<uint32_t*>(at + smp * kRowB + short_place(d) * 2) = lead;
+        *reinterpret_cast<uint32_t*>(at + kTermB + smp * kRowB + short_place(d) * 2) = resid;
       }
     }
     if (part == 0) us_s[smp] = pow2_reciprocal(sc);
@@ -492,7 +518,7 @@ __global__ __launch_bounds__(64 * kMfmaWaves, 2) void mlp_f32_short_kernel(MlpAr
 #pragma unroll
   for (int ct = 0; ct < 4; ++ct) u_s[ct] = us_s[16 * ct + j];
 
-  // A neuron tile's weights as A operands, A[row j][k = 32 s + 8 q + e] = W[k][16 nt + j], and its four biases
+  // A neuron tile's weights as A operands, A[row j][k = 32 s + 16 (e >> 2) + 4 q + (e & 3)] = W[k][16 nt + j], and its four biases
   // per lane, are fetched one tile ahead: all 64 loads of the next tile are in flight while the matrix
   // instructions of this one run.
   float raw[kMfmaKSteps][8], bias4[4];
@@ -513,18 +539,18 @@ __global__ __launch_bounds__(64 * kMfmaWaves, 2) void mlp_f32_short_kernel(MlpAr
     const int KS = (K + 31) >> 5;
     // address = a wave-uniform row pointer + an unsigned per-lane offset (no per-load vector arithmetic); only
     // a ragged last step clamps its rows per lane
-    const unsigned lane_off = 4u * static_cast<unsigned>(8 * q * N + min(16 * nt + j, N - 1));  // bytes
+    const unsigned lane_off = 4u * static_cast<unsigned>(4 * q * N + min(16 * nt + j, N - 1));  // bytes
 #pragma unroll
     for (int st = 0; st < kMfmaKSteps; ++st) {
       if (st < KS) {
         if (32 * st + 32 <= K) {
 #pragma unroll
           for (int e = 0; e < 8; ++e)
-            raw[st][e] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(W + (32 * st + e) * N) + lane_off);
+            raw[st][e] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(W + (32 * st + 16 * (e >> 2) + (e & 3)) * N) + lane_off);
         } else {
           const unsigned col = static_cast<unsigned>(min(16 * nt + j, N - 1));
 #pragma unroll
-          for (int e = 0; e < 8; ++e) raw[st][e] = W[static_cast<unsigned>(min(32 * st + 8 * q + e, K - 1) * N) + col];
+          for (int e = 0; e < 8; ++e) raw[st][e] = W[static_cast<unsigned>(min(32 * st + 16 * (e >> 2) + 4 * q + (e & 3), K - 1) * N) + col];
         }
       }
     }
@@ -550,14 +576,14 @@ __global__ __launch_bounds__(64 * kMfmaWaves, 2) void mlp_f32_short_kernel(MlpAr
     for (int slot = 0; slot < kMfmaSlots; ++slot) {
       const int nt = wave + kMfmaWaves * slot;
       if (nt >= NT) continue;
-      // ---- zeros beyond a ragged fan-in or fan-out, scale from the tile's largest magnitude, split ----
+      // ---- zeros beyond a ragged fan-in or fan-out, scale from the neuron's largest magnitude, split ----
       if ((K & 31) != 0 || 16 * nt + 16 > N) {
         const bool ok = 16 * nt + j < N;
 #pragma unroll
         for (int st = 0; st < kMfmaKSteps; ++st) {
           if (st < KS) {
 #pragma unroll
-            for (int e = 0; e < 8; ++e) raw[st][e] = (ok && 32 * st + 8 * q + e < K) ? raw[st][e] : 0.f;
+            for (int e = 0; e < 8; ++e) raw[st][e] = (ok && 32 * st + 16 * (e >> 2) + 4 * q + (e & 3) < K) ? raw[st][e] : 0.f;
           }
         }
 #pragma unroll
@@ -571,8 +597,12 @@ __global__ __launch_bounds__(64 * kMfmaWaves, 2) void mlp_f32_short_kernel(MlpAr
           for (int e = 0; e < 8; ++e) w_max = fmaxf(w_max, fabsf(raw[st][e]));
         }
       }
-      const float s_w = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(split_pow2_scale(wave_max(w_max)))));
-      const float u_w = pow2_reciprocal(s_w);
+      w_max = fmaxf(w_max, __shfl_xor(w_max, 16, 64));
+      w_max = fmaxf(w_max, __shfl_xor(w_max, 32, 64));
+      const float s_w = split_pow2_scale(w_max);
+      float u_w[4];  // 1 / scale of the neurons 4 q + i
+#pragma unroll
+      for (int i = 0; i < 4; ++i) u_w[i] = __shfl(pow2_reciprocal(s_w), 4 * q + i, 64);
       f16x8 wa[2][kMfmaKSteps];
 #pragma unroll
       for (int st = 0; st < kMfmaKSteps; ++st) {
@@ -590,21 +620,20 @@ __global__ __launch_bounds__(64 * kMfmaWaves, 2) void mlp_f32_short_kernel(MlpAr
       // ---- four sample tiles ----
 #pragma unroll
       for (int ct = 0; ct < 4; ++ct) {
-        floatx4m acc = {0.f, 0.f, 0.f, 0.f};  // all three partial products (residual terms unscaled)
+        floatx4m acc = {0.f, 0.f, 0.f, 0.f}, cross = {0.f, 0.f, 0.f, 0.f};
         const unsigned char* src = at + (16 * ct + j) * kRowB + 16 * q;
 #pragma unroll
         for (int st = 0; st < kMfmaKSteps; ++st) {
           if (st < KS) {
             const f16x8 x0 = *reinterpret_cast<const f16x8*>(src + 64 * st);
             const f16x8 x1 = *reinterpret_cast<const f16x8*>(src + kTermB + 64 * st);
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(wa[0][st], x1, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(wa[1][st], x0, acc, 0, 0, 0);
+            cross = __builtin_amdgcn_mfma_f32_16x16x32_f16(wa[0][st], x1, cross, 0, 0, 0);
             acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(wa[0][st], x0, acc, 0, 0, 0);
+            cross = __builtin_amdgcn_mfma_f32_16x16x32_f16(wa[1][st], x0, cross, 0, 0, 0);
           }
         }
-        const float u = u_s[ct] * u_w;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) held[slot][ct][i] = fmaf(acc[i], u, b4[i]);
+        for (int i = 0; i < 4; ++i) held[slot][ct][i] = fmaf(acc[i] + cross[i], u_s[ct] * u_w[i], b4[i]);
       }
       // the activation of the tile's sixteen values per lane, switched once and not per value
       auto apply = [&](auto f) {
@@ -666,7 +695,7 @@ __global__ __launch_bounds__(64 * kMfmaWaves, 2) void mlp_f32_short_kernel(MlpAr
         uint2 lead, resid;
         split2_pair_true(s_new[ct] * held[slot][ct][0], s_new[ct] * held[slot][ct][1], lead.x, resid.x);
         split2_pair_true(s_new[ct] * held[slot][ct][2], s_new[ct] * held[slot][ct][3], lead.y, resid.y);
-        unsigned char* dst = at + (16 * ct + j) * kRowB + (16 * nt + 4 * q) * 2;
+        unsigned char* dst = at + (16 * ct + j) * kRowB + short_place(16 * nt + 4 * q) * 2;
         *reinterpret_cast<uint2*>(dst) = lead;
         *reinterpret_cast<uint2*>(dst + kTermB) = resid;
       }
@@ -675,9 +704,8 @@ __global__ __launch_bounds__(64 * kMfmaWaves, 2) void mlp_f32_short_kernel(MlpAr
     off += K * N + N;
   }
 
-  // ---- the network output [A][sample] -> memory, or its loss (as in mlp_f32_kernel) -----------------------
+  // ---- the network output [A][sample] -> memory, or its loss: sixteen samples per wave, as the form above has them ----
   const int A = a.sh.dims[n_layers];
-  const int s = tid & 63, b = b0 + s;
   if (LOSS == LOSS_NONE) {
     float* dst = a.out + (static_cast<size_t>(member) * a.B + b0) * A;
     const int rows = min(TB, a.B - b0);
@@ -687,26 +715,14 @@ __global__ __launch_bounds__(64 * kMfmaWaves, 2) void mlp_f32_short_kernel(MlpAr
     }
     return;
   }
-  if (wave != 0) return;
-  float loss = 0.f;
-  if (b < a.B) {
-    if (LOSS == LOSS_CE) {
-      const int y = min(max(static_cast<const int32_t*>(a.target)[b], 0), A - 1);  // labels outside [0, A) are clamped
-      float mx = fin[s];
-      for (int o = 1; o < A; ++o) mx = fmaxf(mx, fin[o * TB + s]);
-      float se = 0.f;
-      for (int o = 0; o < A; ++o) se += expf(fin[o * TB + s] - mx);
-      loss = (mx + logf(se)) - fin[y * TB + s];
-    } else {
-      const float* tg = static_cast<const float*>(a.target) + (static_cast<size_t>(member) * a.B + b) * A;
-      for (int o = 0; o < A; ++o) {
-        const float d = fin[o * TB + s] - tg[o];
-        loss = fmaf(d, d, loss);
-      }
-    }
+  if (wave < 4) {
+    const int b = b0 + 16 * wave + j;
+    const float loss = mlp_finish<kMfmaMaxWidth / 16, LOSS, 1>(
+        a, member, b, b < a.B, A, q, [&](int t, int i) { return fin[(16 * t + 4 * q + i) * TB + 16 * wave + j]; });
+    if (lane == 0) red_s[wave] = loss;
   }
-  loss = wave_sum(loss);
-  if (s == 0) a.partial[static_cast<size_t>(member) * a.tiles + tile] = loss;
+  __syncthreads();
+  if (tid == 0) a.partial[static_cast<size_t>(member) * a.tiles + tile] = (red_s[0] + red_s[1]) + (red_s[2] + red_s[3]);
 }
 
 // ---- the fp32 matrix form ------------------------------------------------------------------------------
@@ -957,7 +973,7 @@ __global__ __launch_bounds__(512, 4) void mlp_f32_units_kernel(MlpArgs a, int gr
         if (16 * t >= A) break;
         transpose_groups(x[t]);
       }
-      mlp_finish<NTM, LOSS>(a, member, b, b < s_end, A, q, x);
+      mlp_finish<NTM, LOSS>(a, member, b, b < s_end, A, q, [&](int t, int i) { return x[t][i]; });
     } else {
       const float loss = f32_sample_loss<NTM, LOSS>(a, member, b, b < s_end, A, q, x);
       if (q == 0) loss_s[b - first * kMlpTile] = loss;
@@ -1032,7 +1048,16 @@ int launch_mlp_f32(const MlpShape& sh, const float* params, const float* obs, in
     return launch_units(mlp_f32_units_kernel<LOSS_MSE>);
   }
   if (form == FORM_SPLIT) {
-    if (a.tiles == 1 && sh.max_width > 128 && sh.n_layers > 2) {
+    bool wide = false, whole = true;
+    for (int l = 0; l < sh.n_layers; ++l) {
+      wide |= sh.dims[l] >= 192 && sh.dims[l + 1] >= 192;
+      wide |= sh.dims[l + 1] == 256 && a.tiles == 1 && pop > 256;  // (64-256-16, 1000 members of 64: 64 there and 59 here)
+      whole &= sh.dims[l] % 32 == 0;
+    }
+    // (a single layer: 256-256, one member of 300, classification 26 us there and 30 here, squared error 24 and 21.5;
+    // outputs of 255, whose rows start off 16 bytes, one member of 2000 31 and 25.5)
+    const bool single = loss == LOSS_MSE || (loss == LOSS_NONE && sh.dims[sh.n_layers] % 4 != 0);
+    if (wide && whole && (sh.n_layers > 1 || single) && (a.tiles == 1 || static_cast<int64_t>(pop) * a.tiles <= 256)) {
       int kp = 32;      // widest fan-in, padded to the matrix instruction's 32
       for (int l = 0; l < sh.n_layers; ++l) kp = max(kp, (sh.dims[l] + 31) & ~31);
       a.ldw = kp;
@@ -1044,7 +1069,7 @@ int launch_mlp_f32(const MlpShape& sh, const float* params, const float* obs, in
                                            hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
         if (e != hipSuccess) (void)hipGetLastError();
         EVO_REQUIRE(e == hipSuccess, EVO_ERR_HIP, "hipFuncSetAttribute failed: %s", hipGetErrorString(e));
-        hipLaunchKernelGGL(kern, dim3(8 * ((pop + 7) / 8)), dim3(64 * kMfmaWaves), lds, s, a);
+        hipLaunchKernelGGL(kern, dim3(8 * ((pop + 7) / 8) * a.tiles), dim3(64 * kMfmaWaves), lds, s, a);
         return check_launch("mlp_f32_short_kernel");
       };
       if (loss == LOSS_NONE) return launch_short(mlp_f32_short_kernel<LOSS_NONE>);

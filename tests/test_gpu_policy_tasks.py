@@ -110,7 +110,8 @@ def test_mlp_f32_forms_at_their_edges(evo, dims, pop, B, shared):
 @pytest.mark.parametrize("dims,acts,B,shared", [
     ((16, 32, 4), (1, 0), 512, True), ((20, 50, 60, 5), (1, 2, 0), 300, False), ((63, 64, 64), (2, 1), 65, True),
     ((1, 1), (0,), 1, True), ((33, 17, 64), (1, 0), 130, False), ((5, 48, 3), (2, 0), 1100, True), ((8,) * 8 + (7,), (1,) * 8, 17, True),
-    ((64, 150, 40, 5), (1, 2, 0), 300, True), ((100, 70, 9), (1, 0), 65, False)])
+    ((64, 150, 40, 5), (1, 2, 0), 300, True), ((100, 70, 9), (1, 0), 65, False), ((64, 256, 256, 16), (1, 2, 0), 130, True),
+    ((192, 224, 7), (2, 0), 193, False), ((256, 255), (1,), 70, True)])
 def test_mlp_f32_bits_do_not_depend_on_the_population(evo, dims, acts, B, shared):
     """A member's outputs and fitness are the same bits evaluated alone, in a few members or in a large population: which
     kernel takes a network, and how many samples a workgroup, follows from the whole problem's size."""
