@@ -188,16 +188,40 @@ __global__ __launch_bounds__(kBf16Threads, NT >= 12 ? 2 : NT == 8 ? 3 : 4) void 
       off += K * N + N, k0 = 0, ++l;
     }
   };
-  // A last layer whose width is no multiple of 8 comes element by element, into LDS of its own behind the window: all of
-  // it at the start where that is little (rag_rows = K), else 32 rows at a time.
+  // A last layer whose width is no multiple of 8 comes into LDS of its own behind the window: where that is little all of it
+  // element by element, requested at the start; else by rows, 16 bytes at a time on whatever address and the last up to
+  // seven elements of a row one by one, all rows (rag_rows = K) or 32 of them.  (256-250, one member: 22 -> 13.5 us against
+  // element by element.)
   constexpr int kRagged = 8;                   // elements per thread that are requested ahead
   const int rag_K = a.sh.dims[n_layers - 1], rag_N = a.sh.dims[n_layers];
   const bool ragged = a.rag_rows > 0;
   const float rag_inv = 1.0f / static_cast<float>(rag_N);
   int rag_k0 = 0;                              // first row in LDS
-  auto rag_put = [&](int e, uint16_t v) {      // (e below 2^14: exact, as above)
+  auto rag_put = [&](int e, uint16_t v) {      // (e below 2^11: exact, as above)
     const int r = static_cast<int>((static_cast<float>(e) + 0.5f) * rag_inv), c = e - r * rag_N;
     *reinterpret_cast<uint16_t*>(window_s + a.rag_at + r * gen_stride(rag_N) + 2 * c) = v;
+  };
+  auto rag_fetch = [&](int k0, int rows) {     // (more than 2^11 elements: eight columns and more)
+    for (int r = tid >> 3; r < rows; r += kBf16Threads / 8) {
+      const uint16_t* src = theta + Pw + (k0 + r) * rag_N;
+      unsigned char* dst = window_s + a.rag_at + r * gen_stride(rag_N);
+      u32x4v v[kMaxWidth / 64];
+#pragma unroll
+      for (int i = 0; i < kMaxWidth / 64; ++i)  // (lanes beyond the row's last whole piece fetch its last eight elements)
+        v[i] = *reinterpret_cast<const u32x4u*>(src + min(8 * (tid & 7) + 64 * i, rag_N - 8));
+#pragma unroll
+      for (int i = 0; i < kMaxWidth / 64; ++i) {
+        const int c = 8 * (tid & 7) + 64 * i;
+        if (c + 8 <= rag_N) {
+          *reinterpret_cast<u32x4v*>(dst + 2 * c) = v[i];
+        } else if (c < rag_N) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            if (rag_N - 8 + e >= c)
+              *reinterpret_cast<uint16_t*>(dst + 2 * (rag_N - 8 + e)) = static_cast<uint16_t>(v[i][e >> 1] >> (16 * (e & 1)));
+        }
+      }
+    }
   };
   const bool rag_ahead = ragged && a.rag_rows >= rag_K && rag_K * rag_N <= kRagged * kBf16Threads;
   uint16_t rag[kRagged];
@@ -361,8 +385,7 @@ __global__ __launch_bounds__(kBf16Threads, NT >= 12 ? 2 : NT == 8 ? 3 : 4) void 
         __syncthreads();                       // every wave has read the rows before
         rag_k0 = k0;
         const int rows = a.rag_rows >= K ? K : min(32, K - k0);
-#pragma unroll 4
-        for (int e = tid; e < rows * N; e += kBf16Threads) rag_put(e, theta[Pw + k0 * N + e]);
+        rag_fetch(k0, rows);
         if ((rows & 31) != 0) zero_rows(a.rag_at + rows * stride, stride);
         __syncthreads();
       }

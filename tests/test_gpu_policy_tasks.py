@@ -370,11 +370,13 @@ def test_mlp_bf16(evo, dims, acts, pop, B):
 
 
 # Every other bfloat16 shape: widths at the edges of the tile classes (64, 128, 256), input widths with half a step of 32,
-# last layers whose rows are no whole 16-byte pieces (with odd P: rows that start on two bytes), one layer only, weights
+# last layers whose rows are no whole 16-byte pieces (with odd P: rows that start on two bytes; all of them at once or 32
+# rows at a time, whose last step may be a half one), one layer only, weights
 # in several windows, batches around the sixteen observations of a wave.  Tolerance as above: 2^-9 per rounded activation.
 @pytest.mark.parametrize("dims,acts,pop,B", [((64, 64, 1), (2, 0), 5, 1), ((48, 144, 96, 12), (1, 1, 0), 4, 50),
                                              ((128, 128, 8), (2, 1), 3, 16), ((80, 16, 255), (1, 0), 3, 17),
-                                             ((256, 256, 256, 250), (2, 2, 0), 2, 64), ((256, 256, 32), (2, 0), 3, 33),
+                                             ((256, 256, 256, 250), (2, 2, 0), 2, 64), ((240, 255), (0,), 2, 33), ((64, 208, 251), (2, 0), 2, 50),
+                                             ((256, 256, 32), (2, 0), 3, 33),
                                              ((16, 13), (1,), 3, 64), ((208, 37), (0,), 2, 31), ((256, 112, 17), (2, 2), 3, 48),
                                              ((16, 240, 16, 64, 7), (2, 1, 2, 1), 3, 40), ((112, 128, 128, 96, 4), (2, 2, 2, 0), 2, 15)])
 def test_mlp_bf16_any_width(evo, dims, acts, pop, B):
