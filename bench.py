@@ -52,7 +52,7 @@ MEASURED_TRAFFIC_BYTES = {
 # the population of the oracle's bounded sample (about 10-30 s of CPU time on one core).
 # What the rocprofv3 counters in profiles/ say bounds the dominant kernel.
 BOUND_DETAIL = {
-    "cfg1": "launch latency: five launches of a few microseconds each (profiles/mlp_f32_kernel_cfg1.md)",
+    "cfg1": "launch latency: four launches of a few microseconds each (profiles/mlp_f32_kernel_cfg1.md)",
     "cfg2": "both convolutions on the matrix cores: MFMA busy 47 %, VALU issue 63 % on the same SIMDs (16 % of the cycles overlap), LDS busy 64 %, "
             "31 % of wave time waiting at three waves per SIMD (profiles/convnet_kernel_cfg2.md)",
     "cfg3": "vector-instruction issue along a 1000-step dependency chain: VALU busy 66 %, MFMA busy 21 %, 36 % of wave "

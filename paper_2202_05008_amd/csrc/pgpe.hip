@@ -597,13 +597,13 @@ __global__ __launch_bounds__(256) void tell_kernel(TellArgs a) {
 }
 
 // ---- one whole generation in one launch (small problems) ----------------------------------------------------
-// ask -> forward + loss -> fitness -> ranks -> tell for problems whose five launches are bound by launch latency
+// ask -> forward + loss -> fitness -> ranks -> tell for problems whose launches are bound by their latency
 // (Section 2's loop of ask, evaluate, tell at cfg1's size).  Workgroup (tile, member): draws the member's parameters
 // into LDS exactly as ask_kernel would store them, runs mlp_f32_body on its tile of samples and hands the tile's
 // loss sum over.  The first n_tell workgroups then wait for every tile's sum (every other workgroup exits, so those
 // that wait cannot keep anyone from arriving; the wait is bounded), form every member's fitness and utility in LDS
 // with the arithmetic of finalize_kernel and rank_kernel and run tell_block for their block of parameters: the
-// same bits as the five launches give.  mu and sigma are first written after every workgroup has read them.
+// same bits as the calls one by one give.  mu and sigma are first written after every workgroup has read them.
 //
 // The hand-over has no counter and no fence: on this chip a release at device scope writes a die's cache back
 // (measured: 5 us from the end of the forward to the counted arrival, 13 us until 512 arrivals had been seen).
@@ -614,7 +614,7 @@ __global__ __launch_bounds__(256) void tell_kernel(TellArgs a) {
 // among the NaNs, is stored as the default NaN.)
 struct GenSmallArgs {
   MlpArgs mlp;       // params and partial unused: the parameters are drawn here, the sums go through `sums`
-  TellArgs tell;     // shaped unused: the utilities are formed here
+  TellArgs tell;     // pairs and fitness unused: the pair weights are formed here
   float* fitness;    // [pop] out
   float scale;       // fitness = scale * sum of the member's loss sums
   uint32_t* sums;    // [2][kSmallMaxTiles] loss sums of (member, tile) as bit patterns, by parity of the generation
