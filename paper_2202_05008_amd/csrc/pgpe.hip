@@ -29,7 +29,7 @@ struct pgpe_state {
   bool pending;
   uint64_t seed;
   int32_t pop;
-  bool tickets_ready;  // the two counters of the one-launch generation have been cleared
+  bool tickets_ready;  // the words of the one-launch generation have been cleared
 };
 
 namespace evo {
@@ -46,7 +46,7 @@ struct Workspace {
 static inline size_t ws_arrays_bytes(int pop_max) {
   return ((static_cast<size_t>(pop_max) * 2 + 2 * kNormBlocks) * 4 + 255) & ~size_t(255);
 }
-constexpr int kSmallSumWords = 2 * 4096;  // the two arrays of loss sums of the one-launch generation
+constexpr int kSmallSumWords = 2 * 4096;  // the loss sums of the one-launch generation, two words each
 constexpr unsigned kGradNormParts = kSmallSumWords;
 static inline size_t ws_bytes(int pop_max) { return ws_arrays_bytes(pop_max) + 256 + 4 * kSmallSumWords; }
 
@@ -605,25 +605,26 @@ __global__ __launch_bounds__(256) void tell_kernel(TellArgs a) {
 // with the arithmetic of finalize_kernel and rank_kernel and run tell_block for their block of parameters: the
 // same bits as the calls one by one give.  mu and sigma are first written after every workgroup has read them.
 //
-// The hand-over has no counter and no fence: on this chip a release at device scope writes a die's cache back
-// (measured: 5 us from the end of the forward to the counted arrival, 13 us until 512 arrivals had been seen).
-// The sums themselves are the flags.  There are two arrays of them, used by even and odd generations; a word
-// holds kNotYet until its workgroup stores its sum with one device-scope store, the waiting workgroups poll the
-// words with device-scope loads, and every workgroup re-arms its word of the OTHER array, which the previous
-// launch has finished with and the next one will use.  (A sum that happened to have kNotYet's bits, one pattern
-// among the NaNs, is stored as the default NaN.)
+// The hand-over has no fence and no counter that anyone waits for: on this chip a release at device scope writes a die's
+// cache back (measured: 5 us from the end of the forward to the counted arrival, 13 us until 512 arrivals had been seen).
+// The sums themselves are the flags: a workgroup stores its sum and the number of the launch in one 8-byte device-scope
+// store, and the waiting workgroups poll the words with device-scope loads until all carry this launch's number.  The
+// number lives on the device and the last waiting workgroup to finish advances it, so no launch ever meets its own
+// number in an older sum, whatever happened to the state or the population in between and however often a recorded
+// launch is replayed.  (Words that a generation cleared for the next one, in two arrays by the parity of t, were such older
+// sums after a reset, an import, a generation by the separate calls or a larger population than the one before.)
 struct GenSmallArgs {
   MlpArgs mlp;       // params and partial unused: the parameters are drawn here, the sums go through `sums`
   TellArgs tell;     // pairs and fitness unused: the pair weights are formed here
   float* fitness;    // [pop] out
   float scale;       // fitness = scale * sum of the member's loss sums
-  uint32_t* sums;    // [2][kSmallMaxTiles] loss sums of (member, tile) as bit patterns, by parity of the generation
-  uint32_t* done;    // waiting workgroups that have finished (the last one clears it and advances gen_rw)
+  uint64_t* sums;    // [kSmallMaxTiles] (launch number, bits of the loss sum) of (member, tile)
+  uint32_t* launches;  // launches so far
+  uint32_t* done;    // waiting workgroups that have finished (the last one clears it and advances launches and gen_rw)
   uint32_t* gen_rw;  // the device copy of t, or null
   int pop, shaping, n_tell, total;
 };
 constexpr int kSmallMaxTiles = 4096;       // (member, tile) pairs of one launch
-constexpr uint32_t kNotYet = 0x7fc5a5a5u;  // a quiet NaN that no arithmetic produces
 constexpr int kSmallSpinLimit = 1 << 21;   // polls of about a microsecond: a sum that has not come by then never will
 typedef __attribute__((address_space(3))) const float* lds_cfloat_ptr;
 
@@ -637,11 +638,8 @@ __global__ __launch_bounds__(256) void generation_small_kernel(GenSmallArgs g) {
   const int wg = member * gridDim.x + tile;
   const int P = g.tell.P, nquads = g.tell.nquads;
   const uint32_t gen = g.tell.gen_dev ? *g.tell.gen_dev : g.tell.gen;
-  uint32_t* mine = g.sums + (gen & 1u) * kSmallMaxTiles;
-  if (tid == 0) {
-    missing = 0;
-    __hip_atomic_store(g.sums + ((gen & 1u) ^ 1u) * kSmallMaxTiles + wg, kNotYet, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
+  const uint32_t launch = *g.launches + 1u;  // this launch's number
+  if (tid == 0) missing = 0;
   // ---- ask: this member's row, as ask_kernel forms it ----
   {
     const float sign = (member & 1) ? -1.0f : 1.0f;
@@ -660,11 +658,9 @@ __global__ __launch_bounds__(256) void generation_small_kernel(GenSmallArgs g) {
   // ---- forward and loss of this tile; thread 0 holds the tile's sum and hands it over ----
   float* mlp_lds = gs_smem + 4 * nquads;
   const float tile_loss = mlp_f32_body<LOSS>(g.mlp, (lds_cfloat_ptr)gs_smem, member, tile, mlp_lds);
-  if (tid == 0) {
-    uint32_t bits = __float_as_uint(tile_loss);
-    if (bits == kNotYet) bits = 0x7fc00000u;
-    __hip_atomic_store(mine + wg, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
+  if (tid == 0)
+    __hip_atomic_store(g.sums + wg, (static_cast<uint64_t>(launch) << 32) | __float_as_uint(tile_loss), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
   if (wg >= g.n_tell) return;
   __syncthreads();  // the tile's LDS is free
   // ---- every tile's sum, polled into LDS ----
@@ -676,17 +672,25 @@ __global__ __launch_bounds__(256) void generation_small_kernel(GenSmallArgs g) {
   float2* pairs_s = reinterpret_cast<float2*>(shaped_s + pop4);
   float* part_s = reinterpret_cast<float*>(pairs_s) + pop4;
   for (int i = tid; i < g.total; i += 256) {
-    uint32_t bits = __hip_atomic_load(mine + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    for (int polls = 0; bits == kNotYet && polls < kSmallSpinLimit; ++polls) {
+    uint64_t word = __hip_atomic_load(g.sums + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int polls = 0; static_cast<uint32_t>(word >> 32) != launch && polls < kSmallSpinLimit; ++polls) {
       __builtin_amdgcn_s_sleep(2);
-      bits = __hip_atomic_load(mine + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      word = __hip_atomic_load(g.sums + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    if (bits == kNotYet) missing = 1;
-    part_s[i] = __uint_as_float(bits);
+    if (static_cast<uint32_t>(word >> 32) != launch) missing = 1;
+    part_s[i] = __uint_as_float(static_cast<uint32_t>(word));
   }
+  // the last of the waiting workgroups to finish advances the launch's number, and t where it lives on the device
+  auto finish = [&]() {
+    if (tid != 0 || atomicAdd(g.done, 1u) != static_cast<uint32_t>(g.n_tell - 1)) return;
+    *g.done = 0u;
+    *g.launches = launch;
+    if (g.gen_rw) *g.gen_rw += 1u;
+  };
   __syncthreads();
   if (missing) {  // never seen; the fitness says so rather than a silent wrong update
     if (wg == 0 && tid == 0) g.fitness[0] = __builtin_nanf("");
+    finish();
     return;
   }
   // ---- fitness, orderable words and utilities of every member, in LDS ----
@@ -723,14 +727,7 @@ __global__ __launch_bounds__(256) void generation_small_kernel(GenSmallArgs g) {
   small_pairs(fit_s, g.pop, g.shaping, ord_s, shaped_s, reinterpret_cast<double*>(tell_smem), pairs_s);
   // ---- tell for this workgroup's block of parameters ----
   tell_block<OPT, SRULE, false>(g.tell, wg, static_cast<const float2*>(pairs_s), tell_smem);
-  if (g.gen_rw == nullptr) return;
-  __syncthreads();
-  if (tid == 0) {  // t on the device: the last of the waiting workgroups to finish advances it
-    if (atomicAdd(g.done, 1u) == static_cast<uint32_t>(g.n_tell - 1)) {
-      *g.done = 0u;
-      *g.gen_rw += 1u;
-    }
-  }
+  finish();
 }
 
 // ---- ClipUp: two norms over P, each as partial sums in a fixed order ------------------------------------------
@@ -1061,16 +1058,12 @@ int pgpe_generation_small(pgpe_state* st, uint64_t seed, int32_t pop, const MlpS
                 "pgpe_generation: %u update workgroups for %ld evaluation workgroups, %zu bytes of LDS: not a small problem",
                 n_tell, total, lds);
   }
-  static_assert(kSmallSumWords == 2 * kSmallMaxTiles, "two arrays of sums");
+  static_assert(kSmallSumWords == 2 * kSmallMaxTiles, "two words per sum");
   Workspace ws = ws_carve(st->work, c.pop_max);
-  g.done = ws.gen + 16;  // inside the 256 bytes kept for the generation word
-  g.sums = ws.gen + 64;  // behind them
-  if (!st->tickets_ready) {  // once per state: nothing has arrived, nobody has finished
-    rc = fill(reinterpret_cast<float*>(g.done), 1, 0.f, s);
-    float not_yet;  // the bit pattern as a float (moved, never computed with)
-    const uint32_t not_yet_bits = kNotYet;
-    memcpy(&not_yet, &not_yet_bits, sizeof(not_yet));
-    if (!rc) rc = fill(reinterpret_cast<float*>(g.sums), kSmallSumWords, not_yet, s);
+  g.done = ws.gen + 16, g.launches = ws.gen + 32;  // inside the 256 bytes kept for the generation word
+  g.sums = reinterpret_cast<uint64_t*>(ws.gen + 64);  // behind them
+  if (!st->tickets_ready) {  // once per state: no launch so far, nothing has arrived, nobody has finished
+    rc = fill(reinterpret_cast<float*>(g.done), 64 - 16 + kSmallSumWords, 0.f, s);
     if (rc) return rc;
     st->tickets_ready = true;
   }

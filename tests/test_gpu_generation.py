@@ -149,6 +149,52 @@ def test_what_is_not_small_is_refused(evo):
     assert g.generation == gc.generation == g2.generation == 1
 
 
+@pytest.mark.parametrize("device_t", [False, True])
+def test_one_launch_among_other_calls(evo, device_t):
+    """One-launch generations with anything between them -- generations by the three calls, other population sizes, a
+    reset, an import of an earlier state -- are those of the three calls: no launch takes an earlier one's sums."""
+    dims, acts, pop_max, B = (16, 32, 4), (1, 0), 64, 300
+    P = mlp_param_count(dims)
+    mu0 = gen.initial_mu(7, P, 0.3)
+    one, three = (evo.PGPE(evo.make_pgpe_config(P=P, pop_max=pop_max), mu0) for _ in range(2))
+    if device_t:
+        one.device_generation(), three.device_generation()
+    pd = evo.make_policy_desc(evo.EVO_POLICY_MLP, dims, acts)
+    x, y = (dev(a) for a in gen.class_blobs(8, B, dims[0], dims[-1]))
+    td = evo.make_task_desc(evo.EVO_TASK_CLASSIFY, B=B, obs=x, target=y)
+    td = evo.make_task_desc(evo.EVO_TASK_CLASSIFY, B=B, obs=x, target=y, work=_work(evo, td, pd, pop_max))
+    fit1, fit3 = (torch.empty(pop_max, device="cuda") for _ in range(2))
+    seed = 0
+
+    def by_three(es, pop, fit):
+        params = torch.empty(pop, P, device="cuda")
+        es.ask(seed, pop, params)
+        evo.rollout(td, pd, params, pop, 1, fit)
+        es.tell(fit)
+
+    saved = [es.export_state() for es in (one, three)]
+    steps = [("one", 64), ("one", 64), ("three", 64), ("one", 64), ("one", 32), ("one", 64), ("one", 16), ("three", 8), ("one", 64),
+             ("reset", 0), ("one", 64), ("reset", 0), ("one", 64), ("one", 64), ("import", 0), ("one", 64), ("import", 0), ("one", 48)]
+    for n, (what, pop) in enumerate(steps):
+        seed = 5000 + n
+        if what == "reset":
+            for es in (one, three):
+                evo.pgpe_reset(es.handle)
+        elif what == "import":
+            for es, state in zip((one, three), saved):
+                es.import_state(state)
+        else:
+            by_three(three, pop, fit3[:pop])
+            if what == "one":
+                one.generation_step(seed, pop, td, pd, fit1[:pop])
+            else:
+                by_three(one, pop, fit1[:pop])
+            assert torch.equal(fit1[:pop], fit3[:pop]), "step %d: fitness" % n
+        for name, a, b in zip(("mu", "sigma", "m", "v"), _state(one), _state(three)):
+            assert np.array_equal(a, b), "step %d (%s): %s differs" % (n, what, name)
+    assert one.generation == three.generation
+
+
 def test_one_launch_generation_replayed_from_a_graph(evo):
     """One recorded launch replays as successive generations (t and the parity of the hand-over arrays live on the
     device): six replays, with eager work and waits between them, against six generations of the three calls."""
