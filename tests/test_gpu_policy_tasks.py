@@ -78,16 +78,21 @@ def test_pop_forward_mlp_f32_matrix_cores(evo, dims, acts, pop, B, shared, scale
 
 
 # Where the fp32 forms change over and their tiles end: one and two pieces of 64 samples per workgroup and their
-# remainders, layers of 128 / 129 wide, odd widths and batches, a fan-in that fills a k step by one, eight layers; narrow
-# networks on the fp32 matrix instruction (more than 512 members: smaller problems stay on the vector form), whose
-# workgroups take several pieces.  Same bound as above: sums of at most 256 fp32 products.
+# remainders, layers of 128 / 129 wide, odd widths and batches, a fan-in that fills a k step by one, eight layers; wide whole
+# layers shared out by neurons (few workgroups, or 64 samples); narrow networks on the vector form and (widths of 48 and more,
+# 1100 products and more) on the fp32 matrix instruction, a few members over all dies, workgroups of one to sixteen pieces of
+# 64 samples and their remainders.  Same bound as above: sums of at most 256 fp32 products.
 @pytest.mark.parametrize("dims,pop,B,shared", [
     ((65, 128, 9), 130, 129, True), ((64, 129, 33), 3, 128, False), ((33, 64, 257 - 1, 1), 2, 63, True),
     ((96, 31, 97, 17), 9, 193, False), ((70, 16, 70, 16, 70, 16, 70, 16, 3), 5, 66, True),
     ((64, 256, 40, 5), 9, 64, False), ((64, 256, 40, 5), 9, 65, False),
-    ((64, 64, 64, 256), 9, 64, True), ((64, 96, 64, 129), 5, 17, True), ((256, 16, 16, 256), 3, 64, False),  # outputs wider than inputs
+    ((64, 64, 64, 256), 9, 64, True), ((64, 96, 64, 129), 5, 17, True), ((256, 16, 16, 256), 3, 64, False),  # outputs wider than inputs,
+    ((192, 192, 256), 3, 50, True), ((64, 64, 256), 260, 50, False),                                            # shared out by neurons
     ((16, 32, 4), 520, 64, True), ((15, 17, 33, 64), 513, 17, False), ((63, 64, 1), 1030, 130, True),
-    ((4, 8, 2), 600, 1, True), ((1, 1), 514, 1100, True), ((20, 50, 60, 5), 700, 300, False)])
+    ((4, 8, 2), 600, 1, True), ((1, 1), 514, 1100, True), ((20, 50, 60, 5), 700, 300, False),
+    ((48, 1), 3, 1, True), ((1, 48), 70, 17, False), ((16, 48, 2), 600, 1100, True), ((33, 40, 6), 2, 4000, True),
+    ((32, 35, 7), 63, 65, False), ((32, 35, 7), 64, 64, False),
+    ((192, 224, 10), 2, 130, True), ((192, 192, 33), 260, 40, False), ((64, 256, 3), 257, 64, True), ((224, 255), 2, 129, True)])
 def test_mlp_f32_forms_at_their_edges(evo, dims, pop, B, shared):
     n = len(dims) - 1
     acts = tuple((1, 2, 0)[i % 3] for i in range(n - 1)) + (0,)
@@ -171,7 +176,7 @@ def test_mlp_f32_more_workgroups_than_one_grid_dimension_takes(evo):
 
 def test_mlp_f32_infinite_input_stays_in_its_sample(evo):
     """An infinity among the observations of one sample: the other samples, and the neurons beyond a ragged layer, see nothing of it."""
-    for dims, pop in (((20, 33, 5), 513), ((70, 33, 5), 4)):
+    for dims, pop in (((20, 33, 5), 513), ((20, 50, 5), 513), ((70, 33, 5), 4), ((192, 224, 5), 4)):
         acts, B = (1, 0), 40
         params = gen.random_params(23, pop, mlp_param_count(dims), 0.3)
         obs = np.random.default_rng(24).standard_normal((B, dims[0])).astype(np.float32)
