@@ -36,8 +36,8 @@ __global__ __launch_bounds__(256) void mlp_f32_kernel(MlpArgs a) {
 // the next layer's B operand (k = 32 s + 16 (e >> 2) + 4 q + (e & 3) for lane group q, element e).  Activations never
 // leave the registers, and a layer needs no exchange between waves.
 //
-// The weights pass through LDS in chunks of sixteen units (eight in networks of widths up to 128; a unit = one neuron tile x 32 k), already split into two fp16
-// terms and in operand order, so that every wave's read is one conflict-free 16-byte access per lane.  The eight waves
+// The weights pass through LDS in chunks of sixteen units (eight in networks of widths up to 128; a unit = one neuron tile
+// x 32 k), already split into two fp16 terms and in operand order, so that every wave's read is one conflict-free 16-byte access per lane.  The eight waves
 // stage together and run ahead of their own products, across layers: while chunk i is consumed, chunk i + 1 is split
 // and stored, the neurons' largest magnitudes of chunk i + 2 are published, and chunk i + 3 is on its way from memory.
 // One barrier per chunk.  Out-of-range rows and columns are zeros by the buffer's own bounds check.
@@ -45,10 +45,10 @@ __global__ __launch_bounds__(256) void mlp_f32_kernel(MlpArgs a) {
 // magnitude; the activations of a SAMPLE from the largest magnitude among its outputs of the layer (in-lane maxima and
 // two lane exchanges).  Both factors ride in the multiply-add that adds the bias.
 // Bound by the issue of vector instructions and their latency at two waves per SIMD (staging, activations, the outputs'
-// splits; matrix pipe about 13 % busy).  Against the form it replaced, which kept activations in LDS, gathered every
+// splits; vector pipe 45 %, matrix pipe 15 %, LDS 19 % busy).  Against the form it replaced, which kept activations in LDS, gathered every
 // wave's own weights and split them for 64 samples at a time: 100-200-120-10, 500 members of 300 samples 235 -> 163 us;
 // 64-256-256-16, 1024 of 512 926 -> 570 us; 128-128-128-8, 1000 of 200 258 -> 99 us; its error against 64 bits fell from
-// 2.9e-7 to 2.1e-7 (64-256-256-16) with the cross terms in a chain of their own.
+// 2.8e-7 to 2.1e-7 (64-256-256-16) with the cross terms in a chain of their own.
 typedef float floatx4m __attribute__((ext_vector_type(4)));
 constexpr int kMfmaMaxWidth = 256;             // fan-in and fan-out of a layer
 constexpr int kMfmaWaves = 8;
