@@ -373,6 +373,11 @@ int evo_forage_step(const task_desc* td, int32_t pop, const float* pos_dev, cons
  * be NULL. */
 int evo_forage_state(const task_desc* td, const policy_desc* pd, const void* params_dev, int32_t pop, int32_t steps,
                      float* pos_dev, float* vel_dev, int32_t* reward_dev, uint32_t* counts_dev, void* stream);
+/* The same where a wait of one workgroup of a world for another lasts at most wait_ticks (10 ns each) before the world is
+ * played again without waits; 0: every wait fails.  The results are those of evo_forage_state whatever the bound. */
+int evo_forage_state_bounded(const task_desc* td, const policy_desc* pd, const void* params_dev, int32_t pop, int32_t steps,
+                             float* pos_dev, float* vel_dev, int32_t* reward_dev, uint32_t* counts_dev,
+                             uint64_t wait_ticks, void* stream);
 /* One cart-pole step for n independent (state, action) pairs: state_dev[n][4], action_dev[n]
  * -> next_dev[n][4], reward_dev[n].  Only td->cp is read. */
 int evo_task_step(const task_desc* td, const float* state_dev, const float* action_dev, float* next_dev,

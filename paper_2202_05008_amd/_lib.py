@@ -49,6 +49,8 @@ _SIGNATURES = {
     "evo_forage_step": (C.c_int, [C.POINTER(task_desc), C.c_int32] + [C.c_void_p] * 10),
     "evo_forage_state": (C.c_int, [C.POINTER(task_desc), C.POINTER(policy_desc), C.c_void_p, C.c_int32, C.c_int32]
                          + [C.c_void_p] * 5),
+    "evo_forage_state_bounded": (C.c_int, [C.POINTER(task_desc), C.POINTER(policy_desc), C.c_void_p, C.c_int32, C.c_int32]
+                                 + [C.c_void_p] * 4 + [C.c_uint64, C.c_void_p]),
     "pgpe_device_generation": (C.c_int, [C.c_void_p, C.POINTER(C.c_void_p), C.c_void_p]),
     "pgpe_sync_generation": (C.c_int, [C.c_void_p, C.c_void_p]),
     "pgpe_ask": (C.c_int, [C.c_void_p, C.c_uint64, C.c_int32, C.c_void_p, C.c_int32, C.c_void_p]),

@@ -178,7 +178,7 @@ static int seq2seq_impl(const task_desc* td, const policy_desc* pd, const void* 
 // The shared-world task: fitness and / or the state after the last step.
 static int forage_impl(const task_desc* td, const policy_desc* pd, const void* params_dev, int32_t pop, int32_t steps,
                        float* fitness_dev, float* pos_dev, float* vel_dev, int32_t* reward_dev, uint32_t* counts_dev,
-                       void* stream) {
+                       void* stream, uint64_t wait_ticks = kForageWaitTicks) {
   EVO_REQUIRE(td != nullptr && (td->kind == EVO_TASK_FORAGE || td->kind == EVO_TASK_FORAGE_SOLO), EVO_ERR_ARG,
               "forage: needs an EVO_TASK_FORAGE or EVO_TASK_FORAGE_SOLO task");
   const bool solo = td->kind == EVO_TASK_FORAGE_SOLO;
@@ -207,7 +207,7 @@ static int forage_impl(const task_desc* td, const policy_desc* pd, const void* p
   if (rc) return rc;
   return launch_forage(sh, static_cast<const float*>(params_dev), pop, td->n_rollouts, steps, td->cp, td->reset_seed,
                        td->generation, td->generation_dev, td->work_dev, fitness_dev, pos_dev, vel_dev, reward_dev,
-                       counts_dev, as_stream(stream));
+                       counts_dev, wait_ticks, as_stream(stream));
 }
 
 static int rollout_impl(const task_desc* td, const policy_desc* pd, const void* params_dev, int32_t pop,
@@ -480,6 +480,13 @@ extern "C" int evo_forage_state(const task_desc* td, const policy_desc* pd, cons
                                 uint32_t* counts_dev, void* stream) {
   EVO_REQUIRE(pos_dev || vel_dev || reward_dev || counts_dev, EVO_ERR_ARG, "evo_forage_state: no output requested");
   return forage_impl(td, pd, params_dev, pop, steps, nullptr, pos_dev, vel_dev, reward_dev, counts_dev, stream);
+}
+
+extern "C" int evo_forage_state_bounded(const task_desc* td, const policy_desc* pd, const void* params_dev, int32_t pop,
+                                        int32_t steps, float* pos_dev, float* vel_dev, int32_t* reward_dev,
+                                        uint32_t* counts_dev, uint64_t wait_ticks, void* stream) {
+  EVO_REQUIRE(pos_dev || vel_dev || reward_dev || counts_dev, EVO_ERR_ARG, "evo_forage_state_bounded: no output requested");
+  return forage_impl(td, pd, params_dev, pop, steps, nullptr, pos_dev, vel_dev, reward_dev, counts_dev, stream, wait_ticks);
 }
 
 extern "C" int evo_forage_step(const task_desc* td, int32_t pop, const float* pos_dev, const float* vel_dev,

@@ -4,9 +4,12 @@
 // include/evo.h (unit square, food and poison items that reappear elsewhere once eaten, sensing of
 // the nearest food, poison and other agent, point-mass motion with drag and walls).
 //
-// Agents of one world see each other's positions of the current step, so a step is a grid-wide
-// dependency: one kernel launch per step, positions double-buffered in the task's workspace.
-// A launch is a few microseconds of work spread as widely as its parallelism allows:
+// Agents of one world see each other's positions of the current step, so a step is a dependency
+// between all workgroups of a world.  Two forms, the same trajectories bit for bit: the whole episode in
+// one launch whose workgroups hand positions over to each other (world_resident_kernel below), and one
+// launch per step, positions double-buffered in the task's workspace (world_step_kernel: into recorded
+// graphs, for worlds that do not fit the chip, and for the single-step hook).
+// A step's launch is a few microseconds of work spread as widely as its parallelism allows:
 //   workgroup = 8 agents x 4 worlds, two waves per world (main and helper; the four main waves read
 //   the same policy weights);
 //   eight lanes per agent: they split the nearest-neighbour scans (each judges two candidates per
@@ -22,6 +25,8 @@
 #include "kernels.h"
 
 #include <atomic>
+#include <cmath>
+#include <mutex>
 #include "philox.h"
 
 namespace evo {
@@ -382,16 +387,15 @@ __device__ __forceinline__ int touch_scan(const WorldConst& c, float2 p, const f
 constexpr int kExchangeWords = 6;
 
 template <int H, bool TANH>
-__global__ __launch_bounds__(kStepThreads) void world_step_kernel(StepArgs a) {
-  extern __shared__ float4 lds4[];
+__device__ __forceinline__ void world_step_block(StepArgs a, int block_x, int block_y, float4* lds4) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int slot = wave & (kWorldsPerBlock - 1);  // which of the workgroup's worlds
   const bool helper = wave >= kWorldsPerBlock;    // waves 4..7 assist waves 0..3
   const int q = lane & (kLanesPerAgent - 1);
-  const int agent0 = blockIdx.x * kAgentsPerBlock;
+  const int agent0 = block_x * kAgentsPerBlock;
   const int agent = agent0 + lane / kLanesPerAgent;
-  const int world = blockIdx.y * kWorldsPerBlock + slot;
+  const int world = block_y * kWorldsPerBlock + slot;
   const bool world_live = world < a.worlds;
   const bool live = world_live && agent < a.pop;
   const int n_food = a.c.n_food, n_items = a.c.n_items;
@@ -428,7 +432,7 @@ __global__ __launch_bounds__(kStepThreads) void world_step_kernel(StepArgs a) {
           const size_t o = static_cast<size_t>(world) * n_items + i;
           uint32_t cnt = a.counts_in[o];
           if (a.hits_prev) cnt += a.hits_prev[o];
-          if (blockIdx.x == 0) {  // one workgroup per world keeps the item book
+          if (block_x == 0) {  // one workgroup per world keeps the item book
             if (a.counts_out) a.counts_out[o] = cnt;
             if (a.hits_clear) a.hits_clear[o] = 0u;
           }
@@ -527,6 +531,670 @@ __global__ __launch_bounds__(kStepThreads) void world_step_kernel(StepArgs a) {
     a.vel_out[me] = v;
     a.reward[me] = a.accumulate ? a.reward[me] + reward : reward;
   }
+}
+
+template <int H, bool TANH>
+__global__ __launch_bounds__(kStepThreads) void world_step_kernel(StepArgs a) {
+  extern __shared__ float4 lds4[];
+  world_step_block<H, TANH>(a, blockIdx.x, blockIdx.y, lds4);
+}
+
+// ---- the whole episode of shared worlds in one launch -----------------------------------------------------
+// A launch per step takes 9.1 us (1024 agents, 8 worlds, H = 32), of which the gap, the reloading of the weights and the
+// staging of four worlds are two thirds; this kernel's step takes 3.6 us, and 2.4 us where a world is small.  The agents
+// stay where they are: a workgroup owns agents of ONE world for all steps, weights, state
+// and reward in registers, and what a step has to hand over goes through memory as its own flag: an agent's position is
+// one 8-byte word, x and y with the step's number modulo four in the two top bits of x (a coordinate lies in [0, 1], so
+// they are free), and the items that a workgroup's agents touch are words of 32 items under the step's number.  Every workgroup
+// polls the words of its world until all carry the number.  A word handed over and seen by everyone takes 1.6 us on this
+// chip, the same whether a world's workgroups share a die or not (a plain load misses the news in the vector cache; atomics
+// on the die's cache 3.3 us; invalidating the vector cache before a plain load 30 us).
+//
+// Waves: eight main waves own the agents: scan of the other agents, policy, motion, touches.  Beside their scan the item
+// waves move the touched items (each of them in a copy of its own, so they need no order among themselves; where an item
+// goes next is drawn ahead) and find the agents' nearest items, eight lanes per agent.
+// Lanes of a main wave: the agent scan takes all 64 for the wave's agents together (a candidate is read from LDS once for
+// four agents, and only the distance is tracked: 5.5 vector instructions per candidate instead of 8; the index is looked
+// up afterwards among the candidates of the lane that holds the minimum).  Policy: sixteen lanes per agent for H <= 32;
+// for H = 64 a wave per agent, since sixteen lanes would need 303 registers each for the weights.
+// The order of every sum is world_step_kernel's, so the trajectories are its trajectories bit for bit.
+// What a step consists of (cycles of a main wave, 8600 in all at 1024 agents): waiting for the positions 2000 + 900 (the
+// slowest workgroup), scan 2100 (at the issue rate of two main waves and an item wave per SIMD), look-up 500, waiting for
+// the items 900, policy 950, motion and touches 1300 (a dependent chain at one instruction per 6 to 7 cycles).  With the
+// items and touches in the main waves and one helper wave a step took 9600.
+//
+// A wait needs the other workgroups of the world on the chip.  The host launches no more workgroups than compute units
+// and one such launch at a time; where other work holds the chip all the same, a wait ends after wait_ticks, the
+// world's flag is raised, everybody leaves, and world_rerun_kernel plays the world again from its start without
+// waiting for anyone.
+constexpr int kMainWaves = 8;           // main waves per workgroup
+constexpr int kMaxResident = 256;       // workgroups of a launch; the room in the workspace is for these
+constexpr uint32_t kFar = 0x7F800000u;  // infinity's bits
+constexpr int resident_lanes(int H) { return H <= 32 ? 16 : 64; }                           // of a main wave, per agent
+constexpr int resident_agents(int H) { return kMainWaves * 64 / resident_lanes(H); }        // per workgroup
+constexpr int item_waves(int H) { return resident_agents(H) / kAgentsPerBlock; }            // per workgroup
+constexpr int resident_threads(int H) { return 64 * (kMainWaves + item_waves(H)); }
+
+struct ResidentArgs {
+  const float* params;  // [pop][P]
+  int P, pop, worlds, steps;
+  int act[3];
+  WorldConst c;
+  uint32_t key0, key1, gen;
+  const uint32_t* gen_dev;
+  int per_lane;          // candidates per lane of the agent scan (even)
+  uint32_t lane_magic;   // ceil(2^32 / per_lane): j / per_lane is the high word of j times this for the j here
+  unsigned long long* even;  // [worlds][pop] tagged positions of even and of odd steps
+  unsigned long long* odd;
+  unsigned long long* hand;  // [2][worlds of the launch][groups][chunks] tagged touches
+  uint32_t tag0;             // the tag of step t's touches is tag0 + t (a number of no launch before)
+  int world0, per_launch;    // the launch's first world and the most worlds it has
+  int groups;                // workgroups of a world
+  uint32_t* flag;            // [worlds]: a wait has ended without its word
+  unsigned long long wait_ticks;  // of the 100 MHz clock; 0: every wait fails (test hook)
+  int32_t* reward;       // [worlds][pop]
+  float2* pos_out;       // [worlds][pop] state after the last step
+  float2* vel_out;       // [worlds][pop]
+  uint32_t* counts_out;  // [worlds][n_items] or null: the book after the last step
+};
+
+// A lane's columns c0 .. c0 + HQ - 1 of the layers, rows in their natural order.
+template <int H, int LPA>
+struct ResidentSlice {
+  static constexpr int HQ = H / LPA;
+  float w1[kObs][HQ], b1[HQ], w2[H][HQ], b2[HQ], w3[HQ][2], b3[2];
+};
+template <int H, int LPA>
+__device__ __forceinline__ void resident_load(const float* __restrict__ th, int q, ResidentSlice<H, LPA>& s) {
+  constexpr int HQ = ResidentSlice<H, LPA>::HQ;
+  const int c0 = q * HQ;
+  const float* W1 = th;
+  const float* b1 = W1 + kObs * H;
+  const float* W2 = b1 + H;
+  const float* b2 = W2 + H * H;
+  const float* W3 = b2 + H;
+  const float* b3 = W3 + H * 2;
+#pragma unroll
+  for (int u = 0; u < HQ; ++u) {
+#pragma unroll
+    for (int i = 0; i < kObs; ++i) s.w1[i][u] = W1[i * H + c0 + u];
+#pragma unroll
+    for (int i = 0; i < H; ++i) s.w2[i][u] = W2[i * H + c0 + u];
+    s.b1[u] = b1[c0 + u], s.b2[u] = b2[c0 + u];
+    s.w3[u][0] = W3[(c0 + u) * 2], s.w3[u][1] = W3[(c0 + u) * 2 + 1];
+  }
+  s.b3[0] = b3[0], s.b3[1] = b3[1];
+}
+
+// Layer 2, sixteen lanes per agent: activation I of the agent, broadcast over its row inside the multiply-add.  A lane
+// move may not read a register in the two instructions after it is written: the statements that read a register first
+// (I < HQ) bring their own wait, and each chain runs through one of them per register before any other.
+template <int H, int I>
+__device__ __forceinline__ void row_layer(const ResidentSlice<H, 16>& s, const float (&mine)[H / 16],
+                                          float (&part)[H / 16]) {
+  constexpr int HQ = H / 16;
+  if constexpr (I < H) {
+#pragma unroll
+    for (int u = 0; u < HQ; ++u) {
+      if constexpr (I < HQ)
+        asm("s_nop 1\n\tv_fmac_f32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf"
+            : "+v"(part[u])
+            : "v"(mine[I % HQ]), "v"(s.w2[I][u]), "n"(I / HQ));
+      else
+        asm("v_fmac_f32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf"
+            : "+v"(part[u])
+            : "v"(mine[I % HQ]), "v"(s.w2[I][u]), "n"(I / HQ));
+    }
+    row_layer<H, I + 1>(s, mine, part);
+  }
+}
+
+template <int CTRL>
+__device__ __forceinline__ float lane_move(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float lane_value(float x, int lane) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane));
+}
+
+// The policy of dims (8, H, H, 2); every lane of the agent returns both outputs.  The sums are policy_forward's with
+// eight lanes per agent: layers 1 and 2 from the bias over the inputs in order, layer 3 as eight chains of H / 8 neurons
+// added in a tree of neighbours.
+template <int H, int LPA, bool TANH>
+__device__ __forceinline__ float2 resident_forward(const ResidentSlice<H, LPA>& s, const int (&act_rt)[3], int lane,
+                                                   const float (&obs)[kObs]) {
+  constexpr int HQ = ResidentSlice<H, LPA>::HQ;
+  const int act[3] = {TANH ? EVO_ACT_TANH : act_rt[0], TANH ? EVO_ACT_TANH : act_rt[1],
+                      TANH ? EVO_ACT_TANH : act_rt[2]};
+  float h1[HQ], part[HQ];
+#pragma unroll
+  for (int u = 0; u < HQ; ++u) {
+    h1[u] = s.b1[u];
+#pragma unroll
+    for (int i = 0; i < kObs; ++i) h1[u] = fmaf(obs[i], s.w1[i][u], h1[u]);
+    h1[u] = activate(h1[u], act[0]);
+    part[u] = s.b2[u];
+  }
+  if constexpr (LPA == 16) {
+    row_layer<H, 0>(s, h1, part);
+  } else {
+#pragma unroll
+    for (int i = 0; i < H; ++i) part[0] = fmaf(lane_value(h1[0], i), s.w2[i][0], part[0]);
+  }
+#pragma unroll
+  for (int u = 0; u < HQ; ++u) part[u] = activate(part[u], act[1]);
+  float o[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    float x = 0.f;
+    if constexpr (LPA == 16) {  // a chain starts in the even lane of a pair and ends in the odd one
+#pragma unroll
+      for (int u = 0; u < HQ; ++u) x = fmaf(part[u], s.w3[u][j], x);
+      x = lane_move<0xA0>(x);  // quad_perm 0,0,2,2
+#pragma unroll
+      for (int u = 0; u < HQ; ++u) x = fmaf(part[u], s.w3[u][j], x);
+      x = lane_move<0xF5>(x);  // quad_perm 1,1,3,3
+      x += partner<1>(x);
+      x += partner<2>(x);
+      x += partner<3>(x);
+    } else {  // a chain of eight lanes; its last lane holds the value
+      static_assert(LPA == 16 || H == 64, "a wave per agent: one neuron per lane, eight per chain");
+      x = part[0] * s.w3[0][j];
+      const float first = x;
+#pragma unroll
+      for (int k = 1; k < 8; ++k) {
+        const float before = lane_move<0x111>(x);  // row_shr:1
+        x = (lane & 7) == 0 ? first : fmaf(part[0], s.w3[0][j], before);
+      }
+      float p[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) p[k] = lane_value(x, 8 * k + 7);
+      x = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+    }
+    o[j] = activate(x + s.b3[j], act[2]);
+  }
+  return make_float2(o[0], o[1]);
+}
+
+// A wave-uniform value in a vector register (the scan's multiply-adds run at half rate on a scalar operand).
+__device__ __forceinline__ float in_vector(float uniform) {
+  float v;
+  asm("v_mov_b32 %0, %1" : "=v"(v) : "s"(uniform));
+  return v;
+}
+
+// 100 MHz, the same on the whole chip.
+__device__ __forceinline__ unsigned long long now_ticks() { return wall_clock64(); }
+
+// What a wait does every 64 looks: has the world been given up, or has this wait taken too long?
+__device__ __forceinline__ bool give_up(uint32_t* flag, unsigned long long wait_ticks, unsigned long long& since) {
+  const unsigned long long now = now_ticks();
+  if (since == 0) since = now;
+  if (now - since >= wait_ticks) __hip_atomic_store(flag, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u;
+}
+__device__ __forceinline__ unsigned long long peek(const unsigned long long* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void hand_over(unsigned long long* p, unsigned long long w) {
+  __hip_atomic_store(p, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+constexpr int kChunk = 32;     // slots of the item lists: two for each lane of a row of sixteen
+constexpr int kMaxChunks = 9;  // 256 items in two lists of whole chunks
+
+// Number of the lowest set bit; 0xFFFFFFFF of none.
+__device__ __forceinline__ uint32_t first_bit(uint32_t x) { return static_cast<uint32_t>(__builtin_ffs(x)) - 1u; }
+// Where in LDS.
+__device__ __forceinline__ uint32_t lds_address(const uint32_t* p) {
+  return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((const __attribute__((address_space(3))) uint32_t*)p));
+}
+// Minimum over an agent's eight lanes.
+__device__ __forceinline__ uint32_t agent_min(uint32_t x) {
+  x = min(x, static_cast<uint32_t>(partner_bits<0>(x)));
+  x = min(x, static_cast<uint32_t>(partner_bits<1>(x)));
+  return min(x, static_cast<uint32_t>(partner_bits<2>(x)));
+}
+// The nearest food and the nearest poison, as offsets; eight lanes per agent.  Smallest distance first, then the lowest
+// index that has it.  Both lists (of `food` and `poison` chunks) go together; the shorter one's last chunk is judged again.
+__device__ __forceinline__ float4 nearest_items(float2 p, const float2* list, int food, int poison, int q) {
+  Nearest n[2] = {{__builtin_inff(), 0x7fffffff}, {__builtin_inff(), 0x7fffffff}};
+#pragma unroll 1
+  for (int c = 0; c < max(food, poison); ++c) {
+    const int base[2] = {min(c, food - 1) * kChunk, (food + min(c, poison - 1)) * kChunk};
+    float4 x[2], y[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      x[j] = *reinterpret_cast<const float4*>(list + base[j] + 2 * q);
+      y[j] = *reinterpret_cast<const float4*>(list + base[j] + 16 + 2 * q);
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      nearest_offer<false>(n[j], p, x[j].x, x[j].y, base[j] + 2 * q, -1);
+      nearest_offer<false>(n[j], p, x[j].z, x[j].w, base[j] + 2 * q + 1, -1);
+      nearest_offer<false>(n[j], p, y[j].x, y[j].y, base[j] + 16 + 2 * q, -1);
+      nearest_offer<false>(n[j], p, y[j].z, y[j].w, base[j] + 16 + 2 * q + 1, -1);
+    }
+  }
+  uint32_t at[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const uint32_t d = __float_as_uint(n[j].d2), m = agent_min(d);
+    at[j] = agent_min(d == m ? static_cast<uint32_t>(n[j].idx) : 0x7fffffffu);
+    at[j] = min(at[j], static_cast<uint32_t>((food + poison) * kChunk - 1));  // (every list has an item at a finite place)
+  }
+  const float2 f = list[at[0]], g = list[at[1]];
+  return make_float4(f.x - p.x, f.y - p.y, g.x - p.x, g.y - p.y);
+}
+
+template <int H, bool TANH>
+__global__ __launch_bounds__(resident_threads(H)) void world_resident_kernel(const ResidentArgs a) {
+  constexpr int LPA = resident_lanes(H), APW = 64 / LPA, kAgents = resident_agents(H), kItemWaves = item_waves(H);
+  extern __shared__ float4 lds4[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int place = blockIdx.x / a.groups, group = blockIdx.x - place * a.groups, world = a.world0 + place;
+  const int n_food = a.c.n_food, n_items = a.c.n_items;
+  const int food_pad = pad_to(n_food, kChunk), slots = food_pad + pad_to(n_items - n_food, kChunk);
+  const int chunks = slots / kChunk;
+  // candidates: lane l judges agents l G .. l G + G - 1, which start at an odd number of 16-byte words from each other,
+  // so that sixteen lanes' 16-byte reads meet every bank once
+  const int G = a.per_lane, S = (G >> 1) & 1 ? G : G + 2;
+  const int region = 64 * S;
+  const int lists = kItemWaves * slots;
+  float4* s_near = lds4;                                             // [agents] offsets of the nearest food and poison
+  float2* s_own = reinterpret_cast<float2*>(s_near + kAgents);       // [agents] positions of the workgroup's agents
+  float2* s_pos = s_own + kAgents;                                   // the world's agents
+  float2* s_item = s_pos + region;                                   // [item waves][slots] where the items are
+  float2* s_next = s_item + lists;                                   // [item waves][slots] and where they go when eaten
+  uint32_t* s_count = reinterpret_cast<uint32_t*>(s_next + lists);   // [item waves][slots] times eaten
+  uint32_t* s_all = s_count + lists;                                 // [item waves][chunks] touched by anyone
+  uint32_t* s_hit = s_all + kItemWaves * kMaxChunks;                 // [chunks] touched by this workgroup
+  uint32_t* s_done = s_hit + kMaxChunks;                             // main waves whose touches are in s_hit
+  uint32_t* s_stop = s_done + 1;
+  const uint32_t gen = a.gen_dev ? *a.gen_dev : a.gen;
+  const float inf = __builtin_inff();
+  auto place_agent = [&](int j) {
+    const u32x4 w = philox4x32_10(static_cast<uint32_t>(j), static_cast<uint32_t>(world), gen, kTagAgent, a.key0, a.key1);
+    return make_float2(unit_open(w.x), unit_open(w.y));
+  };
+  // everybody's start; the slots of no agent lie infinitely far away
+#pragma unroll 1
+  for (int i = tid; i < region; i += resident_threads(H)) {
+    const int l = i / S, k = i - l * S, j = l * G + k;
+    s_pos[i] = k < G && j < a.pop ? place_agent(j) : make_float2(inf, inf);
+  }
+  if (tid < kAgents) s_own[tid] = place_agent(min(group * kAgents + tid, a.pop - 1));
+  if (tid < kItemWaves * kMaxChunks + kMaxChunks + 2) s_all[tid] = 0u;  // s_all, s_hit, s_done and s_stop
+  __syncthreads();
+
+  auto item_of = [&](int slot) {  // item index of a slot, or -1
+    const bool is_food = slot < food_pad;
+    const int i = is_food ? slot : n_food + slot - food_pad;
+    return i < (is_food ? n_food : n_items) ? i : -1;
+  };
+  auto place_item = [&](int i, uint32_t c) {
+    const u32x4 w = philox4x32_10(256u * c + static_cast<uint32_t>(i), static_cast<uint32_t>(world), gen, kTagItem,
+                                  a.key0, a.key1);
+    return make_float2(unit_open(w.x), unit_open(w.y));
+  };
+#pragma unroll 1
+  for (int j = tid; j < lists; j += resident_threads(H)) {
+    const int i = item_of(j % slots);
+    s_item[j] = i >= 0 ? place_item(i, 0u) : make_float2(inf, inf);
+    s_next[j] = i >= 0 ? place_item(i, 1u) : make_float2(inf, inf);
+    s_count[j] = 0u;
+  }
+  __syncthreads();
+  const int words = a.groups * chunks;  // a world's touches of a step
+  unsigned long long* hand = a.hand + static_cast<size_t>(place) * words;
+  const size_t half = static_cast<size_t>(a.per_launch) * words;
+
+  if (wave >= kMainWaves) {  // ---- item waves; the two barriers of a step are those of the main waves below
+    const int iw = wave - kMainWaves, q = lane & (kLanesPerAgent - 1);
+    const int mine = iw * kAgentsPerBlock + lane / kLanesPerAgent;
+    float2* food = s_item + iw * slots;
+    float2* next = s_next + iw * slots;
+    uint32_t* count = s_count + iw * slots;
+    uint32_t* all = s_all + iw * kMaxChunks;
+    auto settle = [] {  // LDS keeps a wave's order; this keeps the compiler's
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    auto touched = [&](int slot) {  // slot 2 q of a chunk in bit q of its word, slot 2 q + 1 in bit 16 + q
+      return ((all[slot / kChunk] >> ((slot & 1) * 16 + ((slot & (kChunk - 1)) >> 1))) & 1u) != 0u;
+    };
+    // what anybody touched moves on (false: given up)
+    auto collect = [&](int step) -> bool {
+      const unsigned long long* in = hand + (step & 1) * half;
+      const uint32_t tag = a.tag0 + static_cast<uint32_t>(step);
+      bool stop = false;
+#pragma unroll 1
+      for (int i = lane; i < words; i += 128) {  // two words at a time
+        const int j = i + 64 < words ? i + 64 : i;
+        unsigned long long w0, w1, since = 0;
+        for (uint32_t looks = 0;;) {
+          w0 = peek(in + i), w1 = peek(in + j);
+          if (static_cast<uint32_t>(w0 >> 32) == tag && static_cast<uint32_t>(w1 >> 32) == tag && a.wait_ticks) break;
+          if ((looks++ & 63) == 63 || !a.wait_ticks) {
+            if (give_up(a.flag + world, a.wait_ticks, since)) {
+              stop = true;
+              break;
+            }
+          }
+        }
+        if (static_cast<uint32_t>(w0)) atomicOr(all + i % chunks, static_cast<uint32_t>(w0));
+        if (j != i && static_cast<uint32_t>(w1)) atomicOr(all + j % chunks, static_cast<uint32_t>(w1));
+      }
+      settle();
+#pragma unroll 1
+      for (int slot = lane; slot < slots; slot += 64)  // (slots of no item are never touched)
+        if (touched(slot)) food[slot] = next[slot];
+      settle();
+      return __builtin_amdgcn_ballot_w64(stop) == 0;
+    };
+    // off the step's critical path: where the moved ones would go next
+    auto refill = [&] {
+#pragma unroll 1
+      for (int slot = lane; slot < slots; slot += 64)
+        if (touched(slot)) {
+          const uint32_t n = ++count[slot];
+          next[slot] = place_item(item_of(slot), n + 1u);
+        }
+      settle();
+      if (lane < chunks) all[lane] = 0u;
+      settle();
+    };
+    bool go_on = true;
+#pragma unroll 1
+    for (int t = 0; t < a.steps; ++t) {
+      if (t > 1) refill();
+      if (!go_on) *s_stop = 1u;
+      __syncthreads();
+      if (*s_stop) return;
+      if (t > 0) go_on = collect(t);
+      const float2 p = s_own[mine];
+      const float4 both = nearest_items(p, food, food_pad / kChunk, chunks - food_pad / kChunk, q);
+      if (q == 0) s_near[mine] = both;
+      __syncthreads();
+    }
+    if (a.counts_out && group == 0 && iw == 0) {
+      if (a.steps > 1) refill();
+      collect(a.steps);
+      refill();
+      for (int slot = lane; slot < slots; slot += 64) {
+        const int i = item_of(slot);
+        if (i >= 0) a.counts_out[static_cast<size_t>(world) * n_items + i] = count[slot];
+      }
+    }
+    return;
+  }
+
+  // ---- main waves
+  const int row = lane >> 4, q = lane & 15;
+  const int slot0 = wave * APW + (LPA == 16 ? row : 0);  // the agent's place in the workgroup
+  const bool live = group * kAgents + slot0 < a.pop;
+  const int agent = min(group * kAgents + slot0, a.pop - 1);  // lanes without an agent follow the last one and hand nothing over
+  const bool speaks = live && (LPA == 16 ? q : lane) == 0;
+  const size_t me = static_cast<size_t>(world) * a.pop + agent;
+  ResidentSlice<H, LPA> weights;
+  resident_load<H, LPA>(a.params + static_cast<size_t>(agent) * a.P, LPA == 16 ? q : lane, weights);
+  auto pos_slot = [&](int j) { return j + static_cast<int>(__umulhi(j, a.lane_magic)) * (S - G); };  // agent j's place
+  const int own_lane = agent / G;  // whose candidates the agent itself is among
+  int own_lanes[APW];              // the same of all the wave's agents
+#pragma unroll
+  for (int i = 0; i < APW; ++i) own_lanes[i] = __builtin_amdgcn_readlane(own_lane, 16 * i);
+  float2 p = s_own[slot0], v = make_float2(0.f, 0.f);
+  int reward = 0;
+  constexpr int kStride = LPA == 16 ? 2 : 4;  // chunks judged for touches at a time
+  const uint64_t live_lanes = __builtin_amdgcn_ballot_w64(live);
+
+#pragma unroll 1
+  for (int t = 0; t < a.steps; ++t) {
+    if (t > 0) {
+      const unsigned long long* in = (t & 1 ? a.odd : a.even) + static_cast<size_t>(world) * a.pop;
+      const uint32_t want = static_cast<uint32_t>(t) & 3u;
+      bool stop = false;
+#pragma unroll 1
+      for (int j = tid; j < a.pop; j += 2 * 64 * kMainWaves) {  // two words at a time
+        const int k = j + 64 * kMainWaves;
+        const bool two = k < a.pop;
+        const int k1 = two ? k : j;
+        unsigned long long w0, w1, since = 0;
+        for (uint32_t looks = 0;;) {
+          w0 = peek(in + j), w1 = peek(in + k1);
+          if ((static_cast<uint32_t>(w0) >> 30) == want && (static_cast<uint32_t>(w1) >> 30) == want && a.wait_ticks) break;
+          if ((looks++ & 63) == 63 || !a.wait_ticks) {
+            if (give_up(a.flag + world, a.wait_ticks, since)) {
+              stop = true;
+              break;
+            }
+          }
+        }
+        s_pos[pos_slot(j)] = make_float2(__uint_as_float(static_cast<uint32_t>(w0) & 0x3FFFFFFFu),
+                                         __uint_as_float(static_cast<uint32_t>(w0 >> 32)));
+        if (two)
+          s_pos[pos_slot(k)] = make_float2(__uint_as_float(static_cast<uint32_t>(w1) & 0x3FFFFFFFu),
+                                           __uint_as_float(static_cast<uint32_t>(w1 >> 32)));
+      }
+      if (stop) *s_stop = 1u;
+    }
+    __syncthreads();     // the positions of step t
+    if (*s_stop) return;  // set before this barrier or after the last one only: all leave together
+
+    // the nearest other agent of the wave's agents
+    float px[APW], py[APW];
+    uint32_t best[APW];
+#pragma unroll
+    for (int i = 0; i < APW; ++i) {
+      px[i] = in_vector(lane_value(p.x, 16 * i)), py[i] = in_vector(lane_value(p.y, 16 * i));
+      best[i] = kFar;
+    }
+    const float4* cand = reinterpret_cast<const float4*>(s_pos + lane * S);
+    auto judge = [&](const float4& c) {
+#pragma unroll
+      for (int i = 0; i < APW; ++i) {
+        const uint32_t d0 = __float_as_uint(dist2(c.x - px[i], c.y - py[i]));
+        const uint32_t d1 = __float_as_uint(dist2(c.z - px[i], c.w - py[i]));
+        best[i] = min(min(best[i], d0), d1);  // squares' sums order like their bits
+      }
+    };
+    const int units = G >> 1;
+    int u = 0;
+#pragma unroll 1
+    for (; u + 4 <= units; u += 4) {
+      float4 c[4];
+#pragma unroll
+      for (int n = 0; n < 4; ++n) c[n] = cand[u + n];
+#pragma unroll
+      for (int n = 0; n < 4; ++n) judge(c[n]);
+    }
+#pragma unroll 1
+    for (; u < units; ++u) judge(cand[u]);
+    // every agent met itself there: the lane that holds it drops out for it, and the agent's row judges that lane's
+    // other candidates in its place
+    uint32_t beside = kFar;
+#pragma unroll 1
+    for (int base = 0; base < G; base += 16) {
+      const int k = base + q;
+      const float2 c = s_pos[own_lane * S + min(k, G - 1)];
+      const uint32_t d = __float_as_uint(dist2(c.x - p.x, c.y - p.y));
+      beside = min(beside, ((k < G) & (own_lane * G + k != agent)) ? d : kFar);
+    }
+#pragma unroll
+    for (int i = 0; i < APW; ++i) best[i] = lane == own_lanes[i] ? kFar : best[i];
+    // minimum over the lanes, agent i's in row i (a wave per agent: in every lane)
+    uint32_t m;
+    if constexpr (APW == 4) {
+      const auto x = __builtin_amdgcn_permlane32_swap(best[0], best[2], false, false);
+      const auto y = __builtin_amdgcn_permlane32_swap(best[1], best[3], false, false);
+      const auto z = __builtin_amdgcn_permlane16_swap(min(x[0], x[1]), min(y[0], y[1]), false, false);
+      m = min(z[0], z[1]);
+    } else {
+      const auto x = __builtin_amdgcn_permlane32_swap(best[0], best[0], false, false);
+      m = min(x[0], x[1]);
+      const auto z = __builtin_amdgcn_permlane16_swap(m, m, false, false);
+      m = min(z[0], z[1]);
+    }
+    m = min(m, beside);
+    m = min(m, static_cast<uint32_t>(partner_bits<0>(m)));
+    m = min(m, static_cast<uint32_t>(partner_bits<1>(m)));
+    m = min(m, static_cast<uint32_t>(partner_bits<2>(m)));
+    m = min(m, static_cast<uint32_t>(partner_bits<3>(m)));
+    // lowest lane that holds it, then the lowest of that lane's candidates at this distance: the lowest index
+    uint32_t held_lo = 0, held_hi = 0;
+#pragma unroll
+    for (int i = 0; i < APW; ++i) {
+      const uint64_t held = __builtin_amdgcn_ballot_w64(best[i] == static_cast<uint32_t>(__builtin_amdgcn_readlane(m, 16 * i)));
+      held_lo = APW == 1 || row == i ? static_cast<uint32_t>(held) : held_lo;
+      held_hi = APW == 1 || row == i ? static_cast<uint32_t>(held >> 32) : held_hi;
+    }
+    const uint64_t near_by = __builtin_amdgcn_ballot_w64(beside == m);
+    uint32_t holder = min(first_bit(held_lo), first_bit(held_hi) | 32u);
+    holder = (static_cast<uint32_t>(near_by >> (16 * row)) & 0xFFFFu) != 0u ? min(holder, static_cast<uint32_t>(own_lane)) : holder;
+    const float2* theirs = s_pos + holder * S;
+    const int self = agent - static_cast<int>(holder) * G;  // the agent's own place among them, if any
+    auto find = [&](int base) {  // (bit number of nothing: -1)
+      const int k = base + q;
+      const float2 c = theirs[min(k, G - 1)];
+      const bool same = (k < G) & (k != self) & (__float_as_uint(dist2(c.x - p.x, c.y - p.y)) == m);
+      return first_bit(static_cast<uint32_t>(__builtin_amdgcn_ballot_w64(same) >> (16 * row)) & 0xFFFFu);
+    };
+    uint32_t slot = find(0);
+#pragma unroll 1
+    for (int base = 16; base < G; base += 16) {
+      const uint32_t later = find(base);
+      slot = static_cast<int>(slot) < 0 && static_cast<int>(later) >= 0 ? base + later : slot;
+    }
+    const float2 near = theirs[min(slot, static_cast<uint32_t>(G - 1))];
+    __syncthreads();  // the nearest items
+
+    const float4 item = s_near[slot0];
+    // the first chunks that the agent may touch, on their way during the policy
+    float4 ahead[LPA == 16 ? 2 : 1];
+#pragma unroll
+    for (int c = 0; c < (LPA == 16 ? 2 : 1); ++c)
+      ahead[c] = *reinterpret_cast<const float4*>(s_item + min(LPA == 16 ? c : row, chunks - 1) * kChunk + 2 * q);
+    const float obs[kObs] = {v.x, v.y, item.x, item.y, item.z, item.w, near.x - p.x, near.y - p.y};
+    const float2 action = resident_forward<H, LPA, TANH>(weights, a.act, lane, obs);
+    move_axis(a.c, action.x, p.x, v.x);
+    move_axis(a.c, action.y, p.y, v.y);
+    if ((LPA == 16 ? q : lane) == 0) s_own[slot0] = p;
+    if (speaks && t + 1 < a.steps)
+      hand_over((t & 1 ? a.even : a.odd) + me,
+                (static_cast<unsigned long long>(__float_as_uint(p.y)) << 32) | __float_as_uint(p.x) |
+                    (static_cast<uint32_t>(t + 1) & 3u) << 30);
+    // what the moved agents touch: the main waves' words meet in LDS, and the last of them tells the world
+    auto judge_items = [&](const float4& it, int chunk, uint64_t& even, uint64_t& odd) {
+      const float limit = chunk < chunks ? a.c.r2 : -1.f;  // (a chunk past the last one: nothing)
+      const bool hit0 = dist2(it.x - p.x, it.y - p.y) <= limit, hit1 = dist2(it.z - p.x, it.w - p.y) <= limit;
+      const int found = static_cast<int>(hit0) + static_cast<int>(hit1);
+      reward += chunk * kChunk < food_pad ? found : -found;
+      even = __builtin_amdgcn_ballot_w64(hit0) & live_lanes, odd = __builtin_amdgcn_ballot_w64(hit1) & live_lanes;
+    };
+#pragma unroll 1
+    for (int c = 0; c < chunks; c += kStride) {
+      uint32_t word;
+      if constexpr (LPA == 16) {  // two chunks, each judged by all rows: their words to lanes 0 and 1
+        uint64_t even[2], odd[2];
+        uint32_t w[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          if (c > 0) ahead[j] = *reinterpret_cast<const float4*>(s_item + min(c + j, chunks - 1) * kChunk + 2 * q);
+          judge_items(ahead[j], c + j, even[j], odd[j]);
+          uint32_t e = static_cast<uint32_t>(even[j] | even[j] >> 32), o = static_cast<uint32_t>(odd[j] | odd[j] >> 32);
+          e |= e >> 16, o |= o >> 16;
+          w[j] = (e & 0xFFFFu) | o << 16;
+        }
+        word = lane == 0 ? w[0] : w[1];
+      } else {  // four chunks, a row each: their words to lanes 0 .. 3
+        uint64_t even, odd;
+        if (c > 0) ahead[0] = *reinterpret_cast<const float4*>(s_item + min(c + row, chunks - 1) * kChunk + 2 * q);
+        judge_items(ahead[0], c + row, even, odd);
+        word = (static_cast<uint32_t>(even >> (16 * (lane & 3))) & 0xFFFFu) | static_cast<uint32_t>(odd >> (16 * (lane & 3))) << 16;
+      }
+      if (lane < kStride && c + lane < chunks) atomicOr(s_hit + c + lane, word);
+    }
+    // A wave's LDS operations are carried out in order: who counts last finds every wave's touches in what it reads next.
+    // (A fence here would also wait for the position's store, 800 cycles.)
+    if (lane < kMaxChunks) {
+      uint32_t before, bits;
+      asm volatile("ds_add_rtn_u32 %0, %2, %3\n\tds_read_b32 %1, %4\n\ts_waitcnt lgkmcnt(0)"
+                   : "=&v"(before), "=&v"(bits)
+                   : "v"(lds_address(s_done)), "v"(lane == 0 ? 1u : 0u), "v"(lds_address(s_hit + lane))
+                   : "memory");
+      if (__builtin_amdgcn_readfirstlane(before) == kMainWaves - 1) {
+        if (lane < chunks) {
+          const uint32_t tag = a.tag0 + static_cast<uint32_t>(t) + 1u;
+          hand_over(hand + ((t + 1) & 1) * half + group * chunks + lane, (static_cast<unsigned long long>(tag) << 32) | bits);
+          s_hit[lane] = 0u;
+        }
+        if (lane == 0) *s_done = 0u;
+      }
+    }
+  }
+  reward = agent_sum<16>(reward);
+  if constexpr (LPA == 64) {
+    reward += __shfl_xor(reward, 16);
+    reward += __shfl_xor(reward, 32);
+  }
+  if (speaks) {
+    a.reward[me] = reward;
+    a.pos_out[me] = p;
+    a.vel_out[me] = v;
+  }
+}
+
+// Plays the worlds again that world_resident_kernel gave up, step by step with world_step_block, one workgroup for four
+// worlds (a world of the four that was not given up gets the same result once more).  Nothing to do otherwise.
+struct RerunArgs {
+  const uint32_t* flag;  // [worlds]
+  int steps;
+  float2* pos[2];
+  uint32_t* book;        // counts[2] and hits[3]: 5 x [worlds][n_items]
+  uint32_t* counts_out;  // [worlds][n_items] or null
+};
+
+template <int H, bool TANH>
+__global__ __launch_bounds__(kStepThreads) void world_rerun_kernel(StepArgs a, RerunArgs r) {
+  extern __shared__ float4 lds4[];
+  const int world0 = blockIdx.x * kWorldsPerBlock, world1 = min(world0 + kWorldsPerBlock, a.worlds);
+  uint32_t any = 0;
+  for (int w = world0; w < world1; ++w) any |= r.flag[w];
+  if (!any) return;
+  if (a.gen_dev) a.gen = *a.gen_dev;
+  const size_t nb = static_cast<size_t>(a.worlds) * a.c.n_items;
+  for (int i = world0 * a.pop + threadIdx.x; i < world1 * a.pop; i += kStepThreads) {
+    const u32x4 w = philox4x32_10(static_cast<uint32_t>(i % a.pop), static_cast<uint32_t>(i / a.pop), a.gen, kTagAgent, a.key0, a.key1);
+    r.pos[0][i] = make_float2(unit_open(w.x), unit_open(w.y));
+    a.vel_out[i] = make_float2(0.f, 0.f);
+    a.reward[i] = 0;
+  }
+  for (int k = 0; k < 5; ++k)
+    for (int i = world0 * a.c.n_items + threadIdx.x; i < world1 * a.c.n_items; i += kStepThreads) r.book[k * nb + i] = 0u;
+  const int blocks = (a.pop + kAgentsPerBlock - 1) / kAgentsPerBlock;
+#pragma unroll 1
+  for (int t = 0; t < r.steps; ++t) {
+    // what the step before wrote is read by other waves of this workgroup (and its touches were set behind this
+    // compute unit's cache)
+    __threadfence();
+    __syncthreads();
+    a.pos_in = r.pos[t & 1], a.pos_out = r.pos[(t + 1) & 1];
+    a.counts_in = r.book + (t & 1) * nb, a.counts_out = r.book + ((t + 1) & 1) * nb;
+    a.hits_prev = t > 0 ? r.book + (2 + (t + 2) % 3) * nb : nullptr;
+    a.hits_cur = r.book + (2 + t % 3) * nb, a.hits_clear = r.book + (2 + (t + 1) % 3) * nb;
+#pragma unroll 1
+    for (int b = 0; b < blocks; ++b) {
+      world_step_block<H, TANH>(a, b, blockIdx.x, lds4);
+      __syncthreads();  // the staging area is free again
+    }
+  }
+  __threadfence();
+  __syncthreads();
+  if (r.counts_out)
+    for (int i = world0 * a.c.n_items + threadIdx.x; i < world1 * a.c.n_items; i += kStepThreads)
+      r.counts_out[i] = r.book[(r.steps & 1) * nb + i] + r.book[(2 + (r.steps - 1) % 3) * nb + i];
 }
 
 // ---- single-agent form: every member alone in its own copy of each world ---------------------------------
@@ -655,6 +1323,11 @@ struct ResetArgs {
   float2* vel;       // [worlds][pop]
   int32_t* reward;   // [worlds][pop]
   uint32_t* book;    // counts[2] and hits[3]: 5 x [worlds][n_items], all zero at the start
+  // of the launch with waits, or null: positions of odd steps (a step number no reader waits for first), touches and flags
+  unsigned long long* odd;
+  unsigned long long* hand;
+  uint32_t* flag;
+  int n_hand;
 };
 
 __global__ __launch_bounds__(256) void world_reset_kernel(ResetArgs a) {
@@ -666,8 +1339,11 @@ __global__ __launch_bounds__(256) void world_reset_kernel(ResetArgs a) {
     a.pos[i] = make_float2(unit_open(w.x), unit_open(w.y));
     a.vel[i] = make_float2(0.f, 0.f);
     a.reward[i] = 0;
+    if (a.odd) a.odd[i] = ~0ull;
   }
   if (i < 5 * a.worlds * a.n_items) a.book[i] = 0u;
+  if (i < a.n_hand) a.hand[i] = 0ull;
+  if (a.flag && i < a.worlds) a.flag[i] = 0u;
 }
 
 // fitness[a] = mean over the worlds of the summed reward (an exact integer sum, one division).
@@ -692,10 +1368,22 @@ __global__ __launch_bounds__(256) void world_counts_kernel(const uint32_t* count
 }
 
 struct Layout {
-  size_t pos[2], vel, reward, book, bytes;  // byte offsets into the workspace
+  size_t pos[2], vel, reward, book, hand, flag, bytes;  // byte offsets into the workspace
+  bool room;                                            // hand and flag are there
 };
 
-static Layout carve(int pop, int worlds, int n_items) {
+static int item_chunks(int n_food, int n_items) {
+  return (pad_to(n_food, kChunk) + pad_to(n_items - n_food, kChunk)) / kChunk;
+}
+// world_resident_kernel: workgroups of a world, and the words in which a world's touches of a step are handed over.
+static int resident_groups(int pop, int H) { return (pop + resident_agents(H) - 1) / resident_agents(H); }
+static size_t touch_words(int pop, int H, int chunks) {
+  return static_cast<size_t>(resident_groups(pop, H)) * chunks;
+}
+// Worlds of one launch of it.
+static int resident_worlds(int pop, int worlds, int H) { return std::min(worlds, kMaxResident / resident_groups(pop, H)); }
+
+static Layout carve(int pop, int worlds, int n_food, int n_items) {
   const size_t agents = static_cast<size_t>(pop) * worlds;
   auto up = [](size_t n) { return (n + 255) & ~size_t(255); };
   Layout l;
@@ -705,7 +1393,14 @@ static Layout carve(int pop, int worlds, int n_items) {
   l.vel = o, o += up(agents * sizeof(float2));
   l.reward = o, o += up(agents * sizeof(int32_t));
   l.book = o, o += up(5 * static_cast<size_t>(worlds) * n_items * sizeof(uint32_t));
-  l.bytes = o;
+  // room for the launch with waits wherever a hidden width could take it (at most 53 KB), unless it would be what makes
+  // the workspace too large for the built-in scratch
+  size_t words = 0;
+  for (int H : {32, 64}) words = std::max(words, touch_words(pop, H, item_chunks(n_food, n_items)) * resident_worlds(pop, worlds, H));
+  l.hand = o, l.flag = o + up(2 * words * sizeof(unsigned long long));
+  l.bytes = l.flag + up(static_cast<size_t>(worlds) * sizeof(uint32_t));
+  l.room = words > 0 && (o > EVO_STATIC_SCRATCH_BYTES || l.bytes <= EVO_STATIC_SCRATCH_BYTES);
+  if (!l.room) l.bytes = o;
   return l;
 }
 
@@ -784,16 +1479,85 @@ int forage_supported(const MlpShape& sh, int pop, int worlds, const float* cp) {
 size_t forage_workspace_bytes(int pop, int worlds, const float* cp) {
   WorldConst c;
   if (fill_const(cp, &c) || pop < 1 || worlds < 1) return 0;
-  return carve(pop, worlds, c.n_items).bytes;
+  return carve(pop, worlds, c.n_food, c.n_items).bytes;
+}
+
+// ---- the whole episode in one launch: host side ----
+// Launches with waits follow one another: two at a time could each hold a part of the chip and wait for the rest of it.
+struct ResidentTurn {
+  std::mutex m;
+  hipEvent_t done = nullptr;
+  bool used = false;
+};
+
+template <int H>
+static int launch_resident_acts(const ResidentArgs& a, int worlds, size_t lds, hipStream_t s) {
+  const bool all_tanh = a.act[0] == EVO_ACT_TANH && a.act[1] == EVO_ACT_TANH && a.act[2] == EVO_ACT_TANH;
+  const dim3 grid(worlds * a.groups), threads(resident_threads(H));
+  if (all_tanh) hipLaunchKernelGGL((world_resident_kernel<H, true>), grid, threads, lds, s, a);
+  else hipLaunchKernelGGL((world_resident_kernel<H, false>), grid, threads, lds, s, a);
+  return check_launch("world_resident_kernel");
+}
+static int launch_resident(int H, const ResidentArgs& a, int worlds, size_t lds, hipStream_t s) {
+  switch (H) {
+    case 16: return launch_resident_acts<16>(a, worlds, lds, s);
+    case 32: return launch_resident_acts<32>(a, worlds, lds, s);
+    default: return launch_resident_acts<64>(a, worlds, lds, s);
+  }
+}
+
+template <int H>
+static int launch_rerun_acts(const StepArgs& a, const RerunArgs& r, size_t lds, hipStream_t s) {
+  const bool all_tanh = a.act[0] == EVO_ACT_TANH && a.act[1] == EVO_ACT_TANH && a.act[2] == EVO_ACT_TANH;
+  const void* kernel = all_tanh ? reinterpret_cast<const void*>(&world_rerun_kernel<H, true>)
+                                : reinterpret_cast<const void*>(&world_rerun_kernel<H, false>);
+  if (lds > 64 * 1024) {
+    const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kMaxLdsBytes));
+    EVO_REQUIRE(e == hipSuccess, EVO_ERR_HIP, "forage: raising the LDS limit of the second run failed: %s", hipGetErrorString(e));
+  }
+  const dim3 grid((a.worlds + kWorldsPerBlock - 1) / kWorldsPerBlock);
+  if (all_tanh) hipLaunchKernelGGL((world_rerun_kernel<H, true>), grid, dim3(kStepThreads), lds, s, a, r);
+  else hipLaunchKernelGGL((world_rerun_kernel<H, false>), grid, dim3(kStepThreads), lds, s, a, r);
+  return check_launch("world_rerun_kernel");
+}
+static int launch_rerun(int H, const StepArgs& a, const RerunArgs& r, size_t lds, hipStream_t s) {
+  switch (H) {
+    case 16: return launch_rerun_acts<16>(a, r, lds, s);
+    case 32: return launch_rerun_acts<32>(a, r, lds, s);
+    default: return launch_rerun_acts<64>(a, r, lds, s);
+  }
+}
+
+// May this call take the launch with waits?  Not into a recorded graph (its replays would not take their turn), and
+// only with a compute unit per workgroup.  The turn of the device, or null.
+static ResidentTurn* resident_turn(int workgroups, hipStream_t s) {
+  static ResidentTurn turns[64];
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &capture) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  int device = 0, cus = 0;
+  if (capture != hipStreamCaptureStatusNone || hipGetDevice(&device) != hipSuccess || device < 0 || device >= 64 ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || workgroups > cus)
+    return nullptr;
+  ResidentTurn* turn = &turns[device];
+  std::lock_guard<std::mutex> lock(turn->m);
+  if (!turn->done && hipEventCreateWithFlags(&turn->done, hipEventDisableTiming) != hipSuccess) {
+    turn->done = nullptr;
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  return turn;
 }
 
 int launch_forage(const MlpShape& sh, const float* params, int pop, int worlds, int steps, const float* cp,
                   uint64_t seed, uint32_t gen, const uint32_t* gen_dev, void* work, float* fitness, float* pos_out,
-                  float* vel_out, int32_t* reward_out, uint32_t* counts_out, hipStream_t s) {
+                  float* vel_out, int32_t* reward_out, uint32_t* counts_out, uint64_t wait_ticks, hipStream_t s) {
   WorldConst c;
   int rc = fill_const(cp, &c);
   if (rc) return rc;
-  const Layout l = carve(pop, worlds, c.n_items);
+  const Layout l = carve(pop, worlds, c.n_food, c.n_items);
   char* base = static_cast<char*>(work);
   float2* pos[2] = {reinterpret_cast<float2*>(base + l.pos[0]), reinterpret_cast<float2*>(base + l.pos[1])};
   float2* vel = reinterpret_cast<float2*>(base + l.vel);
@@ -803,11 +1567,30 @@ int launch_forage(const MlpShape& sh, const float* params, int pop, int worlds, 
   uint32_t* counts[2] = {book, book + nb};
   uint32_t* hits[3] = {book + 2 * nb, book + 3 * nb, book + 4 * nb};
 
+  // The whole episode in one launch for as many worlds as the chip holds at once, one such launch after the other: where a
+  // world has at most 256 workgroups (any that is supported; at H = 64 pop <= 2048), and with constants that keep every position a number in [0, 1] (the tags
+  // of the handed-over positions need it).  Microseconds per step, 24 + 24 items, a launch per step / this way:
+  //   H = 32: 64 x 8 worlds 7.2 / 3.0, 1024 x 1 7.2 / 3.6, 1024 x 8 9.3 / 3.9, 4800 x 1 51 / 9.0, 64 x 512 27 / 13.4, 1024 x 64 62 / 29
+  //   H = 64: 64 x 8 13.2 / 3.1, 1024 x 2 11.6 / 4.0, 600 x 6 15.6 / 8.4, 1024 x 8 17.9 / 16.6
+  const int H = sh.dims[1], groups = resident_groups(pop, H), per_launch = resident_worlds(pop, worlds, H);
+  const bool tame = std::isfinite(cp[0]) && std::isfinite(cp[1]) && std::isfinite(cp[2]) && std::isfinite(cp[3]);
+  ResidentTurn* turn = nullptr;
+  if (tame && l.room && per_launch > 0 &&
+      static_cast<uint64_t>((worlds + per_launch - 1) / per_launch) * (static_cast<uint64_t>(steps) + 1) < (1ull << 32))
+    turn = resident_turn(groups * per_launch, s);
+
   ResetArgs ra;
   ra.pop = pop, ra.worlds = worlds, ra.n_items = c.n_items;
   ra.key0 = static_cast<uint32_t>(seed), ra.key1 = static_cast<uint32_t>(seed >> 32), ra.gen = gen, ra.gen_dev = gen_dev;
   ra.pos = pos[0], ra.vel = vel, ra.reward = reward, ra.book = book;
-  const int n_reset = static_cast<int>(std::max(static_cast<size_t>(worlds) * pop, 5 * nb));
+  ra.odd = nullptr, ra.hand = nullptr, ra.flag = nullptr, ra.n_hand = 0;
+  const int chunks = item_chunks(c.n_food, c.n_items);
+  if (turn) {
+    ra.odd = reinterpret_cast<unsigned long long*>(pos[1]);
+    ra.hand = reinterpret_cast<unsigned long long*>(base + l.hand), ra.n_hand = static_cast<int>(2 * touch_words(pop, H, chunks) * per_launch);
+    ra.flag = reinterpret_cast<uint32_t*>(base + l.flag);
+  }
+  const int n_reset = static_cast<int>(std::max({static_cast<size_t>(worlds) * pop, 5 * nb, static_cast<size_t>(ra.n_hand)}));
   hipLaunchKernelGGL(world_reset_kernel, dim3((n_reset + 255) / 256), dim3(256), 0, s, ra);
   rc = check_launch("world_reset_kernel");
   if (rc) return rc;
@@ -819,7 +1602,41 @@ int launch_forage(const MlpShape& sh, const float* params, int pop, int worlds, 
   a.key0 = ra.key0, a.key1 = ra.key1, a.gen = gen, a.gen_dev = gen_dev;
   a.vel_in = vel, a.vel_out = vel, a.reward = reward, a.accumulate = 1;
   a.actions_in = nullptr, a.obs_out = nullptr;
-  for (int t = 0; t < steps; ++t) {
+  if (turn) {
+    ResidentArgs b;
+    b.params = params, b.P = sh.P, b.pop = pop, b.worlds = worlds, b.steps = steps;
+    b.act[0] = sh.act[0], b.act[1] = sh.act[1], b.act[2] = sh.act[2];
+    b.c = c, b.key0 = a.key0, b.key1 = a.key1, b.gen = gen, b.gen_dev = gen_dev;
+    b.per_lane = pad_to((pop + 63) / 64, 2);
+    b.lane_magic = static_cast<uint32_t>(((1ull << 32) + b.per_lane - 1) / b.per_lane);
+    b.even = reinterpret_cast<unsigned long long*>(pos[0]), b.odd = reinterpret_cast<unsigned long long*>(pos[1]);
+    b.hand = ra.hand, b.groups = groups, b.flag = ra.flag, b.wait_ticks = wait_ticks;
+    b.reward = reward, b.pos_out = pos[steps & 1], b.vel_out = vel, b.counts_out = counts_out;
+    const int stride = (b.per_lane >> 1) & 1 ? b.per_lane : b.per_lane + 2;
+    const size_t slots = static_cast<size_t>(chunks) * kChunk;
+    const size_t lds = resident_agents(H) * (sizeof(float4) + sizeof(float2)) +
+                       (64 * static_cast<size_t>(stride) + 2 * item_waves(H) * slots) * sizeof(float2) +
+                       (item_waves(H) * (slots + kMaxChunks) + kMaxChunks + 2) * sizeof(uint32_t);
+    {
+      std::lock_guard<std::mutex> lock(turn->m);
+      hipError_t e = turn->used ? hipStreamWaitEvent(s, turn->done, 0) : hipSuccess;
+      EVO_REQUIRE(e == hipSuccess, EVO_ERR_HIP, "forage: waiting for the launch before failed: %s", hipGetErrorString(e));
+      b.per_launch = per_launch;
+      for (int w = 0; w < worlds; w += per_launch) {
+        b.world0 = w, b.tag0 = static_cast<uint32_t>(w / per_launch) * (static_cast<uint32_t>(steps) + 1u);
+        rc = launch_resident(H, b, std::min(per_launch, worlds - w), lds, s);
+        if (rc) return rc;
+      }
+      e = hipEventRecord(turn->done, s);
+      EVO_REQUIRE(e == hipSuccess, EVO_ERR_HIP, "forage: recording the launch failed: %s", hipGetErrorString(e));
+      turn->used = true;
+    }
+    RerunArgs r;
+    r.flag = ra.flag, r.steps = steps, r.pos[0] = pos[0], r.pos[1] = pos[1], r.book = book, r.counts_out = counts_out;
+    rc = launch_rerun(H, a, r, step_lds_bytes(pop, c.n_food, c.n_items), s);
+    if (rc) return rc;
+  }
+  for (int t = 0; t < (turn ? 0 : steps); ++t) {
     a.pos_in = pos[t & 1], a.pos_out = pos[(t + 1) & 1];
     a.counts_in = counts[t & 1], a.counts_out = counts[(t + 1) & 1];
     a.hits_prev = t > 0 ? hits[(t + 2) % 3] : nullptr;  // the page written by step t - 1
@@ -840,7 +1657,7 @@ int launch_forage(const MlpShape& sh, const float* params, int pop, int worlds, 
   if (e == hipSuccess && reward_out)
     e = hipMemcpyAsync(reward_out, reward, agents * sizeof(int32_t), hipMemcpyDeviceToDevice, s);
   EVO_REQUIRE(e == hipSuccess, EVO_ERR_HIP, "forage: copying the final state failed: %s", hipGetErrorString(e));
-  if (counts_out) {
+  if (counts_out && !turn) {
     // step steps - 1 read counts[(steps - 1) & 1] + hits of step steps - 2 into counts[steps & 1]; its own hits are
     // in hits[(steps - 1) % 3]
     hipLaunchKernelGGL(world_counts_kernel, dim3((static_cast<int>(nb) + 255) / 256), dim3(256), 0, s,

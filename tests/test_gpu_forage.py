@@ -215,6 +215,67 @@ def test_full_size_constant_actions_and_properties(evo):
     assert counts.min() > 0, "over 500 steps every item of every world is eaten at some point"
 
 
+def _state(evo, td, pd, params, pop, worlds, n_items, steps, wait_ticks=None):
+    out = dict(pos=torch.empty(worlds, pop, 2, dtype=torch.float32, device="cuda"),
+               vel=torch.empty(worlds, pop, 2, dtype=torch.float32, device="cuda"),
+               reward=torch.empty(worlds, pop, dtype=torch.int32, device="cuda"),
+               counts=torch.empty(worlds, n_items, dtype=torch.int32, device="cuda"))
+    if wait_ticks is None:
+        evo.evo_forage_state(td, pd, params, pop, steps, **out)
+    else:
+        evo.evo_forage_state_bounded(td, pd, params, pop, steps, wait_ticks, **out)
+    return out
+
+
+# agents per workgroup 32 (H = 64: 8), 64 lanes of candidates, items in chunks of 32 per list (256 items: nine chunks)
+@pytest.mark.parametrize("pop,worlds,H,steps,n_food,n_poison,acts",
+                         [(2, 1, 16, 9, 1, 1, (1, 1, 1)), (32, 3, 32, 9, 32, 32, (1, 1, 1)), (33, 3, 32, 9, 33, 32, (1, 1, 1)),
+                          (64, 2, 16, 12, 9, 6, (1, 2, 0)), (129, 2, 32, 9, 5, 7, (0, 0, 0)), (8, 2, 64, 9, 24, 24, (1, 1, 1)),
+                          (9, 4, 64, 9, 33, 223, (2, 1, 1)), (300, 4, 64, 12, 32, 33, (1, 1, 1)), (1000, 8, 32, 12, 24, 24, (1, 1, 1)),
+                          (1090, 7, 16, 9, 1, 255, (1, 1, 1)), (64, 130, 32, 5, 24, 24, (1, 1, 1)),
+                          (700, 5, 64, 5, 24, 24, (1, 1, 1)), (4800, 1, 32, 5, 24, 24, (1, 1, 1))])
+def test_the_episode_in_one_launch_is_the_episode_step_by_step(evo, pop, worlds, H, steps, n_food, n_poison, acts):
+    """Whole episodes with observation-driven policies: where every wait is given up the worlds are played again by the
+    step kernel's code, and both give the same bits (stacked agents and agents in corners among them: a wide thrust
+    drives many into the walls).  A workspace full of another call's words changes nothing."""
+    w = dict(forage.WORLD_DEFAULT, n_food=n_food, n_poison=n_poison, radius=0.0625, thrust=0.25, vmax=2.0)
+    pd = evo.make_policy_desc(evo.EVO_POLICY_MLP, (8, H, H, 2), acts)
+    params = dev(_random_policies(pop, (8, H, H, 2), 0.5, pop + H))
+    td = _task(evo, w, worlds, pop, pd)
+    n_items = n_food + n_poison
+    one = _state(evo, td, pd, params, pop, worlds, n_items, steps)
+    again = _state(evo, td, pd, params, pop, worlds, n_items, steps, 0)
+    after = _state(evo, td, pd, params, pop, worlds, n_items, steps)
+    for k in one:
+        assert torch.equal(one[k], again[k]), k
+        assert torch.equal(one[k], after[k]), k
+    assert pop < 32 or int(one["counts"].sum()) > 0, "items must be eaten"
+    fit = torch.empty(pop, dtype=torch.float32, device="cuda")
+    evo.rollout(td, pd, params, pop, steps, fit)
+    assert np.array_equal(host(fit), host(one["reward"]).sum(axis=0).astype(np.float32) / np.float32(worlds))
+
+
+def test_one_launch_episodes_on_two_streams(evo):
+    """Each launch fills the chip: they take turns, whatever stream they are on."""
+    w = dict(forage.WORLD_DEFAULT, radius=0.0625)
+    pd = evo.make_policy_desc(evo.EVO_POLICY_MLP, (8, 16, 16, 2), (1, 1, 1))
+    pop, worlds, steps = 1024, 8, 20
+    params = [dev(_random_policies(pop, (8, 16, 16, 2), 0.5, s)) for s in (1, 2)]
+    tds = [_task(evo, w, worlds, pop, pd) for _ in range(2)]
+    want = [_state(evo, td, pd, p, pop, worlds, 48, steps) for td, p in zip(tds, params)]
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    torch.cuda.synchronize()
+    got = [[], []]
+    for _ in range(4):
+        for i, s in enumerate(streams):
+            with torch.cuda.stream(s):
+                got[i].append(_state(evo, tds[i], pd, params[i], pop, worlds, 48, steps))
+    torch.cuda.synchronize()
+    for i in range(2):
+        for g in got[i]:
+            assert all(torch.equal(g[k], want[i][k]) for k in g)
+
+
 def test_errors_are_reported(evo):
     w = forage.WORLD_DEFAULT
     good = evo.make_policy_desc(evo.EVO_POLICY_MLP, (8, 32, 32, 2), (1, 1, 1))
