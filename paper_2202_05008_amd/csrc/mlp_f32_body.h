@@ -4,6 +4,8 @@
 #pragma once
 #include "kernels.h"
 
+#include <type_traits>
+
 namespace evo {
 
 struct MlpArgs {
@@ -40,19 +42,70 @@ __device__ __forceinline__ float activate(float x, int act) {
   return x;
 }
 
-// Sum over the 64 lanes of a wave in a fixed butterfly order (every lane gets the result).
+// Sum over the 64 lanes of a wave in a fixed butterfly order, distances 32 to 1 (every lane gets the result).  Register
+// to register: swaps of halves and rows, then rotations of a row (the lanes 8 and 4 places on hold what the lanes at these
+// distances hold, as the values repeat by then), then quad permutations.  (Through LDS, as shuffles, 0.3 us per sum.)
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(h[0]) + __uint_as_float(h[1]);
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xf, 0xf, false));  // row_ror:8
+  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x124, 0xf, 0xf, false));  // row_ror:4
+  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4e, 0xf, 0xf, false));   // quad_perm 2,3,0,1
+  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xb1, 0xf, 0xf, false));   // quad_perm 1,0,3,2
   return v;
 }
 
+// Neurons o0 .. o0 + G - 1 of a layer for the wave's 64 samples (bias, then the inputs in order).  Those behind the last one
+// are not stored; their weights are what follows in LDS (at most 7 floats behind the parameters), or, in memory, the
+// last neuron's.
+template <int G, typename WPtr>
+__device__ __forceinline__ void mlp_f32_neurons(const float* hin, float* hout, WPtr W, WPtr bias, int n_in, int n_out, int o0,
+                                                int s, int act) {
+  constexpr bool kInLds = !std::is_same<WPtr, const float*>::value;
+  float acc[G];
+  if (kInLds || o0 + G <= n_out) {
+#pragma unroll
+    for (int j = 0; j < G; ++j) acc[j] = bias[o0 + j];
+    // unrolled so that the weight and activation reads of several k are issued before the first is waited for
+#pragma unroll 4
+    for (int k = 0; k < n_in; ++k) {
+      const float hk = hin[k * kMlpTile + s];
+      const WPtr wr = W + k * n_out + o0;
+#pragma unroll
+      for (int j = 0; j < G; ++j) acc[j] = fmaf(hk, wr[j], acc[j]);
+    }
+  } else {
+    int at[G];
+#pragma unroll
+    for (int j = 0; j < G; ++j) at[j] = min(o0 + j, n_out - 1), acc[j] = bias[at[j]];
+#pragma unroll 4
+    for (int k = 0; k < n_in; ++k) {
+      const float hk = hin[k * kMlpTile + s];
+      const WPtr wr = W + k * n_out;
+#pragma unroll
+      for (int j = 0; j < G; ++j) acc[j] = fmaf(hk, wr[at[j]], acc[j]);
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < G; ++j)
+    if (o0 + j < n_out) hout[(o0 + j) * kMlpTile + s] = activate(acc[j], act);
+}
+
 // WPtr: pointer to the member's flat parameters (global memory: const float*; LDS: an address-space-3 pointer).
-// lds: 2 * a.ldw * 64 floats.  Every thread of the 256 returns; nothing is left in flight.  With a loss, thread 0
+// staged: null, or where in memory the parameters lie that theta is to be filled with first (theta in LDS then).
+// lds: 2 * a.ldw * 64 floats.  Every thread of the 64 WAVES returns; nothing is left in flight.  With a loss, thread 0
 // returns the tile's loss sum, which is also stored to a.partial when that is not null.
-template <int LOSS, typename WPtr>
-__device__ __forceinline__ float mlp_f32_body(const MlpArgs& a, WPtr theta, int member, int tile, float* lds) {
-  constexpr int TB = kMlpTile;
+// A small network is a chain of latencies: parameters and observations are requested together, once; the four waves
+// share every layer's neurons in groups as large as leaves all four something to do (an output layer of four neurons: one
+// per wave).  Against four neurons per wave at a time with their weights fetched four inputs ahead from memory, get_actions
+// from a recorded graph: 16-32-4, 64 members of 512 samples 8.4 -> 6.1 us, 1000 of 300 27 -> 22.8; 20-30-10, 64 of 512 11.0
+// -> 7.1; 8-24-24-4, 1000 of 128 17.4 -> 13.6.  Unrolled by four inputs: by eight, 74 registers, 20-30-10 takes 9.1.
+template <int LOSS, int WAVES = 4, typename WPtr>
+__device__ __forceinline__ float mlp_f32_body(const MlpArgs& a, WPtr theta, int member, int tile, float* lds,
+                                              float* theta_lds = nullptr, const float* staged = nullptr) {
+  constexpr int TB = kMlpTile, THREADS = 64 * WAVES;
   float* hin = lds;
   float* hout = lds + a.ldw * TB;
   const int tid = threadIdx.x;
@@ -62,12 +115,34 @@ __device__ __forceinline__ float mlp_f32_body(const MlpArgs& a, WPtr theta, int 
   const int b = b0 + s;
   const bool live = b < a.B;
   const float* obs = a.obs + static_cast<size_t>(member) * a.obs_stride;
-  const int D = a.sh.dims[0];
-  // stage the observation tile transposed: hin[d][sample]
+  const int D = a.sh.dims[0], P = a.sh.P;
+  float ahead[4];  // the first parameters, on their way with the observations
+  if (staged) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (THREADS * r < P) ahead[r] = staged[min(tid + THREADS * r, P - 1)];
+  }
+  // the observation tile transposed: hin[d][sample]; lane = sample, the waves take features in turn
+  {
+    const float* row = obs + static_cast<size_t>(min(b, a.B - 1)) * D;
+    if ((D & 3) == 0 && (reinterpret_cast<uintptr_t>(obs) & 15u) == 0) {
 #pragma unroll 4
-  for (int i = tid; i < D * TB; i += 256) {  // unrolled: the loads of four rounds are in flight together
-    const int ss = i / D, d = i - ss * D;
-    hin[d * TB + ss] = (b0 + ss < a.B) ? obs[static_cast<size_t>(b0 + ss) * D + d] : 0.f;
+      for (int d = 4 * wave; d < D; d += 4 * WAVES) {
+        const float4 v = *reinterpret_cast<const float4*>(row + d);
+        hin[d * TB + s] = live ? v.x : 0.f, hin[(d + 1) * TB + s] = live ? v.y : 0.f;
+        hin[(d + 2) * TB + s] = live ? v.z : 0.f, hin[(d + 3) * TB + s] = live ? v.w : 0.f;
+      }
+    } else {
+#pragma unroll 4
+      for (int d = wave; d < D; d += WAVES) hin[d * TB + s] = live ? row[d] : 0.f;
+    }
+  }
+  if (staged) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (tid + THREADS * r < P) theta_lds[tid + THREADS * r] = ahead[r];
+#pragma unroll 4
+    for (int i = tid + 4 * THREADS; i < P; i += THREADS) theta_lds[i] = staged[i];
   }
   __syncthreads();
   int off = 0;
@@ -75,33 +150,19 @@ __device__ __forceinline__ float mlp_f32_body(const MlpArgs& a, WPtr theta, int 
     const int n_in = a.sh.dims[l], n_out = a.sh.dims[l + 1], act = a.sh.act[l];
     const WPtr W = theta + off;
     const WPtr bias = W + n_in * n_out;
-    for (int o0 = wave * 4; o0 < n_out; o0 += 16) {
-      float acc[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) acc[j] = (o0 + j < n_out) ? bias[o0 + j] : 0.f;
-      if (o0 + 3 < n_out) {
-        // unrolled so that the weight and activation reads of four k are issued before the first is waited for
-        // (the sums still run in increasing k)
-#pragma unroll 4
-        for (int k = 0; k < n_in; ++k) {
-          const float hk = hin[k * TB + s];
-          const WPtr wr = W + k * n_out + o0;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) acc[j] = fmaf(hk, wr[j], acc[j]);
-        }
-      } else {
-#pragma unroll 4
-        for (int k = 0; k < n_in; ++k) {
-          const float hk = hin[k * TB + s];
-          const WPtr wr = W + k * n_out + o0;
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-            if (o0 + j < n_out) acc[j] = fmaf(hk, wr[j], acc[j]);
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        if (o0 + j < n_out) hout[(o0 + j) * TB + s] = activate(acc[j], act);
+    if (WAVES == 1) {
+      if (n_out > 4)
+        for (int o0 = 0; o0 < n_out; o0 += 8) mlp_f32_neurons<8>(hin, hout, W, bias, n_in, n_out, o0, s, act);
+      else
+        mlp_f32_neurons<4>(hin, hout, W, bias, n_in, n_out, 0, s, act);
+    } else if (n_out > 16) {
+      for (int o0 = 8 * wave; o0 < n_out; o0 += 32) mlp_f32_neurons<8>(hin, hout, W, bias, n_in, n_out, o0, s, act);
+    } else if (n_out > 8) {
+      if (4 * wave < n_out) mlp_f32_neurons<4>(hin, hout, W, bias, n_in, n_out, 4 * wave, s, act);
+    } else if (n_out > 4) {
+      if (2 * wave < n_out) mlp_f32_neurons<2>(hin, hout, W, bias, n_in, n_out, 2 * wave, s, act);
+    } else if (wave < n_out) {
+      mlp_f32_neurons<1>(hin, hout, W, bias, n_in, n_out, wave, s, act);
     }
     __syncthreads();
     float* t = hin;
@@ -114,7 +175,7 @@ __device__ __forceinline__ float mlp_f32_body(const MlpArgs& a, WPtr theta, int 
   if (LOSS == LOSS_NONE) {
     float* dst = a.out + (static_cast<size_t>(member) * a.B + b0) * A;
     const int rows = min(TB, a.B - b0);
-    for (int i = tid; i < rows * A; i += 256) {
+    for (int i = tid; i < rows * A; i += THREADS) {
       const int ss = i / A, o = i - ss * A;
       dst[i] = hin[o * TB + ss];
     }
@@ -126,12 +187,15 @@ __device__ __forceinline__ float mlp_f32_body(const MlpArgs& a, WPtr theta, int 
     if (LOSS == LOSS_CE) {
       const int y = min(max(static_cast<const int32_t*>(a.target)[b], 0), A - 1);  // labels outside [0, A) are clamped
       float mx = hin[s];
+#pragma unroll 4
       for (int o = 1; o < A; ++o) mx = fmaxf(mx, hin[o * TB + s]);
       float se = 0.f;
+#pragma unroll 4
       for (int o = 0; o < A; ++o) se += expf(hin[o * TB + s] - mx);
       loss = (mx + logf(se)) - hin[y * TB + s];
     } else {
       const float* tg = static_cast<const float*>(a.target) + (static_cast<size_t>(member) * a.B + b) * A;
+#pragma unroll 4
       for (int o = 0; o < A; ++o) {
         const float d = hin[o * TB + s] - tg[o];
         loss = fmaf(d, d, loss);

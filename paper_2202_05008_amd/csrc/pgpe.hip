@@ -383,8 +383,8 @@ __global__ __launch_bounds__(256) void raw_pairs_kernel(const float* __restrict_
   for (int k = threadIdx.x; k < pop / 2; k += 256) pairs_out[k] = pair_weights(fitness[2 * k], fitness[2 * k + 1], b);
 }
 
-// The pair weights of a small population inside a workgroup of 256: thread = member, which counts the keys below its own
-// (every lane reads the same 16 bytes at a time).  fitness: memory or LDS; ord: (pop rounded up to 4) words of LDS,
+// The pair weights of a small population inside a workgroup of 256: four threads per member (128 members: two, more: one),
+// which share the count of the keys below its own.  fitness: memory or LDS; ord: (pop rounded up to 4) words of LDS,
 // 16-byte aligned; c: pop floats of LDS; red: 256 doubles of LDS; pairs: pop / 2 float2 of LDS.  Ends with a barrier.
 __device__ __forceinline__ void small_pairs(const float* fitness, int pop, int shaping, uint32_t* ord, float* c, double* red,
                                             float2* pairs) {
@@ -392,17 +392,23 @@ __device__ __forceinline__ void small_pairs(const float* fitness, int pop, int s
   if (shaping) {
     stage_orderable(fitness, pop, padded, ord, 256);
     __syncthreads();
-    for (int m = tid; m < pop; m += 256) {
-      const uint64_t key_m = (static_cast<uint64_t>(ord[m]) << 32) | static_cast<uint32_t>(m);
+    const int share = pop <= 64 ? 2 : pop <= 128 ? 1 : 0, sharers = 1 << share;  // (log2 of the) threads per member
+    for (int m0 = 0; m0 < pop; m0 += 256 >> share) {
+      const int m = m0 + (tid >> share);
+      const uint64_t key_m = (static_cast<uint64_t>(ord[min(m, pop - 1)]) << 32) | static_cast<uint32_t>(m);
       uint32_t count = 0;
-      for (int j = 0; j < padded; j += 4) {
+#pragma unroll 2
+      for (int j = 4 * (tid & (sharers - 1)); j < padded; j += 4 * sharers) {
         const uint4 o = *reinterpret_cast<const uint4*>(ord + j);
         const uint32_t w[4] = {o.x, o.y, o.z, o.w};
 #pragma unroll
         for (int i = 0; i < 4; ++i)
           count += ((static_cast<uint64_t>(w[i]) << 32) | static_cast<uint32_t>(j + i)) < key_m ? 1u : 0u;
       }
-      c[m] = centered_rank(count, pop);
+      int sum = static_cast<int>(count);
+      if (share >= 1) sum += __builtin_amdgcn_update_dpp(0, sum, 0xb1, 0xf, 0xf, false);  // quad_perm 1,0,3,2
+      if (share >= 2) sum += __builtin_amdgcn_update_dpp(0, sum, 0x4e, 0xf, 0xf, false);  // quad_perm 2,3,0,1
+      if (m < pop && (tid & (sharers - 1)) == 0) c[m] = centered_rank(static_cast<uint32_t>(sum), pop);
     }
     __syncthreads();
     for (int k = tid; k < pop / 2; k += 256) pairs[k] = pair_weights(c[2 * k], c[2 * k + 1], 0.0);

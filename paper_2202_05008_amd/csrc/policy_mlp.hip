@@ -5,8 +5,9 @@
 // Tasks") one kernel: logits never leave the chip.
 //
 // Mapping: workgroup = (member, tile of 64 samples).  Lane = sample, so an activation
-// h[k][sample] is one conflict-free LDS read; the four waves take different groups of four
-// output neurons, whose weights W[k][o..o+3] are contiguous and wave-uniform (scalar loads).
+// h[k][sample] is one conflict-free LDS read; the four waves take different groups of
+// output neurons, whose weights W[k][o..] are contiguous and wave-uniform (LDS broadcasts; networks of
+// more than kStagedParams parameters: scalar loads).
 //
 // Four kernels, chosen by mlp_form below: any fan-in of 64 or more runs on the matrix cores with fp32 operands as two-term
 // scaled fp16 splits (mlp_f32_mfma_kernel or, the same bits, mlp_f32_short_kernel for wide layers and few workgroups;
@@ -22,10 +23,19 @@
 
 namespace evo {
 
-template <int LOSS>
-__global__ __launch_bounds__(256) void mlp_f32_kernel(MlpArgs a) {
+typedef __attribute__((address_space(3))) const float* lds_cfloat_ptr;
+
+// STAGED: the member's parameters pass through LDS, behind the activations; else they are read where they lie.
+template <int LOSS, bool STAGED, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void mlp_f32_kernel(MlpArgs a) {
   extern __shared__ float lds[];
-  mlp_f32_body<LOSS>(a, a.params + static_cast<size_t>(blockIdx.y) * a.sh.P, blockIdx.y, blockIdx.x, lds);
+  const float* theta = a.params + static_cast<size_t>(blockIdx.y) * a.sh.P;
+  if (STAGED) {
+    float* theta_lds = lds + 2 * a.ldw * kMlpTile;
+    mlp_f32_body<LOSS, WAVES>(a, (lds_cfloat_ptr)theta_lds, blockIdx.y, blockIdx.x, lds, theta_lds, theta);
+  } else {
+    mlp_f32_body<LOSS, WAVES>(a, theta, blockIdx.y, blockIdx.x, lds);
+  }
 }
 
 // ---- the matrix-core form ------------------------------------------------------------------------------
@@ -1002,6 +1012,10 @@ __global__ __launch_bounds__(512, 4) void mlp_f32_units_kernel(MlpArgs a, int gr
 //     and 18, 60-5 514 of 64 10.3 and 7.4
 //   enough samples that set-up and latency drop out: 16-32-4 2048 of 500 (6.6e8 products) 100 and 61, 600 of 1024 (3.9e8)
 //     47 and 52 with the loss
+// The vector form: parameters through LDS up to 16 KB of them (more would leave room for fewer workgroups); a tiny network
+// on a thousand workgroups and more by one wave each (3-4, 1000 of 300 samples: 9.8 us with four waves and 7.9 with one; 16
+// of 512: 3.0 and 3.4).
+constexpr int kStagedParams = 4096;
 enum MlpForm { FORM_VECTOR, FORM_SPLIT, FORM_F32 };
 static MlpForm mlp_form(const MlpShape& sh, int pop, int B) {
   int products = 0;
@@ -1091,19 +1105,26 @@ int launch_mlp_f32(const MlpShape& sh, const float* params, const float* obs, in
     return by_width(std::integral_constant<int, LOSS_MSE>());
   }
   a.ldw = sh.max_width;
-  const size_t shmem = sizeof(float) * 2 * a.ldw * kMlpTile;
-  auto launch = [&](auto kern) -> int {
+  const bool staged = sh.P <= kStagedParams;
+  const size_t shmem = sizeof(float) * (2 * a.ldw * kMlpTile + (staged ? sh.P + 8 : 0));
+  auto launch = [&](auto kern, int threads) -> int {
     if (shmem > 64 * 1024) {
       hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                          hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(shmem));
       EVO_REQUIRE(e == hipSuccess, EVO_ERR_HIP, "hipFuncSetAttribute failed: %s", hipGetErrorString(e));
     }
-    hipLaunchKernelGGL(kern, grid, dim3(256), shmem, s, a);
+    hipLaunchKernelGGL(kern, grid, dim3(threads), shmem, s, a);
     return check_launch("mlp_f32_kernel");
   };
-  if (loss == LOSS_NONE) return launch(mlp_f32_kernel<LOSS_NONE>);
-  if (loss == LOSS_CE) return launch(mlp_f32_kernel<LOSS_CE>);
-  return launch(mlp_f32_kernel<LOSS_MSE>);
+  auto by_size = [&](auto loss_c) -> int {
+    constexpr int L = decltype(loss_c)::value;
+    if (!staged) return launch(mlp_f32_kernel<L, false, 4>, 256);
+    const bool lone = sh.dims[0] < 16 && sh.P < (sh.n_layers == 1 ? 80 : 30) && static_cast<int64_t>(pop) * a.tiles >= 1024;
+    return lone ? launch(mlp_f32_kernel<L, true, 1>, 64) : launch(mlp_f32_kernel<L, true, 4>, 256);
+  };
+  if (loss == LOSS_NONE) return by_size(std::integral_constant<int, LOSS_NONE>());
+  if (loss == LOSS_CE) return by_size(std::integral_constant<int, LOSS_CE>());
+  return by_size(std::integral_constant<int, LOSS_MSE>());
 }
 
 // One wavefront per member: lanes read the partial sums coalesced (lane, lane + 64, ...) and the

@@ -147,6 +147,26 @@ def test_mlp_f32_bits_do_not_depend_on_the_population(evo, dims, acts, B, shared
             assert torch.equal(x[m0:m1], y)
 
 
+# The vector form: neurons in groups of 1, 2, 4 and 8 and the garbage behind a layer's last one, parameters around what a
+# workgroup requests ahead (1024) and stages (4096), features read four at a time or one by one, the same networks by one
+# wave (a tiny network on 1024 workgroups or more).  Tolerance: fp32 sums of at most 62 terms, as above.
+@pytest.mark.parametrize("dims,pop,B", [((1, 1), 1024, 3), ((3, 4), 1024, 64), ((7, 5, 1), 1100, 65), ((9, 7), 1030, 2), ((15, 4), 520, 128),
+                                        ((3, 4), 5, 65), ((4, 8, 9, 16, 17), 3, 66), ((8, 33, 3), 4, 64), ((20, 5), 2, 1), ((30, 31), 7, 130),
+                                        ((31, 31, 2), 6, 63), ((60, 68), 3, 40), ((62, 65), 2, 64), ((46, 87), 2, 33)])
+def test_mlp_f32_vector_form_groups_and_staging(evo, dims, pop, B):
+    acts = (1,) * (len(dims) - 2) + (0,)
+    params = gen.random_params(31, pop, mlp_param_count(dims), 0.4)
+    pd = evo.make_policy_desc(evo.EVO_POLICY_MLP, dims, acts)
+    for shared in (True, False):
+        obs = np.random.default_rng(32).standard_normal((B, dims[0]) if shared else (pop, B, dims[0])).astype(np.float32)
+        out = torch.full((pop + 1, B, dims[-1]), np.nan, dtype=torch.float32, device="cuda")
+        evo.pop_forward(pd, dev(params), dev(obs), 0 if shared else B * dims[0], out[:pop], pop, B)
+        got = host(out)
+        assert np.isnan(got[pop]).all()
+        some = sorted({0, 1, pop // 2, pop - 1})
+        assert_close(got[some], opolicy.mlp_forward(params[some], obs if shared else obs[some], dims, acts), 1e-5, "outputs")
+
+
 def test_mlp_f32_more_workgroups_than_one_grid_dimension_takes(evo):
     """65528 members of 131200 samples on the fp32 matrix form are 2^32 threads and more; the members' fitness is that of
     a few of them evaluated by themselves."""
