@@ -22,9 +22,11 @@ enum LossKind { LOSS_NONE = -1, LOSS_CE = 0, LOSS_MSE = 1 };
 constexpr int kMlpTile = 64;
 
 // fp32 MLP.  loss == LOSS_NONE: writes out[pop][B][A].  Otherwise writes the per-tile loss
-// sums partial[pop][tiles] (tiles = ceil(B / kMlpTile)).
+// sums partial[pop][tiles] (tiles = ceil(B / kMlpTile)) or, where one workgroup has all samples of a member, the fitness
+// = scale * their sum, and sets *finished.
 int launch_mlp_f32(const MlpShape& sh, const float* params, const float* obs, int64_t obs_stride, int pop, int B,
-                   float* out, int loss, const void* target, float* partial, hipStream_t s);
+                   float* out, int loss, const void* target, float* partial, float* fitness, float scale, bool* finished,
+                   hipStream_t s);
 
 // bf16-weight MLP on the matrix cores; same contract, one workgroup per member.
 int mlp_bf16_supported(const MlpShape& sh, int B);

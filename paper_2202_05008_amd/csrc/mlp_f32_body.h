@@ -20,6 +20,8 @@ struct MlpArgs {
   int tiles;
   int ldw;  // LDS row capacity (max width)
   int pop;
+  float* fitness;  // where the workgroup that has all of a member's samples puts scale * loss sum, or null: partial
+  float scale;
 };
 
 // tanh without branches: 1 - 2 / (e^{2|x|} + 1) through the hardware's exp2 and reciprocal (absolute error about
@@ -55,6 +57,12 @@ __device__ __forceinline__ float wave_sum(float v) {
   v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4e, 0xf, 0xf, false));   // quad_perm 2,3,0,1
   v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xb1, 0xf, 0xf, false));   // quad_perm 1,0,3,2
   return v;
+}
+
+// What finalize_kernel makes of a member's partial sums (at most 64 of them, in LDS), by one wave; valid in every lane.
+__device__ __forceinline__ float member_loss(const float* sums, int tiles) {
+  const int lane = threadIdx.x & 63;
+  return wave_sum(lane < tiles ? 0.f + sums[lane] : 0.f);
 }
 
 // Neurons o0 .. o0 + G - 1 of a layer for the wave's 64 samples (bias, then the inputs in order).  Those behind the last one
@@ -95,8 +103,11 @@ __device__ __forceinline__ void mlp_f32_neurons(const float* hin, float* hout, W
 
 // WPtr: pointer to the member's flat parameters (global memory: const float*; LDS: an address-space-3 pointer).
 // staged: null, or where in memory the parameters lie that theta is to be filled with first (theta in LDS then).
+// tid: the thread among the 64 WAVES that work on this tile (a workgroup may hold two such teams on tiles of their own, of
+// which the first stages the parameters).
 // lds: 2 * a.ldw * 64 floats.  Every thread of the 64 WAVES returns; nothing is left in flight.  With a loss, thread 0
-// returns the tile's loss sum, which is also stored to a.partial when that is not null.
+// returns the tile's loss sum, which is also stored to a.partial, or as the fitness of a member of one tile, where that is
+// not null.
 // A small network is a chain of latencies: parameters and observations are requested together, once; the four waves
 // share every layer's neurons in groups as large as leaves all four something to do (an output layer of four neurons: one
 // per wave).  Against four neurons per wave at a time with their weights fetched four inputs ahead from memory, get_actions
@@ -104,11 +115,11 @@ __device__ __forceinline__ void mlp_f32_neurons(const float* hin, float* hout, W
 // -> 7.1; 8-24-24-4, 1000 of 128 17.4 -> 13.6.  Unrolled by four inputs: by eight, 74 registers, 20-30-10 takes 9.1.
 template <int LOSS, int WAVES = 4, typename WPtr>
 __device__ __forceinline__ float mlp_f32_body(const MlpArgs& a, WPtr theta, int member, int tile, float* lds,
-                                              float* theta_lds = nullptr, const float* staged = nullptr) {
+                                              float* theta_lds = nullptr, const float* staged = nullptr,
+                                              int tid = threadIdx.x) {
   constexpr int TB = kMlpTile, THREADS = 64 * WAVES;
   float* hin = lds;
   float* hout = lds + a.ldw * TB;
-  const int tid = threadIdx.x;
   const int s = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int b0 = tile * TB;
@@ -203,7 +214,10 @@ __device__ __forceinline__ float mlp_f32_body(const MlpArgs& a, WPtr theta, int 
     }
   }
   loss = wave_sum(loss);
-  if (s == 0 && a.partial) a.partial[static_cast<size_t>(member) * a.tiles + tile] = loss;
+  if (s == 0) {
+    if (a.fitness) a.fitness[member] = a.scale * loss;
+    else if (a.partial) a.partial[static_cast<size_t>(member) * a.tiles + tile] = loss;
+  }
   return loss;
 }
 

@@ -1052,7 +1052,7 @@ int pgpe_generation_small(pgpe_state* st, uint64_t seed, int32_t pop, const MlpS
   unsigned n_tell;
   g.tell = tell_args(st, nullptr, nullptr, nullptr, nullptr, &n_tell);
   g.mlp.sh = sh, g.mlp.params = nullptr, g.mlp.obs = obs, g.mlp.obs_stride = obs_stride, g.mlp.B = B;
-  g.mlp.out = nullptr, g.mlp.target = target, g.mlp.partial = nullptr;
+  g.mlp.out = nullptr, g.mlp.target = target, g.mlp.partial = nullptr, g.mlp.fitness = nullptr;
   g.mlp.tiles = (B + kMlpTile - 1) / kMlpTile, g.mlp.ldw = sh.max_width, g.mlp.pop = pop;
   const long total = static_cast<long>(pop) * g.mlp.tiles;
   const size_t lds_a = sizeof(float) * (4 * static_cast<size_t>(g.tell.nquads) + 2 * static_cast<size_t>(g.mlp.ldw) * kMlpTile);

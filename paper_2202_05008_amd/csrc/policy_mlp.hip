@@ -38,6 +38,22 @@ __global__ __launch_bounds__(64 * WAVES) void mlp_f32_kernel(MlpArgs a) {
   }
 }
 
+// Two tiles, all samples of a member, in one workgroup of two teams, which adds the two sums up as finalize_kernel would: no
+// launch of that kernel.
+template <int LOSS>
+__global__ __launch_bounds__(512) void mlp_f32_pair_kernel(MlpArgs a, float* __restrict__ fitness) {
+  extern __shared__ float lds[];
+  __shared__ float sums[2];
+  const int team = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8), tid = threadIdx.x & 255, member = blockIdx.x;
+  float* theta_lds = lds + 4 * a.ldw * kMlpTile;
+  const float* theta = a.params + static_cast<size_t>(member) * a.sh.P;
+  const float loss = mlp_f32_body<LOSS>(a, (lds_cfloat_ptr)theta_lds, member, team, lds + 2 * team * a.ldw * kMlpTile, theta_lds,
+                                        team == 0 ? theta : nullptr, tid);
+  if (tid == 0) sums[team] = loss;
+  __syncthreads();
+  if (threadIdx.x == 0) fitness[member] = a.scale * (sums[0] + sums[1]);
+}
+
 // ---- the matrix-core form ------------------------------------------------------------------------------
 // Workgroup = (member, tile of 128 or 64 samples), eight waves (two per SIMD).  A wave owns sixteen samples from the
 // observations to the loss: a layer is computed transposed on 16 x 16 tiles (rows = neurons: A operand, the member's
@@ -424,9 +440,12 @@ __global__ __launch_bounds__(64 * kMfmaWaves, KSM <= 4 ? 4 : 2) void mlp_f32_mfm
   if (LOSS == LOSS_NONE) return;
   if (lane == 0) red_s[wave] = loss;
   __syncthreads();
-  if (tid < wg_tiles && b0 / kMlpTile + tid < a.tiles)   // one partial sum per 64 samples
-    a.partial[static_cast<size_t>(member) * a.tiles + b0 / kMlpTile + tid] =
-        (red_s[4 * tid] + red_s[4 * tid + 1]) + (red_s[4 * tid + 2] + red_s[4 * tid + 3]);
+  auto sum64 = [&](int tile) { return (red_s[4 * tile] + red_s[4 * tile + 1]) + (red_s[4 * tile + 2] + red_s[4 * tile + 3]); };
+  if (a.fitness) {  // one or two sums: finalize_kernel's butterfly adds nothing but zeros to them
+    if (tid == 0) a.fitness[member] = a.scale * (a.tiles == 2 ? sum64(0) + sum64(1) : sum64(0));
+  } else if (tid < wg_tiles && b0 / kMlpTile + tid < a.tiles) {  // one partial sum per 64 samples
+    a.partial[static_cast<size_t>(member) * a.tiles + b0 / kMlpTile + tid] = sum64(tid);
+  }
 }
 
 // ---- the split form for few workgroups ------------------------------------------------------------------------
@@ -732,7 +751,9 @@ __global__ __launch_bounds__(64 * kMfmaWaves, 2) void mlp_f32_short_kernel(MlpAr
     if (lane == 0) red_s[wave] = loss;
   }
   __syncthreads();
-  if (tid == 0) a.partial[static_cast<size_t>(member) * a.tiles + tile] = (red_s[0] + red_s[1]) + (red_s[2] + red_s[3]);
+  const float sum = (red_s[0] + red_s[1]) + (red_s[2] + red_s[3]);
+  if (tid == 0 && a.fitness) a.fitness[member] = a.scale * sum;
+  else if (tid == 0) a.partial[static_cast<size_t>(member) * a.tiles + tile] = sum;
 }
 
 // ---- the fp32 matrix form ------------------------------------------------------------------------------
@@ -994,7 +1015,17 @@ __global__ __launch_bounds__(512, 4) void mlp_f32_units_kernel(MlpArgs a, int gr
   for (int piece = wave; piece < pieces; piece += 8) {   // one partial sum per 64 samples, added as the vector form does
     const int at = piece * kMlpTile + lane;
     const float loss = wave_sum(first * kMlpTile + at < s_end ? loss_s[at] : 0.f);
-    if (lane == 0) a.partial[static_cast<size_t>(member) * a.tiles + first + piece] = loss;
+    if (lane == 0) {
+      if (a.fitness) bias_s[piece] = loss;  // (the biases are done with)
+      else a.partial[static_cast<size_t>(member) * a.tiles + first + piece] = loss;
+    }
+  }
+  if (a.fitness) {
+    __syncthreads();
+    if (wave == 0) {
+      const float loss = member_loss(bias_s, a.tiles);
+      if (lane == 0) a.fitness[member] = a.scale * loss;
+    }
   }
 }
 
@@ -1029,7 +1060,8 @@ static MlpForm mlp_form(const MlpShape& sh, int pop, int B) {
 }
 
 int launch_mlp_f32(const MlpShape& sh, const float* params, const float* obs, int64_t obs_stride, int pop, int B,
-                   float* out, int loss, const void* target, float* partial, hipStream_t s) {
+                   float* out, int loss, const void* target, float* partial, float* fitness, float scale, bool* finished,
+                   hipStream_t s) {
   EVO_REQUIRE(sh.max_width <= 256, EVO_ERR_UNSUPPORTED, "fp32 MLP: layer widths above 256 are not supported (%d)",
               sh.max_width);
   MlpArgs a;
@@ -1037,6 +1069,13 @@ int launch_mlp_f32(const MlpShape& sh, const float* params, const float* obs, in
   a.out = out, a.target = target, a.partial = partial;
   a.tiles = (B + kMlpTile - 1) / kMlpTile;
   a.pop = pop;
+  a.fitness = nullptr, a.scale = scale;
+  // a workgroup has all samples of its member: it writes the fitness itself
+  auto whole_member = [&](bool yes) {
+    if (loss == LOSS_NONE || !yes) return;
+    a.fitness = fitness;
+    *finished = true;
+  };
   const dim3 grid(a.tiles, pop);
   const MlpForm form = mlp_form(sh, pop, B);
   if (form == FORM_F32) {
@@ -1046,6 +1085,7 @@ int launch_mlp_f32(const MlpShape& sh, const float* params, const float* obs, in
     const int wgs = (a.tiles + group - 1) / group;
     const size_t lds = f32_lds_bytes(sh, group);
     const bool spread = pop < 64;
+    whole_member(wgs == 1);
     auto launch_units = [&](auto kern) -> int {
       if (lds > 64 * 1024) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -1075,6 +1115,7 @@ int launch_mlp_f32(const MlpShape& sh, const float* params, const float* obs, in
       int kp = 32;      // widest fan-in, padded to the matrix instruction's 32
       for (int l = 0; l < sh.n_layers; ++l) kp = max(kp, (sh.dims[l] + 31) & ~31);
       a.ldw = kp;
+      whole_member(a.tiles == 1);
       // two fp16 terms of a layer's input and the maxima, or the network's output in their place
       const size_t input = static_cast<size_t>(2) * kMlpTile * (kp + 8) * 2 + (kMfmaWaves + 1) * kMlpTile * sizeof(float);
       const size_t lds = std::max(input, sh.dims[sh.n_layers] * kMlpTile * sizeof(float));
@@ -1092,6 +1133,7 @@ int launch_mlp_f32(const MlpShape& sh, const float* params, const float* obs, in
     }
     const int wg_tiles = static_cast<int64_t>(pop) * ((a.tiles + 1) / 2) >= 256 ? 2 : 1;
     const int wgs = (a.tiles + wg_tiles - 1) / wg_tiles;
+    whole_member(wgs == 1);
     auto launch_mfma = [&](auto kern) -> int {
       hipLaunchKernelGGL(kern, dim3(8 * ((pop + 7) / 8) * wgs), dim3(64 * kMfmaWaves), 0, s, a, wg_tiles);
       return check_launch("mlp_f32_mfma_kernel");
@@ -1106,6 +1148,18 @@ int launch_mlp_f32(const MlpShape& sh, const float* params, const float* obs, in
   }
   a.ldw = sh.max_width;
   const bool staged = sh.P <= kStagedParams;
+  whole_member(a.tiles == 1);
+  // two tiles in one workgroup while the chip is not full (us with finalize_kernel / this way: 16-32-4, 64 members of 100
+  // 7.6 / 6.7, 512 of 128 9.8 / 8.6, but 1000 of 128 13.4 / 14.4; four tiles gain nothing, more lose)
+  const size_t pair_lds = sizeof(float) * (4 * a.ldw * kMlpTile + sh.P + 8);
+  if (loss != LOSS_NONE && staged && a.tiles == 2 && pop <= 512 && pair_lds <= 64 * 1024) {
+    a.partial = nullptr, *finished = true;
+    auto launch_pair = [&](auto kern) -> int {
+      hipLaunchKernelGGL(kern, dim3(pop), dim3(512), pair_lds, s, a, fitness);
+      return check_launch("mlp_f32_pair_kernel");
+    };
+    return loss == LOSS_CE ? launch_pair(mlp_f32_pair_kernel<LOSS_CE>) : launch_pair(mlp_f32_pair_kernel<LOSS_MSE>);
+  }
   const size_t shmem = sizeof(float) * (2 * a.ldw * kMlpTile + (staged ? sh.P + 8 : 0));
   auto launch = [&](auto kern, int threads) -> int {
     if (shmem > 64 * 1024) {

@@ -93,7 +93,7 @@ extern "C" int pop_forward(const policy_desc* pd, const void* params_dev, const 
                 "pop_forward: obs_member_stride must be 0 or B*D");
     if (pd->dtype == EVO_F32)
       return launch_mlp_f32(sh, static_cast<const float*>(params_dev), obs_dev, obs_member_stride, pop, B, out_dev,
-                            LOSS_NONE, nullptr, nullptr, s);
+                            LOSS_NONE, nullptr, nullptr, nullptr, 0.f, nullptr, s);
     rc = mlp_bf16_supported(sh, B);
     if (rc) return rc;
     return launch_mlp_bf16(sh, static_cast<const uint16_t*>(params_dev), obs_dev, obs_member_stride, pop, B, out_dev,
@@ -299,11 +299,12 @@ static int rollout_impl(const task_desc* td, const policy_desc* pd, const void* 
     return launch_mlp_bf16(sh, static_cast<const uint16_t*>(params_dev), td->obs_dev, td->obs_member_stride, pop,
                            td->B, nullptr, loss, td->target_dev, fitness_dev, s);
   }
-  rc = launch_mlp_f32(sh, static_cast<const float*>(params_dev), td->obs_dev, td->obs_member_stride, pop, td->B,
-                      nullptr, loss, td->target_dev, partial, s);
-  if (rc) return rc;
   const float scale = loss == LOSS_CE ? -1.0f / static_cast<float>(td->B)
                                       : -1.0f / (static_cast<float>(td->B) * static_cast<float>(A));
+  bool finished = false;
+  rc = launch_mlp_f32(sh, static_cast<const float*>(params_dev), td->obs_dev, td->obs_member_stride, pop, td->B,
+                      nullptr, loss, td->target_dev, partial, fitness_dev, scale, &finished, s);
+  if (rc || finished) return rc;
   return launch_finalize(partial, pop, n_part, scale, fitness_dev, s);
 }
 
