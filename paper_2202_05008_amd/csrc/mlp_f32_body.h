@@ -68,12 +68,30 @@ __device__ __forceinline__ float member_loss(const float* sums, int tiles) {
 // Neurons o0 .. o0 + G - 1 of a layer for the wave's 64 samples (bias, then the inputs in order).  Those behind the last one
 // are not stored; their weights are what follows in LDS (at most 7 floats behind the parameters), or, in memory, the
 // last neuron's.
-template <int G, typename WPtr>
+// QUADS: rows start on 16 bytes, so four weights take one LDS read.
+template <int G, bool QUADS, typename WPtr>
 __device__ __forceinline__ void mlp_f32_neurons(const float* hin, float* hout, WPtr W, WPtr bias, int n_in, int n_out, int o0,
                                                 int s, int act) {
   constexpr bool kInLds = !std::is_same<WPtr, const float*>::value;
   float acc[G];
-  if (kInLds || o0 + G <= n_out) {
+  if constexpr (QUADS) {
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) const f4* quads;
+#pragma unroll
+    for (int j = 0; j < G; j += 4) {
+      const f4 b = *(quads)(bias + o0 + j);
+      acc[j] = b[0], acc[j + 1] = b[1], acc[j + 2] = b[2], acc[j + 3] = b[3];
+    }
+#pragma unroll 4
+    for (int k = 0; k < n_in; ++k) {
+      const float hk = hin[k * kMlpTile + s];
+      f4 w[G / 4];
+#pragma unroll
+      for (int j = 0; j < G / 4; ++j) w[j] = *(quads)(W + k * n_out + o0 + 4 * j);
+#pragma unroll
+      for (int j = 0; j < G; ++j) acc[j] = fmaf(hk, w[j >> 2][j & 3], acc[j]);
+    }
+  } else if (kInLds || o0 + G <= n_out) {
 #pragma unroll
     for (int j = 0; j < G; ++j) acc[j] = bias[o0 + j];
     // unrolled so that the weight and activation reads of several k are issued before the first is waited for
@@ -161,19 +179,27 @@ __device__ __forceinline__ float mlp_f32_body(const MlpArgs& a, WPtr theta, int 
     const int n_in = a.sh.dims[l], n_out = a.sh.dims[l + 1], act = a.sh.act[l];
     const WPtr W = theta + off;
     const WPtr bias = W + n_in * n_out;
+    constexpr bool kQuads = !std::is_same<WPtr, const float*>::value && WAVES > 1;
+    const bool quads = kQuads && ((off | n_out) & 3) == 0;  // (theta itself starts on 16 bytes)
     if (WAVES == 1) {
       if (n_out > 4)
-        for (int o0 = 0; o0 < n_out; o0 += 8) mlp_f32_neurons<8>(hin, hout, W, bias, n_in, n_out, o0, s, act);
+        for (int o0 = 0; o0 < n_out; o0 += 8) mlp_f32_neurons<8, false>(hin, hout, W, bias, n_in, n_out, o0, s, act);
       else
-        mlp_f32_neurons<4>(hin, hout, W, bias, n_in, n_out, 0, s, act);
+        mlp_f32_neurons<4, false>(hin, hout, W, bias, n_in, n_out, 0, s, act);
     } else if (n_out > 16) {
-      for (int o0 = 8 * wave; o0 < n_out; o0 += 32) mlp_f32_neurons<8>(hin, hout, W, bias, n_in, n_out, o0, s, act);
+      if (quads)
+        for (int o0 = 8 * wave; o0 < n_out; o0 += 32) mlp_f32_neurons<8, kQuads>(hin, hout, W, bias, n_in, n_out, o0, s, act);
+      else
+        for (int o0 = 8 * wave; o0 < n_out; o0 += 32) mlp_f32_neurons<8, false>(hin, hout, W, bias, n_in, n_out, o0, s, act);
     } else if (n_out > 8) {
-      if (4 * wave < n_out) mlp_f32_neurons<4>(hin, hout, W, bias, n_in, n_out, 4 * wave, s, act);
+      if (4 * wave < n_out) {
+        if (quads) mlp_f32_neurons<4, kQuads>(hin, hout, W, bias, n_in, n_out, 4 * wave, s, act);
+        else mlp_f32_neurons<4, false>(hin, hout, W, bias, n_in, n_out, 4 * wave, s, act);
+      }
     } else if (n_out > 4) {
-      if (2 * wave < n_out) mlp_f32_neurons<2>(hin, hout, W, bias, n_in, n_out, 2 * wave, s, act);
+      if (2 * wave < n_out) mlp_f32_neurons<2, false>(hin, hout, W, bias, n_in, n_out, 2 * wave, s, act);
     } else if (wave < n_out) {
-      mlp_f32_neurons<1>(hin, hout, W, bias, n_in, n_out, wave, s, act);
+      mlp_f32_neurons<1, false>(hin, hout, W, bias, n_in, n_out, wave, s, act);
     }
     __syncthreads();
     float* t = hin;

@@ -28,7 +28,7 @@ typedef __attribute__((address_space(3))) const float* lds_cfloat_ptr;
 // STAGED: the member's parameters pass through LDS, behind the activations; else they are read where they lie.
 template <int LOSS, bool STAGED, int WAVES>
 __global__ __launch_bounds__(64 * WAVES) void mlp_f32_kernel(MlpArgs a) {
-  extern __shared__ float lds[];
+  extern __shared__ __attribute__((aligned(16))) float lds[];
   const float* theta = a.params + static_cast<size_t>(blockIdx.y) * a.sh.P;
   if (STAGED) {
     float* theta_lds = lds + 2 * a.ldw * kMlpTile;
@@ -42,10 +42,10 @@ __global__ __launch_bounds__(64 * WAVES) void mlp_f32_kernel(MlpArgs a) {
 // launch of that kernel.
 template <int LOSS>
 __global__ __launch_bounds__(512) void mlp_f32_pair_kernel(MlpArgs a, float* __restrict__ fitness) {
-  extern __shared__ float lds[];
-  __shared__ float sums[2];
+  extern __shared__ __attribute__((aligned(16))) float lds[];  // (and no other shared array: the parameters start on 16 bytes)
   const int team = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8), tid = threadIdx.x & 255, member = blockIdx.x;
   float* theta_lds = lds + 4 * a.ldw * kMlpTile;
+  float* sums = theta_lds + a.sh.P + 8;
   const float* theta = a.params + static_cast<size_t>(member) * a.sh.P;
   const float loss = mlp_f32_body<LOSS>(a, (lds_cfloat_ptr)theta_lds, member, team, lds + 2 * team * a.ldw * kMlpTile, theta_lds,
                                         team == 0 ? theta : nullptr, tid);
@@ -1151,7 +1151,7 @@ int launch_mlp_f32(const MlpShape& sh, const float* params, const float* obs, in
   whole_member(a.tiles == 1);
   // two tiles in one workgroup while the chip is not full (us with finalize_kernel / this way: 16-32-4, 64 members of 100
   // 7.6 / 6.7, 512 of 128 9.8 / 8.6, but 1000 of 128 13.4 / 14.4; four tiles gain nothing, more lose)
-  const size_t pair_lds = sizeof(float) * (4 * a.ldw * kMlpTile + sh.P + 8);
+  const size_t pair_lds = sizeof(float) * (4 * a.ldw * kMlpTile + sh.P + 8 + 2);
   if (loss != LOSS_NONE && staged && a.tiles == 2 && pop <= 512 && pair_lds <= 64 * 1024) {
     a.partial = nullptr, *finished = true;
     auto launch_pair = [&](auto kern) -> int {
