@@ -1038,7 +1038,9 @@ __global__ __launch_bounds__(512, 4) void mlp_f32_units_kernel(MlpArgs a, int gr
 //   products per sample >= 1100: 32-32-4 (1152), 514 members of 300 samples 27 and 21, 64 of 512 11.7 and 7.8;
 //     below, 8-24-24-4 (864) 1000 of 128 17.4 and 19.5, 8-16-3 4096 of 16 13.7 and 29
 //   one piece of samples each, many members (half of a workgroup's waves have no samples) >= 1900: 16-32-32-4 (1664)
-//     2048 of 64 29 and 33 with the loss, 40-40-8 (1920) 29 and 27
+//     2048 of 64 29 and 33 with the loss; >= 2800 from 700 members on where hidden widths are multiples of four (four
+//     weights per LDS read in the vector form): 40-40-8 (1920) 1000 of 50 11.8 and 14.8, 2048 of 64 20 and 26,
+//     36-36-36-4 (2736) 1000 of 50 16 and 21, 4096 of 16 50 and 74 with the loss
 //   a width of 48 or more (the vector form keeps 512 bytes of LDS per width, few workgroups fit): 8-64-2 1000 of 128 66
 //     and 18, 60-5 514 of 64 10.3 and 7.4
 //   enough samples that set-up and latency drop out: 16-32-4 2048 of 500 (6.6e8 products) 100 and 61, 600 of 1024 (3.9e8)
@@ -1050,13 +1052,16 @@ constexpr int kStagedParams = 4096;
 enum MlpForm { FORM_VECTOR, FORM_SPLIT, FORM_F32 };
 static MlpForm mlp_form(const MlpShape& sh, int pop, int B) {
   int products = 0;
+  // the vector form reads four weights at a time (44-44-9, 4096 of 16 without a loss: 44 us and 40)
+  bool quads = sh.n_layers > 1 && (sh.max_width <= 40 || B > 16);
   for (int l = 0; l < sh.n_layers; ++l) {
     if (sh.dims[l] >= 64) return FORM_SPLIT;
     products += sh.dims[l] * sh.dims[l + 1];
+    quads &= sh.dims[l + 1] % 4 == 0 || l + 1 == sh.n_layers;
   }
   if (sh.max_width > kF32MaxWidth) return FORM_VECTOR;
-  const bool single = B <= kMlpTile && pop > 1024;
-  return sh.max_width >= 48 || products >= (single ? 1900 : 1100) || 1.0 * products * pop * B >= 6e8 ? FORM_F32 : FORM_VECTOR;
+  const bool single = B <= kMlpTile && pop > (quads ? 700 : 1024);
+  return sh.max_width >= 48 || products >= (single ? (quads ? 2800 : 1900) : 1100) || 1.0 * products * pop * B >= 6e8 ? FORM_F32 : FORM_VECTOR;
 }
 
 int launch_mlp_f32(const MlpShape& sh, const float* params, const float* obs, int64_t obs_stride, int pop, int B,
