@@ -47,8 +47,8 @@ static inline size_t ws_arrays_bytes(int pop_max) {
   return ((static_cast<size_t>(pop_max) * 2 + 2 * kNormBlocks) * 4 + 255) & ~size_t(255);
 }
 constexpr int kSmallSumWords = 2 * 4096;  // the loss sums of the one-launch generation, two words each
-constexpr unsigned kGradNormParts = kSmallSumWords;
-static inline size_t ws_bytes(int pop_max) { return ws_arrays_bytes(pop_max) + 256 + 4 * kSmallSumWords; }
+constexpr unsigned kGradNormParts = 8192;        // workgroups of tell whose partial sums ClipUp takes, three words each
+static inline size_t ws_bytes(int pop_max) { return ws_arrays_bytes(pop_max) + 256 + 4 * 3 * kGradNormParts; }
 
 static inline Workspace ws_carve(void* base, int pop_max) {
   Workspace w;
@@ -444,7 +444,8 @@ struct TellArgs {
   int P, nquads, N, KS;
   uint32_t gen, key0, key1;
   const uint32_t* gen_dev;  // when set: t is read here and the bias corrections are formed in the kernel
-  float* norm_part;        // ClipUp: one partial sum of g_mu^2 per workgroup, or null
+  float* norm_part;        // ClipUp: [3][norm_parts] partial sums of g_mu^2, vel^2 and vel g_mu, one per workgroup, or null
+  int norm_parts;
   float inv_n, lr_mu, lr_sigma, max_change, beta1, beta2, eps, bc1, bc2, momentum;
 };
 
@@ -534,7 +535,7 @@ __device__ __forceinline__ void tell_block(TellArgs a, int block, PAIRS pairs, f
     *reinterpret_cast<float4*>(mine + 4) = make_float4(B[0], B[1], B[2], B[3]);
   }
   __syncthreads();
-  float sq = 0.f;
+  float sq = 0.f, vv = 0.f, vg = 0.f;
   for (int p = tid; p < 4 * QPB; p += 256) {
     const int c = block * QPB * 4 + p;
     if (c >= a.P) break;
@@ -564,7 +565,8 @@ __device__ __forceinline__ void tell_block(TellArgs a, int block, PAIRS pairs, f
       a.mu[c] += vel;
     } else {
       a.v[c] = g_mu;  // ClipUp needs |g_mu| over all of P first: the gradient waits in v
-      sq = fmaf(g_mu, g_mu, sq);
+      const float vel = a.m[c];
+      sq = fmaf(g_mu, g_mu, sq), vv = fmaf(vel, vel, vv), vg = fmaf(vel, g_mu, vg);
     }
     if (SRULE == 0) {
       const float lim = a.max_change * sg;
@@ -578,8 +580,9 @@ __device__ __forceinline__ void tell_block(TellArgs a, int block, PAIRS pairs, f
   }
   if (OPT == OPT_CLIPUP_GRAD && a.norm_part) {
     __syncthreads();  // the partial sums have been read
-    const float t = block_sum256(sq, part);
-    if (tid == 0) a.norm_part[block] = t;
+    const float t = block_sum256(sq, part), tv = block_sum256(vv, part + 4), tg = block_sum256(vg, part + 8);
+    if (tid == 0)
+      a.norm_part[block] = t, a.norm_part[a.norm_parts + block] = tv, a.norm_part[2 * a.norm_parts + block] = tg;
   }
 }
 
@@ -737,8 +740,7 @@ __global__ __launch_bounds__(256) void generation_small_kernel(GenSmallArgs g) {
 }
 
 // ---- ClipUp: two norms over P, each as partial sums in a fixed order ------------------------------------------
-// |g|^2 comes as one partial sum per workgroup of tell (at most kGradNormParts of them, else per workgroup of
-// sqnorm_kernel), |vel|^2 as one per workgroup of the velocity kernel.
+// The sums come per workgroup of tell (at most kGradNormParts of them) and one launch does the rest; with more workgroups |g|^2 per workgroup of sqnorm_kernel and |vel|^2 per workgroup of the velocity kernel, in two launches.
 // Their totals: total256, the same bits in every thread of every workgroup (one thread adding 256 partial sums in turn
 // made each of the two kernels that need a total 7..10 us long).
 // part[b] = sum of x[i]^2 over the elements of workgroup b (grid-stride, kNormBlocks workgroups).
@@ -775,6 +777,53 @@ __global__ __launch_bounds__(256) void clipup_velocity_kernel(float* __restrict_
   if (first < (P & 3)) one(vel[(P & ~3) + first], g[(P & ~3) + first]);
   const float t = block_sum256(acc, scratch);
   if (threadIdx.x == 0) part_v[blockIdx.x] = t;
+}
+
+// Both in one launch, where tell has left the sums of g^2, vel^2 and vel g: the norm of the new velocity
+//   |momentum vel + s g|^2 = momentum^2 vel^2 + 2 momentum s vel g + s^2 g^2,  s = step / |g|,
+// is known before any of it is formed (in fp64; the clip only matters where |vel| exceeds max_speed, which no old velocity
+// does, so nothing cancels: the norm's error against 64 bits, 143 clipped steps of 500..300000 parameters: 4.0e-9 rms, at
+// most 1.8e-8; by a sum over the new velocity's elements 6.0e-9 and 3.4e-8).  Bound by latency: the sums, their total, then
+// three loads and two stores per quad.  Alone, the two launches and this one: 6.0 + 4.6 and 5.5 us at P = 45530, 6.7 + 5.3
+// and 6.7 us at 300007, for at most 0.3 us more in tell.
+__global__ __launch_bounds__(256) void clipup_step_kernel(float* __restrict__ mu, float* __restrict__ vel,
+                                                          const float* __restrict__ g, int P, float momentum, float step,
+                                                          float max_speed, const float* __restrict__ part, int n) {
+  __shared__ double red[3][256];
+  const int tid = threadIdx.x;
+  double acc[3] = {0.0, 0.0, 0.0};
+#pragma unroll 4
+  for (int i = tid; i < n; i += 256)
+#pragma unroll
+    for (int k = 0; k < 3; ++k) acc[k] += static_cast<double>(part[k * n + i]);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) red[k][tid] = acc[k];
+  __syncthreads();
+  for (int s = 128; s > 0; s >>= 1) {
+    if (tid < s)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) red[k][tid] += red[k][tid + s];
+    __syncthreads();
+  }
+  const double gg = red[0][0], vv = red[1][0], vg = red[2][0];
+  const float scale = gg > 0.0 ? static_cast<float>(static_cast<double>(step) / sqrt(gg)) : 0.f;
+  const double m = momentum, sc = scale;
+  const double speed = sqrt(fmax(m * m * vv + 2.0 * m * sc * vg + sc * sc * gg, 0.0));
+  const float clip = speed > static_cast<double>(max_speed) ? static_cast<float>(static_cast<double>(max_speed) / speed) : 1.0f;
+  auto one = [&](float& v, float gi, float& x) {
+    v = fmaf(scale, gi, momentum * v) * clip;
+    x += v;
+  };
+  const int first = blockIdx.x * 256 + tid, stride = gridDim.x * 256;
+#pragma unroll 4
+  for (int i = first; i < P / 4; i += stride) {
+    const float4 gi = reinterpret_cast<const float4*>(g)[i];
+    float4 v = reinterpret_cast<float4*>(vel)[i], x = reinterpret_cast<float4*>(mu)[i];
+    one(v.x, gi.x, x.x), one(v.y, gi.y, x.y), one(v.z, gi.z, x.z), one(v.w, gi.w, x.w);
+    reinterpret_cast<float4*>(vel)[i] = v;
+    reinterpret_cast<float4*>(mu)[i] = x;
+  }
+  if (first < (P & 3)) one(vel[(P & ~3) + first], g[(P & ~3) + first], mu[(P & ~3) + first]);
 }
 
 // Clip the velocity to max_speed and move mu.
@@ -963,8 +1012,9 @@ static TellArgs tell_args(const pgpe_state* st, const float* fitness, float* gmu
   a.bc2 = static_cast<float>(1.0 / (1.0 - pow(static_cast<double>(c.beta2), static_cast<double>(st->t))));
   const int QPB = 256 / KS;
   *blocks_out = static_cast<unsigned>((a.nquads + QPB - 1) / QPB);
-  // the words of the one-launch generation, which ClipUp never runs as, take the partial sums of |g|^2
+  // the words of the one-launch generation, which ClipUp never runs as, take the partial sums
   a.norm_part = c.optimizer == EVO_OPT_CLIPUP && *blocks_out <= kGradNormParts ? reinterpret_cast<float*>(ws.gen + 64) : nullptr;
+  a.norm_parts = static_cast<int>(*blocks_out);
   return a;
 }
 
@@ -1014,15 +1064,15 @@ static int run_tell(pgpe_state* st, const float* fitness, float* gmu, float* gsg
   rc = check_launch("tell_kernel");
   if (rc || gmu || c.optimizer != EVO_OPT_CLIPUP) return rc;
   // ClipUp: |g|, velocity and its norm, clip and move; the gradient waits in v
-  const float* part_g = a.norm_part;
-  int n_g = static_cast<int>(blocks);
-  if (part_g == nullptr) {
-    hipLaunchKernelGGL(sqnorm_kernel, dim3(kNormBlocks), dim3(256), 0, s, st->v, P, ws.norm);
-    part_g = ws.norm, n_g = kNormBlocks;
-  }
   const int grid = (P + 1023) / 1024 < kNormBlocks ? (P + 1023) / 1024 : kNormBlocks;  // four parameters per thread
-  hipLaunchKernelGGL(clipup_velocity_kernel, dim3(grid), dim3(256), 0, s, st->m, st->v, P, c.momentum, c.lr_mu, part_g, n_g,
-                     ws.norm + kNormBlocks);
+  if (a.norm_part) {
+    hipLaunchKernelGGL(clipup_step_kernel, dim3(grid), dim3(256), 0, s, st->mu, st->m, st->v, P, c.momentum, c.lr_mu, c.max_speed,
+                       a.norm_part, a.norm_parts);
+    return check_launch("clipup_step_kernel");
+  }
+  hipLaunchKernelGGL(sqnorm_kernel, dim3(kNormBlocks), dim3(256), 0, s, st->v, P, ws.norm);
+  hipLaunchKernelGGL(clipup_velocity_kernel, dim3(grid), dim3(256), 0, s, st->m, st->v, P, c.momentum, c.lr_mu, ws.norm,
+                     kNormBlocks, ws.norm + kNormBlocks);
   hipLaunchKernelGGL(clipup_apply_kernel, dim3(grid), dim3(256), 0, s, st->mu, st->m, P, c.max_speed,
                      ws.norm + kNormBlocks, grid);
   return check_launch("clipup kernels");
@@ -1064,7 +1114,7 @@ int pgpe_generation_small(pgpe_state* st, uint64_t seed, int32_t pop, const MlpS
                 "pgpe_generation: %u update workgroups for %ld evaluation workgroups, %zu bytes of LDS: not a small problem",
                 n_tell, total, lds);
   }
-  static_assert(kSmallSumWords == 2 * kSmallMaxTiles, "two words per sum");
+  static_assert(kSmallSumWords == 2 * kSmallMaxTiles && kSmallSumWords <= 3 * kGradNormParts, "two words per sum, in the room");
   Workspace ws = ws_carve(st->work, c.pop_max);
   g.done = ws.gen + 16, g.launches = ws.gen + 32;  // inside the 256 bytes kept for the generation word
   g.sums = reinterpret_cast<uint64_t*>(ws.gen + 64);  // behind them

@@ -266,6 +266,27 @@ def test_clipup_norms_at_the_edges(evo, P, pop):
         assert_close(host(g.m), o.m, 1e-5, "velocity, generation %d" % (it + 1))
 
 
+# The norm of the new velocity from sums that tell leaves, three per workgroup: one workgroup, the 64-way split of the pair
+# loop (2844 workgroups), the last size whose sums have room and the first that takes its norms from separate passes.
+# A clipped velocity has the length max_speed: a parameter is rounded twice and the factor once, and a partial sum over a
+# workgroup's 256 parameters at most 1 + 6 + 2 times, which the square root halves: 8 x 2^-24 < 5e-7.
+@pytest.mark.parametrize("P,pop", [(5, 4), (1027, 6), (45490, 130), (8388608, 2), (8388608 + 1100, 2)])
+def test_clipup_clips_to_its_speed(evo, P, pop):
+    g, _ = _states(evo, P, pop, gen.initial_mu(4, P), optimizer=1, lr_mu=0.1, max_speed=0.105)
+    params = torch.empty(pop, P, dtype=torch.float32, device="cuda")
+    clipped = 0
+    for it in range(5):
+        mu = g.mu.clone()
+        g.ask(5 + it, pop, params)
+        g.tell(dev(gen.random_fitness(80 + it, pop)))
+        speed = float(g.m.double().norm())
+        assert speed <= 0.105 * (1 + 5e-7)
+        clipped += speed >= 0.105 * (1 - 5e-7)
+        # factor and sum may be one fma: the sum's rounding, here and there, and that of the velocity
+        assert bool(((g.mu - (mu + g.m)).abs() <= 2.0 ** -23 * (g.mu.abs() + g.m.abs())).all())
+    assert clipped, "five steps at momentum 0.9 must have hit the speed bound"
+
+
 def test_clipup_zero_gradient_and_config_errors(evo):
     P, pop = 100, 8
     mu0 = gen.initial_mu(7, P)
