@@ -43,7 +43,7 @@ MEASURED_TRAFFIC_BYTES = {
     "cfg4": 807197617,     # profiles/mlp_bf16_stream_kernel_cfg4.md
     "cfg5": 4305387571,    # profiles/ask_sphere_tell_kernels_cfg5.md (ask)
     "seq2seq": 890661888,  # profiles/lstm_seq2seq_kernel_seq2seq.md (algorithmic 598 MB: the rest is register spill traffic)
-    "forage": 6920192,     # profiles/world_step_kernel_forage.md (per step launch: weights 5.8 MB + positions)
+    "forage": 325433344,   # profiles/world_resident_kernel_forage.md (positions handed over and polled in each of 500 steps)
     "forage_solo": 5979136,  # profiles/world_solo_kernel_forage_solo.md (the weights, read once; the rest stays on chip)
 }
 
@@ -60,7 +60,8 @@ BOUND_DETAIL = {
     "cfg4": "HBM weight stream: 64 flop per weight byte (profiles/mlp_bf16_stream_kernel_cfg4.md)",
     "cfg5": "HBM write of the population in ask (profiles/ask_sphere_tell_kernels_cfg5.md)",
     "seq2seq": "instruction issue: VALU busy 44 % + MFMA busy 37 %, 29 % of wave time waiting (profiles/lstm_seq2seq_kernel_seq2seq.md)",
-    "forage": "latency of one step launch: vector ALU 20 % busy (profiles/world_step_kernel_forage.md)",
+    "forage": "vector-instruction issue plus one hand-over between workgroups per step: vector ALU 81 % busy, polling included "
+              "(profiles/world_resident_kernel_forage.md)",
     "forage_solo": "vector-instruction issue along the step chain: vector ALU 82 % busy (profiles/world_solo_kernel_forage_solo.md)",
 }
 
@@ -202,19 +203,17 @@ def _build_workload(name, seed, batch=None, f32=False):
         wl["task"] = lambda t: with_work_cached(lambda work: evo.make_task_desc(
             evo.EVO_TASK_FORAGE_SOLO if solo else evo.EVO_TASK_FORAGE, n_rollouts=c.n_rollouts, reset_seed=seed, generation=t + 1, cp=cp, work=work,
             generation_dev=wl.get("gen_dev")))
-        # one launch = one step of every world: per agent the scan over the others (2 sub, 2 mul, add, compare per
+        # one launch = the whole episode: per agent and step the scan over the others (2 sub, 2 mul, add, compare per
         # candidate) and over the items (twice: sensing and touching), and the policy's multiply-adds
         n_items = w["n_food"] + w["n_poison"]
         per_agent = (0.0 if solo else 6.0 * c.pop) + 2 * 6.0 * n_items + 2.0 * sum(c.dims[i] * c.dims[i + 1] for i in range(3))
-        if solo:      # the whole episode is one launch
-            wl["roofline"] = ("alu", per_agent * c.pop * c.n_rollouts * c.steps, PEAK_ALU_F32_TF, "TFLOP/s")
+        wl["roofline"] = ("alu", per_agent * c.pop * c.n_rollouts * c.steps, PEAK_ALU_F32_TF, "TFLOP/s")
+        if solo:
             wl["desc"] = ("forage_solo: every member alone in its own copy of each of %d worlds, %d members, fp32 MLP "
                           "8-32-32-2, %d steps (one launch per episode)" % (c.n_rollouts, c.pop, c.steps))
         else:
-            wl["roofline"] = ("alu", per_agent * c.pop * c.n_rollouts, PEAK_ALU_F32_TF, "TFLOP/s")
-            wl["launches"] = c.steps      # the stage is `steps` launches of the step kernel (+ reset and finish)
             wl["desc"] = ("forage: the population as %d agents of each of %d shared worlds, fp32 MLP 8-32-32-2, %d "
-                          "steps (one launch per step)" % (c.pop, c.n_rollouts, c.steps))
+                          "steps (one launch per episode)" % (c.pop, c.n_rollouts, c.steps))
         wl["dtype"] = "f32"
     else:
         raise SystemExit("unknown workload %r" % name)
@@ -437,7 +436,7 @@ def _run_workload(name, args, steps, warmup, torch):
     value = c.evals_per_generation * steps / elapsed
     bound, work, peak, unit = wl["roofline"]
     dom_stage = "ask" if args.variant == "fused" else wl["roofline_stage"]      # the fused call is timed as the ask stage
-    dom_ms = stage_ms[dom_stage] / wl.get("launches", 1)      # average duration of one launch
+    dom_ms = stage_ms[dom_stage]
     achieved = work / (dom_ms * 1e-3) / (1e12 if unit == "TFLOP/s" else 1e9)
     out = {
         "metric": "member-evals/sec (pop x samples, or env-steps/s, or pop for the sphere) for one whole ES generation",
@@ -451,8 +450,6 @@ def _run_workload(name, args, steps, warmup, torch):
                      "traffic_source": "rocprofv3 --pmc summary under profiles/ of this command (not read in this run)",
                      "kernel": wl["roofline_stage"], "kernel_ms": dom_ms, "bound_detail": BOUND_DETAIL.get(name)},
     }
-    if "launches" in wl:
-        out["roofline"]["launches_per_generation"] = wl["launches"]
     if "fp32_flops" in wl:      # the same launch priced as the fp32 work it stands for
         tf = wl["fp32_flops"] / (dom_ms * 1e-3) / 1e12
         out["roofline"]["priced_as"] = "fp16 matrix instructions as issued (two-term splits of fp32 operands)"

@@ -268,8 +268,9 @@ int pop_forward(const policy_desc* pd, const void* params_dev, const float* obs_
  *       p' < 0: p' = 0, v' = 0;  p' > 1: p' = 1, v' = 0.
  *     Every item (where it lay at the start of the step) with d2(p', item) <= fl(radius radius) is
  *     touched: +1 (food) or -1 (poison) to every agent that touches it; a touched item has been eaten
- *     once more from the next step on.  `steps` launches of one kernel (agents of a world depend on
- *     each other's positions every step); work_dev holds the worlds' state.
+ *     once more from the next step on.  Agents of a world depend on each other's positions every step: the
+ *     episode is one launch whose workgroups exchange them where a world's workgroups fit the chip together, and
+ *     `steps` launches of one kernel otherwise and under capture, with the same results; work_dev holds the worlds' state.
  *   FORAGE_SOLO  the single-agent form of the same world (the paragraph's first sentence): every member lives
  *             alone in its own copy of each world, i.e. a FORAGE world with one agent (agent index 0): all
  *             members start at the same place among the same items and part ways through what they eat; the
