@@ -808,7 +808,8 @@ __global__ __launch_bounds__(256) void clipup_step_kernel(float* __restrict__ mu
   const double gg = red[0][0], vv = red[1][0], vg = red[2][0];
   const float scale = gg > 0.0 ? static_cast<float>(static_cast<double>(step) / sqrt(gg)) : 0.f;
   const double m = momentum, sc = scale;
-  const double speed = sqrt(fmax(m * m * vv + 2.0 * m * sc * vg + sc * sc * gg, 0.0));
+  // a gradient whose squares overflow (scale 0) or whose elements are all 0 leaves momentum vel alone
+  const double speed = sqrt(fmax(m * m * vv + (scale > 0.f ? 2.0 * m * sc * vg + sc * sc * gg : 0.0), 0.0));
   const float clip = speed > static_cast<double>(max_speed) ? static_cast<float>(static_cast<double>(max_speed) / speed) : 1.0f;
   auto one = [&](float& v, float gi, float& x) {
     v = fmaf(scale, gi, momentum * v) * clip;

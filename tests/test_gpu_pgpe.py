@@ -287,6 +287,21 @@ def test_clipup_clips_to_its_speed(evo, P, pop):
     assert clipped, "five steps at momentum 0.9 must have hit the speed bound"
 
 
+def test_clipup_clips_an_old_velocity_when_the_gradient_overflows(evo):
+    """g^2 beyond binary32: the normalised gradient is 0, momentum vel stays, and is clipped where it is too fast (here a
+    velocity from outside)."""
+    P, pop = 1027, 4
+    g, _ = _states(evo, P, pop, gen.initial_mu(4, P), optimizer=1, lr_mu=0.1, max_speed=0.105, shaping=0)
+    g.m.copy_(dev(np.linspace(-1, 1, P, dtype=np.float32)))
+    before = g.m.clone()
+    g.ask(5, pop, torch.empty(pop, P, dtype=torch.float32, device="cuda"))
+    g.tell(dev(np.array([1e28, -1e28, 2e28, 1e28], np.float32)))
+    want = 0.9 * before.double()
+    want *= 0.105 / want.norm()
+    # a velocity is rounded three times, the norm and the factor as above
+    assert float((g.m.double() - want).norm()) <= 5e-7 * 0.105
+
+
 def test_clipup_zero_gradient_and_config_errors(evo):
     P, pop = 100, 8
     mu0 = gen.initial_mu(7, P)
