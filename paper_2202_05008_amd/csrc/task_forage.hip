@@ -1363,22 +1363,24 @@ __global__ __launch_bounds__(256) void world_counts_kernel(const uint32_t* count
 }
 
 struct Layout {
-  size_t pos[2], vel, reward, book, hand, flag, bytes;  // byte offsets into the workspace
+  size_t pos[2], vel, reward, book, hand, flag, bytes;  // byte offsets into the workspace, and what it takes
   bool room;                                            // hand and flag are there
 };
 
 static int item_chunks(int n_food, int n_items) {
   return (pad_to(n_food, kChunk) + pad_to(n_items - n_food, kChunk)) / kChunk;
 }
+// The most chunks that n_items take, whatever the split into food and poison.
+static int most_chunks(int n_items) { return (n_items - 2) / kChunk + 2; }
 // world_resident_kernel: workgroups of a world, and the words in which a world's touches of a step are handed over.
-static int resident_groups(int pop, int H) { return (pop + resident_agents(H) - 1) / resident_agents(H); }
+static int resident_groups(int pop, int H) { return (pop - 1) / resident_agents(H) + 1; }
 static size_t touch_words(int pop, int H, int chunks) {
   return static_cast<size_t>(resident_groups(pop, H)) * chunks;
 }
 // Worlds of one launch of it.
 static int resident_worlds(int pop, int worlds, int H) { return std::min(worlds, kMaxResident / resident_groups(pop, H)); }
 
-static Layout carve(int pop, int worlds, int n_food, int n_items) {
+static Layout carve(int pop, int worlds, int n_items) {
   const size_t agents = static_cast<size_t>(pop) * worlds;
   auto up = [](size_t n) { return (n + 255) & ~size_t(255); };
   Layout l;
@@ -1388,14 +1390,16 @@ static Layout carve(int pop, int worlds, int n_food, int n_items) {
   l.vel = o, o += up(agents * sizeof(float2));
   l.reward = o, o += up(agents * sizeof(int32_t));
   l.book = o, o += up(5 * static_cast<size_t>(worlds) * n_items * sizeof(uint32_t));
-  // room for the launch with waits wherever a hidden width could take it (at most 53 KB), unless it would be what makes
-  // the workspace too large for the built-in scratch
-  size_t words = 0;
-  for (int H : {32, 64}) words = std::max(words, touch_words(pop, H, item_chunks(n_food, n_items)) * resident_worlds(pop, worlds, H));
-  l.hand = o, l.flag = o + up(2 * words * sizeof(unsigned long long));
+  // room for the launch with waits (at most 53 KB), unless it would be what makes the workspace too large for the
+  // built-in scratch.  A workspace made for the largest problem has to serve the smaller ones, so no size may shrink as
+  // pop, worlds or items grow: the room is for the most workgroups that a launch could have at any hidden width, not for
+  // those of this call (whole worlds in kMaxResident workgroups: 1024 agents take more of them than 1026), and what
+  // loses its room asks for the whole built-in scratch.
+  const size_t groups = std::min(static_cast<size_t>(kMaxResident), static_cast<size_t>(resident_groups(pop, 64)) * worlds);
+  l.hand = o, l.flag = o + up(2 * groups * most_chunks(n_items) * sizeof(unsigned long long));
   l.bytes = l.flag + up(static_cast<size_t>(worlds) * sizeof(uint32_t));
-  l.room = words > 0 && (o > EVO_STATIC_SCRATCH_BYTES || l.bytes <= EVO_STATIC_SCRATCH_BYTES);
-  if (!l.room) l.bytes = o;
+  l.room = o > EVO_STATIC_SCRATCH_BYTES || l.bytes <= EVO_STATIC_SCRATCH_BYTES;
+  if (!l.room) l.bytes = EVO_STATIC_SCRATCH_BYTES;
   return l;
 }
 
@@ -1474,7 +1478,7 @@ int forage_supported(const MlpShape& sh, int pop, int worlds, const float* cp) {
 size_t forage_workspace_bytes(int pop, int worlds, const float* cp) {
   WorldConst c;
   if (fill_const(cp, &c) || pop < 1 || worlds < 1) return 0;
-  return carve(pop, worlds, c.n_food, c.n_items).bytes;
+  return carve(pop, worlds, c.n_items).bytes;
 }
 
 // ---- the whole episode in one launch: host side ----
@@ -1552,7 +1556,7 @@ int launch_forage(const MlpShape& sh, const float* params, int pop, int worlds, 
   WorldConst c;
   int rc = fill_const(cp, &c);
   if (rc) return rc;
-  const Layout l = carve(pop, worlds, c.n_food, c.n_items);
+  const Layout l = carve(pop, worlds, c.n_items);
   char* base = static_cast<char*>(work);
   float2* pos[2] = {reinterpret_cast<float2*>(base + l.pos[0]), reinterpret_cast<float2*>(base + l.pos[1])};
   float2* vel = reinterpret_cast<float2*>(base + l.vel);

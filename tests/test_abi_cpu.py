@@ -83,6 +83,32 @@ def test_policy_and_task_descriptions():
     assert need >= 1024 * 4096 + 256 * 4 and need % 256 == 0 and need <= api.rollout_static_scratch_bytes()
 
 
+def test_forage_workspace_never_shrinks_as_the_problem_grows():
+    """A workspace made for the largest population (or the most worlds or items) serves the smaller ones: the size never
+    decreases along any of them, also where it passes the built-in scratch.  No smaller than the state itself."""
+    from paper_2202_05008_amd import api
+    pd = api.make_policy_desc(api.EVO_POLICY_MLP, (8, 32, 32, 2), (1, 1, 1))
+
+    def size(pop, worlds, food, poison):
+        td = api.make_task_desc(api.EVO_TASK_FORAGE, n_rollouts=worlds, reset_seed=1, generation=1,
+                                cp=(0.0625, 0.015625, 0.875, 0.25, 0.03125, float(food), float(poison)))
+        n = api.rollout_workspace_bytes(td, pd, pop)
+        assert n >= pop * worlds * 28 + 5 * worlds * (food + poison) * 4
+        return n
+
+    pops = [2, 3, 8, 9] + list(range(16, 2600, 6)) + list(range(2600, 4900, 100))
+    for worlds in (1, 2, 3, 8, 37, 128, 129, 257, 4096):
+        for food, poison in ((24, 24), (1, 255), (1, 1)):
+            sizes = [size(p, worlds, food, poison) for p in pops]
+            assert sizes == sorted(sizes), (worlds, food, poison)
+    for pop in (2, 64, 1024, 1026, 2048, 2050, 4800):
+        sizes = [size(pop, w, 24, 24) for w in range(1, 4097, 3 if pop < 100 else 1 if pop < 1025 else 17)]
+        assert sizes == sorted(sizes), pop
+        # whatever the split into food and poison, more items never need less
+        by_items = [[size(pop, 5, f, n - f) for f in range(1, n)] for n in range(2, 257)]
+        assert all(max(a) <= min(b) for a, b in zip(by_items, by_items[1:])), pop
+
+
 def test_missing_library_fails_loudly(monkeypatch):
     from paper_2202_05008_amd import _lib
     monkeypatch.setattr(_lib, "_lib", None)
