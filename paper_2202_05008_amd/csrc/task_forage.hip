@@ -25,6 +25,7 @@
 #include "kernels.h"
 
 #include <atomic>
+#include <cfloat>
 #include <cmath>
 #include <mutex>
 #include "philox.h"
@@ -1413,7 +1414,9 @@ static size_t step_lds_bytes(int pop, int n_food, int n_items) {
 
 static int fill_const(const float* cp, WorldConst* c) {
   c->dt = cp[0], c->thrust = cp[1], c->drag = cp[2], c->vmax = cp[3];
-  c->r2 = cp[4] * cp[4];  // the squared touch radius, rounded once
+  // the squared touch radius, rounded once; never infinite, or the empty slots of the item lists, which lie infinitely
+  // far away, would count as touched
+  c->r2 = std::fmin(cp[4] * cp[4], FLT_MAX);
   c->n_food = static_cast<int>(cp[5]);
   c->n_items = c->n_food + static_cast<int>(cp[6]);
   EVO_REQUIRE(cp[5] == static_cast<float>(c->n_food) && cp[6] == static_cast<float>(c->n_items - c->n_food),

@@ -215,6 +215,30 @@ def test_full_size_constant_actions_and_properties(evo):
     assert counts.min() > 0, "over 500 steps every item of every world is eaten at some point"
 
 
+@pytest.mark.parametrize("solo", [False, True])
+@pytest.mark.parametrize("radius", [2.0, 1e19, 2e19, float("inf")])      # 2e19 and more: the square is infinite in binary32
+def test_a_radius_over_the_whole_square_touches_every_item_and_no_empty_slot(evo, solo, radius):
+    """Item lists that fill no chunk of slots: every agent touches every item in every step, in the whole episode as in the
+    single step, and the hits and counts behind a world's items stay those of the next world."""
+    pop, worlds, steps, food, poison = 9, 3, 4, 5, 2
+    w = dict(forage.WORLD_DEFAULT, n_food=food, n_poison=poison, radius=radius)
+    dims, acts = (8, 16, 16, 2), (1, 1, 0)
+    pd = evo.make_policy_desc(evo.EVO_POLICY_MLP, dims, acts)
+    params = dev(_params_constant_action(pop, dims, np.random.default_rng(2)))
+    td = _task(evo, w, worlds, pop, pd, kind=evo.EVO_TASK_FORAGE_SOLO if solo else None)
+    pos, vel, reward, counts, fit = _run_state(evo, td, pd, params, pop, worlds, food + poison, steps, solo=solo)
+    assert (reward == steps * (food - poison)).all() and (fit == steps * (food - poison)).all()
+    assert (counts == steps).all()
+    if not solo:
+        i32, f32 = torch.int32, torch.float32
+        out = [torch.empty(worlds, pop, n, dtype=f32, device="cuda") for n in (8, 2, 2)]
+        rew = torch.empty(worlds, pop, dtype=i32, device="cuda")
+        hit = torch.full((worlds + 1, food + poison), 99, dtype=i32, device="cuda")
+        zero = torch.zeros(worlds, pop, 2, dtype=f32, device="cuda")
+        evo.evo_forage_step(td, pop, dev(pos), zero, dev(counts), zero, *out, rew, hit[:worlds])
+        assert (host(rew) == food - poison).all() and (host(hit)[:worlds] == 1).all() and (host(hit)[worlds] == 99).all()
+
+
 def _state(evo, td, pd, params, pop, worlds, n_items, steps, wait_ticks=None):
     out = dict(pos=torch.empty(worlds, pop, 2, dtype=torch.float32, device="cuda"),
                vel=torch.empty(worlds, pop, 2, dtype=torch.float32, device="cuda"),
