@@ -47,8 +47,9 @@ static inline size_t ws_arrays_bytes(int pop_max) {
   return ((static_cast<size_t>(pop_max) * 2 + 2 * kNormBlocks) * 4 + 255) & ~size_t(255);
 }
 constexpr int kSmallSumWords = 2 * 4096;  // the loss sums of the one-launch generation, two words each
-constexpr unsigned kGradNormParts = 8192;        // workgroups of tell whose partial sums ClipUp takes, three words each
-static inline size_t ws_bytes(int pop_max) { return ws_arrays_bytes(pop_max) + 256 + 4 * 3 * kGradNormParts; }
+constexpr unsigned kGradNormParts = 8192;        // workgroups of tell whose partial sums ClipUp takes
+constexpr unsigned kGradNormBytes = 4 + 3 * 8;   // of each: see TellArgs::norm_part
+static inline size_t ws_bytes(int pop_max) { return ws_arrays_bytes(pop_max) + 256 + kGradNormBytes * kGradNormParts; }
 
 static inline Workspace ws_carve(void* base, int pop_max) {
   Workspace w;
@@ -444,7 +445,8 @@ struct TellArgs {
   int P, nquads, N, KS;
   uint32_t gen, key0, key1;
   const uint32_t* gen_dev;  // when set: t is read here and the bias corrections are formed in the kernel
-  float* norm_part;        // ClipUp: [3][norm_parts] partial sums of g_mu^2, vel^2 and vel g_mu, one per workgroup, or null
+  float* norm_part;        // ClipUp: [kGradNormParts] partial sums of g_mu^2, one per workgroup, or null
+  double* norm_sums;       // behind them: [3][norm_parts] the same in fp64, of vel^2 and of vel g_mu
   int norm_parts;
   float inv_n, lr_mu, lr_sigma, max_change, beta1, beta2, eps, bc1, bc2, momentum;
 };
@@ -535,7 +537,8 @@ __device__ __forceinline__ void tell_block(TellArgs a, int block, PAIRS pairs, f
     *reinterpret_cast<float4*>(mine + 4) = make_float4(B[0], B[1], B[2], B[3]);
   }
   __syncthreads();
-  float sq = 0.f, vv = 0.f, vg = 0.f;
+  float sq = 0.f;
+  double gg = 0.0, vv = 0.0, vg = 0.0;
   for (int p = tid; p < 4 * QPB; p += 256) {
     const int c = block * QPB * 4 + p;
     if (c >= a.P) break;
@@ -565,8 +568,8 @@ __device__ __forceinline__ void tell_block(TellArgs a, int block, PAIRS pairs, f
       a.mu[c] += vel;
     } else {
       a.v[c] = g_mu;  // ClipUp needs |g_mu| over all of P first: the gradient waits in v
-      const float vel = a.m[c];
-      sq = fmaf(g_mu, g_mu, sq), vv = fmaf(vel, vel, vv), vg = fmaf(vel, g_mu, vg);
+      const double vel = a.m[c], g = g_mu;
+      sq = fmaf(g_mu, g_mu, sq), gg = fma(g, g, gg), vv = fma(vel, vel, vv), vg = fma(vel, g, vg);
     }
     if (SRULE == 0) {
       const float lim = a.max_change * sg;
@@ -580,9 +583,18 @@ __device__ __forceinline__ void tell_block(TellArgs a, int block, PAIRS pairs, f
   }
   if (OPT == OPT_CLIPUP_GRAD && a.norm_part) {
     __syncthreads();  // the partial sums have been read
-    const float t = block_sum256(sq, part), tv = block_sum256(vv, part + 4), tg = block_sum256(vg, part + 8);
-    if (tid == 0)
-      a.norm_part[block] = t, a.norm_part[a.norm_parts + block] = tv, a.norm_part[2 * a.norm_parts + block] = tg;
+    double* all = reinterpret_cast<double*>(part);  // [3][256]: a wave adds up one of the three
+    all[tid] = gg, all[256 + tid] = vv, all[512 + tid] = vg;
+    const float t = block_sum256(sq, part + 2 * 3 * 256);  // (with the barrier that the three need)
+    if (tid == 0) a.norm_part[block] = t;
+    const int wave = tid >> 6, lane = tid & 63;
+    if (wave < 3) {
+      const double* x = all + 256 * wave + lane;
+      double sum = (x[0] + x[64]) + (x[128] + x[192]);
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+      if (lane == 0) a.norm_sums[wave * a.norm_parts + block] = sum;
+    }
   }
 }
 
@@ -781,32 +793,37 @@ __global__ __launch_bounds__(256) void clipup_velocity_kernel(float* __restrict_
 
 // Both in one launch, where tell has left the sums of g^2, vel^2 and vel g: the norm of the new velocity
 //   |momentum vel + s g|^2 = momentum^2 vel^2 + 2 momentum s vel g + s^2 g^2,  s = step / |g|,
-// is known before any of it is formed (in fp64; the clip only matters where |vel| exceeds max_speed, which no old velocity
-// does, so nothing cancels: the norm's error against 64 bits, 143 clipped steps of 500..300000 parameters: 4.0e-9 rms, at
-// most 1.8e-8; by a sum over the new velocity's elements 6.0e-9 and 3.4e-8).  Bound by latency: the sums, their total, then
+// is known before any of it is formed.  The three sums are fp64 from the elements on: s comes from a sum of fp32 squares
+// (their overflow takes the normalised gradient to 0), which for elements around 1e-21 holds a few units of the last
+// place, and |s g| is then tens of percent off step; and a velocity from outside may cancel against the gradient.
+// (Length of a clipped velocity against max_speed, 144 steps of 500..300007 parameters: 2.3e-8 rms, at most 4.3e-8; where
+// the new velocity's elements are added up in fp32 2.5e-8 and 5.6e-8.)  Bound by latency: the sums, their total, then
 // three loads and two stores per quad.  Alone, the two launches and this one: 6.0 + 4.6 and 5.5 us at P = 45530, 6.7 + 5.3
 // and 6.7 us at 300007, for at most 0.3 us more in tell.
 __global__ __launch_bounds__(256) void clipup_step_kernel(float* __restrict__ mu, float* __restrict__ vel,
                                                           const float* __restrict__ g, int P, float momentum, float step,
-                                                          float max_speed, const float* __restrict__ part, int n) {
-  __shared__ double red[3][256];
+                                                          float max_speed, const float* __restrict__ part,
+                                                          const double* __restrict__ sums, int n) {
+  __shared__ double red[4][256];
   const int tid = threadIdx.x;
-  double acc[3] = {0.0, 0.0, 0.0};
+  double acc[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll 4
-  for (int i = tid; i < n; i += 256)
+  for (int i = tid; i < n; i += 256) {
+    acc[3] += static_cast<double>(part[i]);
 #pragma unroll
-    for (int k = 0; k < 3; ++k) acc[k] += static_cast<double>(part[k * n + i]);
+    for (int k = 0; k < 3; ++k) acc[k] += sums[k * n + i];
+  }
 #pragma unroll
-  for (int k = 0; k < 3; ++k) red[k][tid] = acc[k];
+  for (int k = 0; k < 4; ++k) red[k][tid] = acc[k];
   __syncthreads();
   for (int s = 128; s > 0; s >>= 1) {
     if (tid < s)
 #pragma unroll
-      for (int k = 0; k < 3; ++k) red[k][tid] += red[k][tid + s];
+      for (int k = 0; k < 4; ++k) red[k][tid] += red[k][tid + s];
     __syncthreads();
   }
-  const double gg = red[0][0], vv = red[1][0], vg = red[2][0];
-  const float scale = gg > 0.0 ? static_cast<float>(static_cast<double>(step) / sqrt(gg)) : 0.f;
+  const double gg = red[0][0], vv = red[1][0], vg = red[2][0], n2 = red[3][0];
+  const float scale = n2 > 0.0 ? static_cast<float>(static_cast<double>(step) / sqrt(n2)) : 0.f;
   const double m = momentum, sc = scale;
   // a gradient whose squares overflow (scale 0) or whose elements are all 0 leaves momentum vel alone
   const double speed = sqrt(fmax(m * m * vv + (scale > 0.f ? 2.0 * m * sc * vg + sc * sc * gg : 0.0), 0.0));
@@ -1015,6 +1032,7 @@ static TellArgs tell_args(const pgpe_state* st, const float* fitness, float* gmu
   *blocks_out = static_cast<unsigned>((a.nquads + QPB - 1) / QPB);
   // the words of the one-launch generation, which ClipUp never runs as, take the partial sums
   a.norm_part = c.optimizer == EVO_OPT_CLIPUP && *blocks_out <= kGradNormParts ? reinterpret_cast<float*>(ws.gen + 64) : nullptr;
+  a.norm_sums = reinterpret_cast<double*>(ws.gen + 64 + kGradNormParts);
   a.norm_parts = static_cast<int>(*blocks_out);
   return a;
 }
@@ -1068,7 +1086,7 @@ static int run_tell(pgpe_state* st, const float* fitness, float* gmu, float* gsg
   const int grid = (P + 1023) / 1024 < kNormBlocks ? (P + 1023) / 1024 : kNormBlocks;  // four parameters per thread
   if (a.norm_part) {
     hipLaunchKernelGGL(clipup_step_kernel, dim3(grid), dim3(256), 0, s, st->mu, st->m, st->v, P, c.momentum, c.lr_mu, c.max_speed,
-                       a.norm_part, a.norm_parts);
+                       a.norm_part, a.norm_sums, a.norm_parts);
     return check_launch("clipup_step_kernel");
   }
   hipLaunchKernelGGL(sqnorm_kernel, dim3(kNormBlocks), dim3(256), 0, s, st->v, P, ws.norm);
@@ -1115,7 +1133,7 @@ int pgpe_generation_small(pgpe_state* st, uint64_t seed, int32_t pop, const MlpS
                 "pgpe_generation: %u update workgroups for %ld evaluation workgroups, %zu bytes of LDS: not a small problem",
                 n_tell, total, lds);
   }
-  static_assert(kSmallSumWords == 2 * kSmallMaxTiles && kSmallSumWords <= 3 * kGradNormParts, "two words per sum, in the room");
+  static_assert(kSmallSumWords == 2 * kSmallMaxTiles && 4 * kSmallSumWords <= kGradNormBytes * kGradNormParts, "two words per sum, in the room");
   Workspace ws = ws_carve(st->work, c.pop_max);
   g.done = ws.gen + 16, g.launches = ws.gen + 32;  // inside the 256 bytes kept for the generation word
   g.sums = reinterpret_cast<uint64_t*>(ws.gen + 64);  // behind them

@@ -287,6 +287,20 @@ def test_clipup_clips_to_its_speed(evo, P, pop):
     assert clipped, "five steps at momentum 0.9 must have hit the speed bound"
 
 
+# Raw fitness down to where the gradient's squares are a few units of binary32's last place (elements around 1e-21) or
+# vanish one by one (1e-23): the length of the normalised step is then not lr_mu, and the bound holds all the same.
+@pytest.mark.parametrize("P", [5, 1027, 70001])
+@pytest.mark.parametrize("size", [1.0, 1e-18, 2e-20, 2e-21, 9e-22, 3e-22, 1e-22])
+def test_clipup_clips_to_its_speed_whatever_the_gradients_size(evo, P, size):
+    pop = 4
+    g, _ = _states(evo, P, pop, gen.initial_mu(4, P), optimizer=1, lr_mu=0.1, max_speed=0.1, shaping=0)
+    params = torch.empty(pop, P, dtype=torch.float32, device="cuda")
+    for it in range(4):
+        g.ask(5 + it, pop, params)
+        g.tell(dev((np.array([1, -1, 2, 1], np.float32) * np.float32(size)).astype(np.float32)))
+        assert float(g.m.double().norm()) <= 0.1 * (1 + 5e-7), it      # (roundings as above)
+
+
 def test_clipup_clips_an_old_velocity_when_the_gradient_overflows(evo):
     """g^2 beyond binary32: the normalised gradient is 0, momentum vel stays, and is clipped where it is too fast (here a
     velocity from outside)."""
