@@ -826,7 +826,7 @@ __global__ __launch_bounds__(256) void clipup_step_kernel(float* __restrict__ mu
   const float scale = n2 > 0.0 ? static_cast<float>(static_cast<double>(step) / sqrt(n2)) : 0.f;
   const double m = momentum, sc = scale;
   // a gradient whose squares overflow (scale 0) or whose elements are all 0 leaves momentum vel alone
-  const double speed = sqrt(fmax(m * m * vv + (scale > 0.f ? 2.0 * m * sc * vg + sc * sc * gg : 0.0), 0.0));
+  const double speed = sqrt(fmax(m * m * vv + (scale != 0.f ? 2.0 * m * sc * vg + sc * sc * gg : 0.0), 0.0));
   const float clip = speed > static_cast<double>(max_speed) ? static_cast<float>(static_cast<double>(max_speed) / speed) : 1.0f;
   auto one = [&](float& v, float gi, float& x) {
     v = fmaf(scale, gi, momentum * v) * clip;

@@ -270,9 +270,10 @@ def test_clipup_norms_at_the_edges(evo, P, pop):
 # loop (2844 workgroups), the last size whose sums have room and the first that takes its norms from separate passes.
 # A clipped velocity has the length max_speed: a parameter is rounded twice and the factor once, and a partial sum over a
 # workgroup's 256 parameters at most 1 + 6 + 2 times, which the square root halves: 8 x 2^-24 < 5e-7.
+@pytest.mark.parametrize("lr_mu", [0.1, -0.1])      # (ascent, and descent for a fitness that counts costs)
 @pytest.mark.parametrize("P,pop", [(5, 4), (1027, 6), (45490, 130), (8388608, 2), (8388608 + 1100, 2)])
-def test_clipup_clips_to_its_speed(evo, P, pop):
-    g, _ = _states(evo, P, pop, gen.initial_mu(4, P), optimizer=1, lr_mu=0.1, max_speed=0.105)
+def test_clipup_clips_to_its_speed(evo, P, pop, lr_mu):
+    g, _ = _states(evo, P, pop, gen.initial_mu(4, P), optimizer=1, lr_mu=lr_mu, max_speed=0.105)
     params = torch.empty(pop, P, dtype=torch.float32, device="cuda")
     clipped = 0
     for it in range(5):
