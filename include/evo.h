@@ -379,6 +379,15 @@ int evo_forage_state(const task_desc* td, const policy_desc* pd, const void* par
 int evo_forage_state_bounded(const task_desc* td, const policy_desc* pd, const void* params_dev, int32_t pop, int32_t steps,
                              float* pos_dev, float* vel_dev, int32_t* reward_dev, uint32_t* counts_dev,
                              uint64_t wait_ticks, void* stream);
+/* The same for a FORAGE roll-out in a stated form, and how it went.  form: 0 as rollout chooses, 1 the episode in one launch
+ * wherever that can run (not under capture), 2 a launch per step.  fail_step > 0: from that step on the waits of the one
+ * launch's first workgroup of every world (fail_items 0: its agents' for positions, 1: its items' for touches) end in
+ * vain, so that the world is given up with other workgroups a step ahead, and played again.  form_dev[worlds] (may be
+ * NULL): 0 the world was played step by step, 1 in the one launch, 2 given up there and played again.  The state is
+ * that of evo_forage_state whatever the form. */
+int evo_forage_state_form(const task_desc* td, const policy_desc* pd, const void* params_dev, int32_t pop, int32_t steps,
+                          float* pos_dev, float* vel_dev, int32_t* reward_dev, uint32_t* counts_dev, int32_t form,
+                          int32_t fail_step, int32_t fail_items, uint32_t* form_dev, void* stream);
 /* One cart-pole step for n independent (state, action) pairs: state_dev[n][4], action_dev[n]
  * -> next_dev[n][4], reward_dev[n].  Only td->cp is read. */
 int evo_task_step(const task_desc* td, const float* state_dev, const float* action_dev, float* next_dev,

@@ -51,6 +51,8 @@ _SIGNATURES = {
                          + [C.c_void_p] * 5),
     "evo_forage_state_bounded": (C.c_int, [C.POINTER(task_desc), C.POINTER(policy_desc), C.c_void_p, C.c_int32, C.c_int32]
                                  + [C.c_void_p] * 4 + [C.c_uint64, C.c_void_p]),
+    "evo_forage_state_form": (C.c_int, [C.POINTER(task_desc), C.POINTER(policy_desc), C.c_void_p, C.c_int32, C.c_int32]
+                              + [C.c_void_p] * 4 + [C.c_int32] * 3 + [C.c_void_p] * 2),
     "pgpe_device_generation": (C.c_int, [C.c_void_p, C.POINTER(C.c_void_p), C.c_void_p]),
     "pgpe_sync_generation": (C.c_int, [C.c_void_p, C.c_void_p]),
     "pgpe_ask": (C.c_int, [C.c_void_p, C.c_uint64, C.c_int32, C.c_void_p, C.c_int32, C.c_void_p]),

@@ -283,6 +283,15 @@ def evo_forage_state_bounded(td, pd, params, pop, steps, wait_ticks, pos=None, v
                                                 wait_ticks, _stream()))
 
 
+def evo_forage_state_form(td, pd, params, pop, steps, form=0, pos=None, vel=None, reward=None, counts=None, fail_step=0,
+                          fail_items=0, forms=None):
+    f32, i32 = torch.float32, torch.int32
+    _check(_lib.load().evo_forage_state_form(C.byref(td), C.byref(pd), _ptr(params), pop, steps,
+                                             _ptr(pos, f32, allow_none=True), _ptr(vel, f32, allow_none=True),
+                                             _ptr(reward, i32, allow_none=True), _ptr(counts, i32, allow_none=True),
+                                             form, fail_step, fail_items, _ptr(forms, i32, allow_none=True), _stream()))
+
+
 def evo_rollout_details(td, pd, params, pop, steps, ret, final):
     _check(_lib.load().evo_rollout_details(C.byref(td), C.byref(pd), _ptr(params), pop, steps,
                                            _ptr(ret, torch.float32, allow_none=True),

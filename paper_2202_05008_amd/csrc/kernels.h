@@ -90,13 +90,20 @@ int launch_cartpole_step(const float* cp, const float* state, const float* actio
 // worlds fit the chip, one launch per step otherwise.  A wait of that one launch lasts at most wait_ticks of the 100 MHz
 // clock (kForageWaitTicks: far above any wait between workgroups that run, short enough to notice).
 constexpr uint64_t kForageWaitTicks = 20000000;
+// How an episode is played; the defaults are what a roll-out takes, the rest is for checks.
+struct ForageForm {
+  int force = 0;  // 1: in one launch wherever that can run, 2: a launch per step, 0: as measured to be faster
+  uint64_t wait_ticks = kForageWaitTicks;
+  int fail_main = 0x7fffffff, fail_items = 0x7fffffff, fail_groups = 0;  // the one launch: see ResidentArgs
+  uint32_t* told = nullptr;  // [worlds]: 0 played step by step, 1 in the one launch, 2 given up there and played again
+};
 // `work` holds forage_workspace_bytes(...) bytes.  The state outputs (positions and velocities
 // [worlds][pop][2], summed rewards [worlds][pop], times eaten [worlds][items]) may be null.
 int forage_supported(const MlpShape& sh, int pop, int worlds, const float* cp);
 size_t forage_workspace_bytes(int pop, int worlds, const float* cp);
 int launch_forage(const MlpShape& sh, const float* params, int pop, int worlds, int steps, const float* cp,
                   uint64_t seed, uint32_t gen, const uint32_t* gen_dev, void* work, float* fitness, float* pos_out,
-                  float* vel_out, int32_t* reward_out, uint32_t* counts_out, uint64_t wait_ticks, hipStream_t s);
+                  float* vel_out, int32_t* reward_out, uint32_t* counts_out, const ForageForm& form, hipStream_t s);
 int launch_forage_step(int pop, int worlds, const float* cp, uint64_t seed, uint32_t gen, const float* pos,
                        const float* vel, const uint32_t* counts, const float* actions, float* obs_out, float* pos_out,
                        float* vel_out, int32_t* reward_out, uint32_t* hit_out, hipStream_t s);

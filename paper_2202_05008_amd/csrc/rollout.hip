@@ -178,7 +178,7 @@ static int seq2seq_impl(const task_desc* td, const policy_desc* pd, const void* 
 // The shared-world task: fitness and / or the state after the last step.
 static int forage_impl(const task_desc* td, const policy_desc* pd, const void* params_dev, int32_t pop, int32_t steps,
                        float* fitness_dev, float* pos_dev, float* vel_dev, int32_t* reward_dev, uint32_t* counts_dev,
-                       void* stream, uint64_t wait_ticks = kForageWaitTicks) {
+                       void* stream, const ForageForm& form = ForageForm()) {
   EVO_REQUIRE(td != nullptr && (td->kind == EVO_TASK_FORAGE || td->kind == EVO_TASK_FORAGE_SOLO), EVO_ERR_ARG,
               "forage: needs an EVO_TASK_FORAGE or EVO_TASK_FORAGE_SOLO task");
   const bool solo = td->kind == EVO_TASK_FORAGE_SOLO;
@@ -207,7 +207,7 @@ static int forage_impl(const task_desc* td, const policy_desc* pd, const void* p
   if (rc) return rc;
   return launch_forage(sh, static_cast<const float*>(params_dev), pop, td->n_rollouts, steps, td->cp, td->reset_seed,
                        td->generation, td->generation_dev, td->work_dev, fitness_dev, pos_dev, vel_dev, reward_dev,
-                       counts_dev, wait_ticks, as_stream(stream));
+                       counts_dev, form, as_stream(stream));
 }
 
 static int rollout_impl(const task_desc* td, const policy_desc* pd, const void* params_dev, int32_t pop,
@@ -487,7 +487,25 @@ extern "C" int evo_forage_state_bounded(const task_desc* td, const policy_desc* 
                                         int32_t steps, float* pos_dev, float* vel_dev, int32_t* reward_dev,
                                         uint32_t* counts_dev, uint64_t wait_ticks, void* stream) {
   EVO_REQUIRE(pos_dev || vel_dev || reward_dev || counts_dev, EVO_ERR_ARG, "evo_forage_state_bounded: no output requested");
-  return forage_impl(td, pd, params_dev, pop, steps, nullptr, pos_dev, vel_dev, reward_dev, counts_dev, stream, wait_ticks);
+  ForageForm form;
+  form.wait_ticks = wait_ticks;
+  if (wait_ticks == 0) form.fail_main = form.fail_items = 0, form.fail_groups = 0x7fffffff;
+  return forage_impl(td, pd, params_dev, pop, steps, nullptr, pos_dev, vel_dev, reward_dev, counts_dev, stream, form);
+}
+
+constexpr uint64_t kFailTicks = 20000;  // 0.2 ms: a wait that is to end in vain
+
+extern "C" int evo_forage_state_form(const task_desc* td, const policy_desc* pd, const void* params_dev, int32_t pop,
+                                     int32_t steps, float* pos_dev, float* vel_dev, int32_t* reward_dev,
+                                     uint32_t* counts_dev, int32_t form, int32_t fail_step, int32_t fail_items,
+                                     uint32_t* form_dev, void* stream) {
+  EVO_REQUIRE(td != nullptr && td->kind == EVO_TASK_FORAGE, EVO_ERR_ARG, "evo_forage_state_form: needs an EVO_TASK_FORAGE task");
+  EVO_REQUIRE(pos_dev || vel_dev || reward_dev || counts_dev || form_dev, EVO_ERR_ARG, "evo_forage_state_form: no output requested");
+  EVO_REQUIRE(form >= 0 && form <= 2 && fail_step >= 0, EVO_ERR_ARG, "evo_forage_state_form: form must be 0, 1 or 2, fail_step >= 0");
+  ForageForm f;
+  f.force = form, f.told = form_dev;
+  if (fail_step > 0) (fail_items ? f.fail_items : f.fail_main) = fail_step, f.fail_groups = 1, f.wait_ticks = kFailTicks;
+  return forage_impl(td, pd, params_dev, pop, steps, nullptr, pos_dev, vel_dev, reward_dev, counts_dev, stream, f);
 }
 
 extern "C" int evo_forage_step(const task_desc* td, int32_t pop, const float* pos_dev, const float* vel_dev,

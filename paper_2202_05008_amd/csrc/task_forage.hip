@@ -593,7 +593,10 @@ struct ResidentArgs {
   int world0, per_launch;    // the launch's first world and the most worlds it has
   int groups;                // workgroups of a world
   uint32_t* flag;            // [worlds]: a wait has ended without its word
-  unsigned long long wait_ticks;  // of the 100 MHz clock; 0: every wait fails (test hook)
+  unsigned long long wait_ticks;  // of the 100 MHz clock
+  // CHECK: from these steps on the main waves of the first fail_groups workgroups of a world wait for positions that nobody
+  // hands over, and their item waves for such touches
+  int fail_main, fail_items, fail_groups;
   int32_t* reward;       // [worlds][pop]
   float2* pos_out;       // [worlds][pop] state after the last step
   float2* vel_out;       // [worlds][pop]
@@ -783,7 +786,9 @@ __device__ __forceinline__ float4 nearest_items(float2 p, const float2* list, in
   return make_float4(f.x - p.x, f.y - p.y, g.x - p.x, g.y - p.y);
 }
 
-template <int H, bool TANH>
+// CHECK: a build of its own in which waits can be made to fail at a stated step (the two comparisons per step cost the
+// kernel proper 3 % in scalar registers that it has to put aside).
+template <int H, bool TANH, bool CHECK>
 __global__ __launch_bounds__(resident_threads(H)) void world_resident_kernel(const ResidentArgs a) {
   constexpr int LPA = resident_lanes(H), APW = 64 / LPA, kAgents = resident_agents(H), kItemWaves = item_waves(H);
   extern __shared__ float4 lds4[];
@@ -861,10 +866,11 @@ __global__ __launch_bounds__(resident_threads(H)) void world_resident_kernel(con
     auto touched = [&](int slot) {  // slot 2 q of a chunk in bit q of its word, slot 2 q + 1 in bit 16 + q
       return ((all[slot / kChunk] >> ((slot & 1) * 16 + ((slot & (kChunk - 1)) >> 1))) & 1u) != 0u;
     };
+    const int fail_items = CHECK && group < a.fail_groups ? a.fail_items : 0x7fffffff;
     // what anybody touched moves on (false: given up)
     auto collect = [&](int step) -> bool {
       const unsigned long long* in = hand + (step & 1) * half;
-      const uint32_t tag = a.tag0 + static_cast<uint32_t>(step);
+      const uint32_t tag = CHECK && step >= fail_items ? ~0u : a.tag0 + static_cast<uint32_t>(step);  // (~0: nobody's)
       bool stop = false;
 #pragma unroll 1
       for (int i = lane; i < words; i += 128) {  // two words at a time
@@ -872,8 +878,8 @@ __global__ __launch_bounds__(resident_threads(H)) void world_resident_kernel(con
         unsigned long long w0, w1, since = 0;
         for (uint32_t looks = 0;;) {
           w0 = peek(in + i), w1 = peek(in + j);
-          if (static_cast<uint32_t>(w0 >> 32) == tag && static_cast<uint32_t>(w1 >> 32) == tag && a.wait_ticks) break;
-          if ((looks++ & 63) == 63 || !a.wait_ticks) {
+          if (static_cast<uint32_t>(w0 >> 32) == tag && static_cast<uint32_t>(w1 >> 32) == tag) break;
+          if ((looks++ & 63) == 63) {
             if (give_up(a.flag + world, a.wait_ticks, since)) {
               stop = true;
               break;
@@ -945,12 +951,13 @@ __global__ __launch_bounds__(resident_threads(H)) void world_resident_kernel(con
   int reward = 0;
   constexpr int kStride = LPA == 16 ? 2 : 4;  // chunks judged for touches at a time
   const uint64_t live_lanes = __builtin_amdgcn_ballot_w64(live);
+  const int fail_main = CHECK && group < a.fail_groups ? a.fail_main : 0x7fffffff;
 
 #pragma unroll 1
   for (int t = 0; t < a.steps; ++t) {
     if (t > 0) {
       const unsigned long long* in = (t & 1 ? a.odd : a.even) + static_cast<size_t>(world) * a.pop;
-      const uint32_t want = static_cast<uint32_t>(t) & 3u;
+      const uint32_t want = CHECK && t >= fail_main ? 4u : static_cast<uint32_t>(t) & 3u;  // (4: nobody's)
       bool stop = false;
 #pragma unroll 1
       for (int j = tid; j < a.pop; j += 2 * 64 * kMainWaves) {  // two words at a time
@@ -960,8 +967,8 @@ __global__ __launch_bounds__(resident_threads(H)) void world_resident_kernel(con
         unsigned long long w0, w1, since = 0;
         for (uint32_t looks = 0;;) {
           w0 = peek(in + j), w1 = peek(in + k1);
-          if ((static_cast<uint32_t>(w0) >> 30) == want && (static_cast<uint32_t>(w1) >> 30) == want && a.wait_ticks) break;
-          if ((looks++ & 63) == 63 || !a.wait_ticks) {
+          if ((static_cast<uint32_t>(w0) >> 30) == want && (static_cast<uint32_t>(w1) >> 30) == want) break;
+          if ((looks++ & 63) == 63) {
             if (give_up(a.flag + world, a.wait_ticks, since)) {
               stop = true;
               break;
@@ -1356,6 +1363,12 @@ __global__ __launch_bounds__(256) void world_fill_kernel(uint32_t* dst, int n, u
   if (i < n) dst[i] = value;
 }
 
+// How each world was played (ForageForm::told), from the flags of the launch with waits.
+__global__ __launch_bounds__(256) void world_told_kernel(const uint32_t* flag, int worlds, uint32_t* told) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < worlds) told[i] = 1u + flag[i];
+}
+
 // counts_out = counts + hits (the book after the last step), for the state hook.
 __global__ __launch_bounds__(256) void world_counts_kernel(const uint32_t* counts, const uint32_t* hits, int n,
                                                            uint32_t* out) {
@@ -1496,8 +1509,9 @@ template <int H>
 static int launch_resident_acts(const ResidentArgs& a, int worlds, size_t lds, hipStream_t s) {
   const bool all_tanh = a.act[0] == EVO_ACT_TANH && a.act[1] == EVO_ACT_TANH && a.act[2] == EVO_ACT_TANH;
   const dim3 grid(worlds * a.groups), threads(resident_threads(H));
-  if (all_tanh) hipLaunchKernelGGL((world_resident_kernel<H, true>), grid, threads, lds, s, a);
-  else hipLaunchKernelGGL((world_resident_kernel<H, false>), grid, threads, lds, s, a);
+  if (a.fail_groups > 0) hipLaunchKernelGGL((world_resident_kernel<H, false, true>), grid, threads, lds, s, a);
+  else if (all_tanh) hipLaunchKernelGGL((world_resident_kernel<H, true, false>), grid, threads, lds, s, a);
+  else hipLaunchKernelGGL((world_resident_kernel<H, false, false>), grid, threads, lds, s, a);
   return check_launch("world_resident_kernel");
 }
 static int launch_resident(int H, const ResidentArgs& a, int worlds, size_t lds, hipStream_t s) {
@@ -1555,7 +1569,7 @@ static ResidentTurn* resident_turn(int workgroups, hipStream_t s) {
 
 int launch_forage(const MlpShape& sh, const float* params, int pop, int worlds, int steps, const float* cp,
                   uint64_t seed, uint32_t gen, const uint32_t* gen_dev, void* work, float* fitness, float* pos_out,
-                  float* vel_out, int32_t* reward_out, uint32_t* counts_out, uint64_t wait_ticks, hipStream_t s) {
+                  float* vel_out, int32_t* reward_out, uint32_t* counts_out, const ForageForm& form, hipStream_t s) {
   WorldConst c;
   int rc = fill_const(cp, &c);
   if (rc) return rc;
@@ -1577,7 +1591,7 @@ int launch_forage(const MlpShape& sh, const float* params, int pop, int worlds, 
   const int H = sh.dims[1], groups = resident_groups(pop, H), per_launch = resident_worlds(pop, worlds, H);
   const bool tame = std::isfinite(cp[0]) && std::isfinite(cp[1]) && std::isfinite(cp[2]) && std::isfinite(cp[3]);
   ResidentTurn* turn = nullptr;
-  if (tame && l.room && per_launch > 0 &&
+  if (form.force != 2 && tame && l.room && per_launch > 0 &&
       static_cast<uint64_t>((worlds + per_launch - 1) / per_launch) * (static_cast<uint64_t>(steps) + 1) < (1ull << 32))
     turn = resident_turn(groups * per_launch, s);
 
@@ -1612,7 +1626,8 @@ int launch_forage(const MlpShape& sh, const float* params, int pop, int worlds, 
     b.per_lane = pad_to((pop + 63) / 64, 2);
     b.lane_magic = static_cast<uint32_t>(((1ull << 32) + b.per_lane - 1) / b.per_lane);
     b.even = reinterpret_cast<unsigned long long*>(pos[0]), b.odd = reinterpret_cast<unsigned long long*>(pos[1]);
-    b.hand = ra.hand, b.groups = groups, b.flag = ra.flag, b.wait_ticks = wait_ticks;
+    b.hand = ra.hand, b.groups = groups, b.flag = ra.flag, b.wait_ticks = form.wait_ticks;
+    b.fail_main = form.fail_main, b.fail_items = form.fail_items, b.fail_groups = form.fail_groups;
     b.reward = reward, b.pos_out = pos[steps & 1], b.vel_out = vel, b.counts_out = counts_out;
     const int stride = (b.per_lane >> 1) & 1 ? b.per_lane : b.per_lane + 2;
     const size_t slots = static_cast<size_t>(chunks) * kChunk;
@@ -1644,6 +1659,12 @@ int launch_forage(const MlpShape& sh, const float* params, int pop, int worlds, 
     a.hits_prev = t > 0 ? hits[(t + 2) % 3] : nullptr;  // the page written by step t - 1
     a.hits_cur = hits[t % 3], a.hits_clear = hits[(t + 1) % 3];
     rc = launch_step_for(sh.dims[1], a, s);
+    if (rc) return rc;
+  }
+  if (form.told) {
+    if (turn) hipLaunchKernelGGL(world_told_kernel, dim3((worlds + 255) / 256), dim3(256), 0, s, ra.flag, worlds, form.told);
+    else hipLaunchKernelGGL(world_fill_kernel, dim3((worlds + 255) / 256), dim3(256), 0, s, form.told, worlds, 0u);
+    rc = check_launch("world_told_kernel");
     if (rc) return rc;
   }
   if (fitness) {

@@ -110,6 +110,12 @@ int main(void) {
   CHECK(rollout_workspace_bytes(&td, &pd, 4) == 0);
   td.kind = 99;
   CHECK(rollout_workspace_bytes(&td, &pd, 4) == 0);
+  td.kind = EVO_TASK_FORAGE;
+  CHECK(evo_forage_state_form(&td, &pd, fake, 4, 1, (float*)fake, NULL, NULL, NULL, 3, 0, 0, NULL, NULL) == EVO_ERR_ARG);
+  CHECK(evo_forage_state_form(&td, &pd, fake, 4, 1, (float*)fake, NULL, NULL, NULL, 1, -1, 0, NULL, NULL) == EVO_ERR_ARG);
+  CHECK(evo_forage_state_form(&td, &pd, fake, 4, 1, NULL, NULL, NULL, NULL, 1, 0, 0, NULL, NULL) == EVO_ERR_ARG);
+  td.kind = EVO_TASK_FORAGE_SOLO;
+  CHECK(evo_forage_state_form(&td, &pd, fake, 4, 1, (float*)fake, NULL, NULL, NULL, 1, 0, 0, NULL, NULL) == EVO_ERR_ARG);
 
   /* argument checks of the launching calls: all refused before any launch */
   td.kind = EVO_TASK_CLASSIFY, td.B = 512;

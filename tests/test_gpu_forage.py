@@ -239,12 +239,17 @@ def test_a_radius_over_the_whole_square_touches_every_item_and_no_empty_slot(evo
         assert (host(rew) == food - poison).all() and (host(hit)[:worlds] == 1).all() and (host(hit)[worlds] == 99).all()
 
 
-def _state(evo, td, pd, params, pop, worlds, n_items, steps, wait_ticks=None):
+def _state(evo, td, pd, params, pop, worlds, n_items, steps, wait_ticks=None, form=None, expect=None, **fail):
+    """The state after an episode; form, fail: evo_forage_state_form's, and how every world must have been played."""
     out = dict(pos=torch.empty(worlds, pop, 2, dtype=torch.float32, device="cuda"),
                vel=torch.empty(worlds, pop, 2, dtype=torch.float32, device="cuda"),
                reward=torch.empty(worlds, pop, dtype=torch.int32, device="cuda"),
                counts=torch.empty(worlds, n_items, dtype=torch.int32, device="cuda"))
-    if wait_ticks is None:
+    if form is not None:
+        forms = torch.full((worlds,), 99, dtype=torch.int32, device="cuda")
+        evo.evo_forage_state_form(td, pd, params, pop, steps, form, forms=forms, **out, **fail)
+        assert expect is None or (forms == expect).all(), (forms.unique().tolist(), form, fail)
+    elif wait_ticks is None:
         evo.evo_forage_state(td, pd, params, pop, steps, **out)
     else:
         evo.evo_forage_state_bounded(td, pd, params, pop, steps, wait_ticks, **out)
@@ -261,7 +266,8 @@ def _state(evo, td, pd, params, pop, worlds, n_items, steps, wait_ticks=None):
 def test_the_episode_in_one_launch_is_the_episode_step_by_step(evo, pop, worlds, H, steps, n_food, n_poison, acts):
     """Whole episodes with observation-driven policies: where every wait is given up the worlds are played again by the
     step kernel's code, and both give the same bits (stacked agents and agents in corners among them: a wide thrust
-    drives many into the walls).  A workspace full of another call's words changes nothing."""
+    drives many into the walls).  A workspace full of another call's words changes nothing.  So do a launch per step, and
+    waits that end in vain in the middle of the episode, with the other workgroups of the world a step ahead."""
     w = dict(forage.WORLD_DEFAULT, n_food=n_food, n_poison=n_poison, radius=0.0625, thrust=0.25, vmax=2.0)
     pd = evo.make_policy_desc(evo.EVO_POLICY_MLP, (8, H, H, 2), acts)
     params = dev(_random_policies(pop, (8, H, H, 2), 0.5, pop + H))
@@ -274,13 +280,20 @@ def test_the_episode_in_one_launch_is_the_episode_step_by_step(evo, pop, worlds,
         assert torch.equal(one[k], again[k]), k
         assert torch.equal(one[k], after[k]), k
     assert pop < 32 or int(one["counts"].sum()) > 0, "items must be eaten"
+    forms = [dict(form=1, expect=1), dict(form=2, expect=0)]
+    for step in (1, 2, steps // 2, steps - 1):
+        forms += [dict(form=1, expect=2, fail_step=step, fail_items=items) for items in (0, 1)]
+    forms += [dict(form=1, expect=2, fail_step=steps, fail_items=1), dict(form=1, expect=1, fail_step=steps, fail_items=0)]
+    for how in forms:
+        other = _state(evo, td, pd, params, pop, worlds, n_items, steps, **how)
+        assert all(torch.equal(one[k], other[k]) for k in one), how
     fit = torch.empty(pop, dtype=torch.float32, device="cuda")
     evo.rollout(td, pd, params, pop, steps, fit)
     assert np.array_equal(host(fit), host(one["reward"]).sum(axis=0).astype(np.float32) / np.float32(worlds))
 
 
 def test_one_launch_episodes_on_two_streams(evo):
-    """Each launch fills the chip: they take turns, whatever stream they are on."""
+    """Each launch fills the chip: they take turns, whatever stream they are on, and no world is given up."""
     w = dict(forage.WORLD_DEFAULT, radius=0.0625)
     pd = evo.make_policy_desc(evo.EVO_POLICY_MLP, (8, 16, 16, 2), (1, 1, 1))
     pop, worlds, steps = 1024, 8, 20
@@ -293,11 +306,37 @@ def test_one_launch_episodes_on_two_streams(evo):
     for _ in range(4):
         for i, s in enumerate(streams):
             with torch.cuda.stream(s):
-                got[i].append(_state(evo, tds[i], pd, params[i], pop, worlds, 48, steps))
+                out, forms = _state(evo, tds[i], pd, params[i], pop, worlds, 48, steps), torch.empty(worlds, dtype=torch.int32, device="cuda")
+                evo.evo_forage_state_form(tds[i], pd, params[i], pop, steps, 1, forms=forms, **out)
+                got[i].append(dict(out, forms=forms))
     torch.cuda.synchronize()
+    for g in got[0] + got[1]:
+        assert (g.pop("forms") == 1).all(), "a launch met the other stream's on the chip"
     for i in range(2):
         for g in got[i]:
             assert all(torch.equal(g[k], want[i][k]) for k in g)
+
+
+@pytest.mark.parametrize("H,acts", [(16, (2, 1, 0)), (32, (0, 2, 1)), (64, (1, 2, 0)), (64, (1, 1, 1))])
+def test_a_recorded_episode_is_the_one_launch_episode(evo, H, acts):
+    """Into a graph the steps are recorded one by one; its replays give the bits of the one launch."""
+    pop, worlds, steps = 70, 3, 11
+    w = dict(forage.WORLD_DEFAULT, radius=0.0625, thrust=0.25, vmax=2.0)
+    pd = evo.make_policy_desc(evo.EVO_POLICY_MLP, (8, H, H, 2), acts)
+    params = dev(_random_policies(pop, (8, H, H, 2), 0.5, H))
+    td = _task(evo, w, worlds, pop, pd)
+    want = _state(evo, td, pd, params, pop, worlds, 48, steps, form=1, expect=1)
+    got = {k: torch.empty_like(v) for k, v in want.items()}
+    forms = torch.empty(worlds, dtype=torch.int32, device="cuda")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        evo.evo_forage_state_form(td, pd, params, pop, steps, 1, forms=forms, **got)
+    for _ in range(3):
+        for t in (*got.values(), forms):
+            t.zero_()
+        graph.replay()
+        assert (forms == 0).all() and all(torch.equal(want[k], got[k]) for k in want)
+        assert all(torch.equal(v, want[k]) for k, v in _state(evo, td, pd, params, pop, worlds, 48, steps, form=1, expect=1).items())
 
 
 def test_errors_are_reported(evo):
