@@ -269,8 +269,9 @@ int pop_forward(const policy_desc* pd, const void* params_dev, const float* obs_
  *     Every item (where it lay at the start of the step) with d2(p', item) <= fl(radius radius) is
  *     touched: +1 (food) or -1 (poison) to every agent that touches it; a touched item has been eaten
  *     once more from the next step on.  Agents of a world depend on each other's positions every step: the
- *     episode is one launch whose workgroups exchange them where a world's workgroups fit the chip together, and
- *     `steps` launches of one kernel otherwise and under capture, with the same results; work_dev holds the worlds' state.
+ *     episode is one launch whose workgroups exchange them where a world's workgroups fit the chip together and that is
+ *     the faster form, and `steps` launches of one kernel otherwise and under capture, with the same results; work_dev holds
+ *     the worlds' state.
  *   FORAGE_SOLO  the single-agent form of the same world (the paragraph's first sentence): every member lives
  *             alone in its own copy of each world, i.e. a FORAGE world with one agent (agent index 0): all
  *             members start at the same place among the same items and part ways through what they eat; the
@@ -374,8 +375,9 @@ int evo_forage_step(const task_desc* td, int32_t pop, const float* pos_dev, cons
  * be NULL. */
 int evo_forage_state(const task_desc* td, const policy_desc* pd, const void* params_dev, int32_t pop, int32_t steps,
                      float* pos_dev, float* vel_dev, int32_t* reward_dev, uint32_t* counts_dev, void* stream);
-/* The same where a wait of one workgroup of a world for another lasts at most wait_ticks (10 ns each) before the world is
- * played again without waits; 0: every wait fails.  The results are those of evo_forage_state whatever the bound. */
+/* The same in one launch wherever that can run, where a wait of one workgroup of a world for another lasts at most
+ * wait_ticks (10 ns each) before the world is played again without such waits; 0: every wait fails.  The results are those
+ * of evo_forage_state whatever the bound. */
 int evo_forage_state_bounded(const task_desc* td, const policy_desc* pd, const void* params_dev, int32_t pop, int32_t steps,
                              float* pos_dev, float* vel_dev, int32_t* reward_dev, uint32_t* counts_dev,
                              uint64_t wait_ticks, void* stream);

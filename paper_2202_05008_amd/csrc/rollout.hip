@@ -488,7 +488,7 @@ extern "C" int evo_forage_state_bounded(const task_desc* td, const policy_desc* 
                                         uint32_t* counts_dev, uint64_t wait_ticks, void* stream) {
   EVO_REQUIRE(pos_dev || vel_dev || reward_dev || counts_dev, EVO_ERR_ARG, "evo_forage_state_bounded: no output requested");
   ForageForm form;
-  form.wait_ticks = wait_ticks;
+  form.force = 1, form.wait_ticks = wait_ticks;
   if (wait_ticks == 0) form.fail_main = form.fail_items = 0, form.fail_groups = 0x7fffffff;
   return forage_impl(td, pd, params_dev, pop, steps, nullptr, pos_dev, vel_dev, reward_dev, counts_dev, stream, form);
 }

@@ -1394,6 +1394,36 @@ static size_t touch_words(int pop, int H, int chunks) {
 // Worlds of one launch of it.
 static int resident_worlds(int pop, int worlds, int H) { return std::min(worlds, kMaxResident / resident_groups(pop, H)); }
 
+// Is the episode in launches of per_launch worlds faster than a launch per step?  Each of them costs a fixed time of its
+// own, and each of its steps about 3 us however few agents the workgroups have; a step's launch takes as many rounds of 256
+// workgroups (8 agents x 4 worlds) as it has.  So a launch per step is better for a few steps, for many worlds of a few
+// agents, and, as a workgroup of the one launch has only 8 agents there, for many workgroups at H = 64.
+// Microseconds per step, a launch per step / this way, 24 + 24 items:
+//   H = 32: 64 x 8 worlds 7.0 / 3.0, 1024 x 1 7.3 / 3.7, 1024 x 8 9.3 / 3.6, 4800 x 1 51 / 8.7, 64 x 512 24 / 12, 1024 x 64 60 / 29,
+//           8 x 512 6.9 / 5.6, 8 x 1024 6.9 / 10.8, 8 x 4096 24 / 43, 16 x 4096 47 / 43, 32 x 4096 92 / 45
+//   H = 16: 8 x 4096 13 / 40, 32 x 4096 46 / 40, 256 x 1024 89 / 89
+//   H = 64: 64 x 8 13.4 / 3.4, 1024 x 2 11.6 / 4.0, 600 x 6 15.3 / 8.4, 1024 x 8 17.0 / 16.6, 8 x 4096 51 / 48, 512 x 64 55 / 65, 1024 x 64 120 / 135
+// and whole calls: H = 32, 1024 x 8, 1 step 13.4 / 20.1, 2 steps 22.2 / 23.0, 4 steps 40 / 30; 8 x 1, 4 steps 23.3 / 25.6.
+// Over 360 sizes of 2 to 4800 agents in 1 to 4096 worlds and 1 to 120 steps the estimates below choose the slower form by
+// 2 % and more eleven times, by 6 % at most.
+static bool one_launch_pays(int H, int pop, int worlds, int steps, int per_launch) {
+  struct Cost {
+    float launch, round, world, agent;  // us of a step's launch: fixed, and of a round: fixed, per world (of four), per agent of a world
+    float step, step_agent;             // us of a step of the one launch: fixed, per agent
+  };
+  const Cost c = H == 16   ? Cost{3.7f, 0.73f, 0.48f, 0.0007f, 2.55f, 0.0009f}
+                 : H == 32 ? Cost{1.6f, 2.7f, 0.75f, 0.0015f, 2.75f, 0.0008f}
+                           : Cost{3.2f, 1.65f, 2.57f, 0.0025f, 3.05f, 0.0021f};
+  const int64_t blocks = static_cast<int64_t>((pop + kAgentsPerBlock - 1) / kAgentsPerBlock) * ((worlds + kWorldsPerBlock - 1) / kWorldsPerBlock);
+  // (H = 16: two workgroups fit a compute unit)
+  const float rounds = H == 16 ? std::max(1.f, static_cast<float>(blocks) / 256.f) : static_cast<float>((blocks + 255) / 256);
+  const float staged = static_cast<float>(pop) + 1.2f * static_cast<float>(std::max(0, pop - 1024));  // fewer workgroups fit
+  const float per_step = c.launch + rounds * (c.round + c.world * static_cast<float>(std::min(worlds, kWorldsPerBlock)) + c.agent * staged);
+  const float scanned = static_cast<float>(H == 64 ? std::min(pop, 512) + 0.35f * static_cast<float>(std::max(0, pop - 512)) : pop);
+  const float launches = static_cast<float>((worlds + per_launch - 1) / per_launch);
+  return static_cast<float>(steps) * (1.05f * per_step - launches * (c.step + c.step_agent * scanned)) > 8.f + 3.5f * launches;
+}
+
 static Layout carve(int pop, int worlds, int n_items) {
   const size_t agents = static_cast<size_t>(pop) * worlds;
   auto up = [](size_t n) { return (n + 255) & ~size_t(255); };
@@ -1584,14 +1614,12 @@ int launch_forage(const MlpShape& sh, const float* params, int pop, int worlds, 
   uint32_t* hits[3] = {book + 2 * nb, book + 3 * nb, book + 4 * nb};
 
   // The whole episode in one launch for as many worlds as the chip holds at once, one such launch after the other: where a
-  // world has at most 256 workgroups (any that is supported; at H = 64 pop <= 2048), and with constants that keep every position a number in [0, 1] (the tags
-  // of the handed-over positions need it).  Microseconds per step, 24 + 24 items, a launch per step / this way:
-  //   H = 32: 64 x 8 worlds 7.2 / 3.0, 1024 x 1 7.2 / 3.6, 1024 x 8 9.3 / 3.9, 4800 x 1 51 / 9.0, 64 x 512 27 / 13.4, 1024 x 64 62 / 29
-  //   H = 64: 64 x 8 13.2 / 3.1, 1024 x 2 11.6 / 4.0, 600 x 6 15.6 / 8.4, 1024 x 8 17.9 / 16.6
+  // world has at most 256 workgroups (any that is supported; at H = 64 pop <= 2048), where that is faster, and with constants
+  // that keep every position a number in [0, 1] (the tags of the handed-over positions need it).
   const int H = sh.dims[1], groups = resident_groups(pop, H), per_launch = resident_worlds(pop, worlds, H);
   const bool tame = std::isfinite(cp[0]) && std::isfinite(cp[1]) && std::isfinite(cp[2]) && std::isfinite(cp[3]);
   ResidentTurn* turn = nullptr;
-  if (form.force != 2 && tame && l.room && per_launch > 0 &&
+  if (form.force != 2 && tame && l.room && per_launch > 0 && (form.force == 1 || one_launch_pays(H, pop, worlds, steps, per_launch)) &&
       static_cast<uint64_t>((worlds + per_launch - 1) / per_launch) * (static_cast<uint64_t>(steps) + 1) < (1ull << 32))
     turn = resident_turn(groups * per_launch, s);
 
