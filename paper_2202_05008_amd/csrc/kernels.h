@@ -88,12 +88,12 @@ int launch_cartpole_step(const float* cp, const float* state, const float* actio
 
 // The shared-world task: every member is an agent of each of `worlds` worlds; the whole episode in one launch where the
 // worlds fit the chip, one launch per step otherwise.  A wait of that one launch lasts at most wait_ticks of the 100 MHz
-// clock (kForageWaitTicks: far above any wait between workgroups that run, short enough to notice).
-constexpr uint64_t kForageWaitTicks = 20000000;
+// clock (kForageWait: as suits the length of the episode).
+constexpr uint64_t kForageWait = ~0ull;
 // How an episode is played; the defaults are what a roll-out takes, the rest is for checks.
 struct ForageForm {
   int force = 0;  // 1: in one launch wherever that can run, 2: a launch per step, 0: as measured to be faster
-  uint64_t wait_ticks = kForageWaitTicks;
+  uint64_t wait_ticks = kForageWait;
   int fail_main = 0x7fffffff, fail_items = 0x7fffffff, fail_groups = 0;  // the one launch: see ResidentArgs
   uint32_t* told = nullptr;  // [worlds]: 0 played step by step, 1 in the one launch, 2 given up there and played again
 };

@@ -567,8 +567,11 @@ __global__ __launch_bounds__(kStepThreads) void world_step_kernel(StepArgs a) {
 //
 // A wait needs the other workgroups of the world on the chip.  The host launches no more workgroups than compute units
 // and one such launch at a time; where other work holds the chip all the same, a wait ends after wait_ticks, the
-// world's flag is raised, everybody leaves, and world_rerun_kernel plays the world again from its start without
-// waiting for anyone.
+// flag of the world's place in its launch is raised, everybody leaves, and world_rerun_kernel plays the world again from
+// its start, on whatever part of the chip it gets.  The flag stays up for the episode's later launches: who waits at that
+// place then leaves at the first look at it, and the place's worlds are played again, the finished ones for the same result.
+// (A check of the launch before at each start took 10 % of the step, by other scalar registers for the loop; so did the
+// place's number in place of the world's at H = 32, while H = 16 gained as much.)
 constexpr int kMainWaves = 8;           // main waves per workgroup
 constexpr int kMaxResident = 256;       // workgroups of a launch; the room in the workspace is for these
 constexpr uint32_t kFar = 0x7F800000u;  // infinity's bits
@@ -592,7 +595,7 @@ struct ResidentArgs {
   uint32_t tag0;             // the tag of step t's touches is tag0 + t (a number of no launch before)
   int world0, per_launch;    // the launch's first world and the most worlds it has
   int groups;                // workgroups of a world
-  uint32_t* flag;            // [worlds]: a wait has ended without its word
+  uint32_t* flag;            // of a world's place in the launch, at the world's number: a wait has ended without its word
   unsigned long long wait_ticks;  // of the 100 MHz clock
   // CHECK: from these steps on the main waves of the first fail_groups workgroups of a world wait for positions that nobody
   // hands over, and their item waves for such touches
@@ -1149,10 +1152,20 @@ __global__ __launch_bounds__(resident_threads(H)) void world_resident_kernel(con
   }
 }
 
-// Plays the worlds again that world_resident_kernel gave up, step by step with world_step_block, one workgroup for four
-// worlds (a world of the four that was not given up gets the same result once more).  Nothing to do otherwise.
+// Plays the worlds again that world_resident_kernel gave up, with world_step_block (a world of its four that was not given
+// up gets the same result once more).  Nothing to do otherwise.
+// The chip may be held by other work here, so nothing may depend on how many of the workgroups run.  The crew of four
+// worlds takes tickets from a counter: phase 0 sets the worlds up, phase t + 1 is step t, the last one the item book,
+// each a ticket per workgroup of the step's grid.  A ticket's holder waits until every ticket of the phases before is
+// done.  Those are held by workgroups that run (a ticket is taken by running), and the holder of the lowest one that is
+// not done waits for nobody: every wait ends, with one workgroup on the chip as well as with all.
+// 1024 agents x 8 worlds x 500 steps, H = 32, every wait given up: 17 ms (by one workgroup per four
+// worlds 455 ms, with the fences in every wave 40 ms); 1024 x 64 x 50 11 ms, 4800 x 1 x 20 2.5 ms.
 struct RerunArgs {
-  const uint32_t* flag;  // [worlds]
+  const uint32_t* flag;  // [per_launch]
+  int per_launch;        // worlds of one launch
+  uint32_t* tickets;     // per four worlds: taken, done (zero at the start)
+  int crew;              // workgroups of four worlds
   int steps;
   float2* pos[2];
   uint32_t* book;        // counts[2] and hits[3]: 5 x [worlds][n_items]
@@ -1162,42 +1175,61 @@ struct RerunArgs {
 template <int H, bool TANH>
 __global__ __launch_bounds__(kStepThreads) void world_rerun_kernel(StepArgs a, RerunArgs r) {
   extern __shared__ float4 lds4[];
-  const int world0 = blockIdx.x * kWorldsPerBlock, world1 = min(world0 + kWorldsPerBlock, a.worlds);
+  const int tid = threadIdx.x, four = blockIdx.x / r.crew;
+  const int world0 = four * kWorldsPerBlock, world1 = min(world0 + kWorldsPerBlock, a.worlds);
   uint32_t any = 0;
-  for (int w = world0; w < world1; ++w) any |= r.flag[w];
+  for (int w = world0; w < world1; ++w) any |= r.flag[w % r.per_launch];
   if (!any) return;
   if (a.gen_dev) a.gen = *a.gen_dev;
   const size_t nb = static_cast<size_t>(a.worlds) * a.c.n_items;
-  for (int i = world0 * a.pop + threadIdx.x; i < world1 * a.pop; i += kStepThreads) {
-    const u32x4 w = philox4x32_10(static_cast<uint32_t>(i % a.pop), static_cast<uint32_t>(i / a.pop), a.gen, kTagAgent, a.key0, a.key1);
-    r.pos[0][i] = make_float2(unit_open(w.x), unit_open(w.y));
-    a.vel_out[i] = make_float2(0.f, 0.f);
-    a.reward[i] = 0;
-  }
-  for (int k = 0; k < 5; ++k)
-    for (int i = world0 * a.c.n_items + threadIdx.x; i < world1 * a.c.n_items; i += kStepThreads) r.book[k * nb + i] = 0u;
-  const int blocks = (a.pop + kAgentsPerBlock - 1) / kAgentsPerBlock;
+  const uint32_t blocks = (a.pop + kAgentsPerBlock - 1) / kAgentsPerBlock;
+  const uint32_t total = blocks * (r.steps + (r.counts_out ? 2u : 1u));  // (below 2^30: 2^20 steps of 613 workgroups)
+  uint32_t* taken = r.tickets + 2 * four;
+  uint32_t* done = taken + 1;
+  uint32_t* s_ticket = reinterpret_cast<uint32_t*>(lds4);  // (in the staging area, before a step uses it)
+  // One thread's part of a round stands in one place: with its count at the round's end and its ticket at the next one's
+  // start, the compiler let the other 63 lanes of its wave go round without it, past the barriers.
 #pragma unroll 1
-  for (int t = 0; t < r.steps; ++t) {
-    // what the step before wrote is read by other waves of this workgroup (and its touches were set behind this
-    // compute unit's cache)
-    __threadfence();
-    __syncthreads();
-    a.pos_in = r.pos[t & 1], a.pos_out = r.pos[(t + 1) & 1];
-    a.counts_in = r.book + (t & 1) * nb, a.counts_out = r.book + ((t + 1) & 1) * nb;
-    a.hits_prev = t > 0 ? r.book + (2 + (t + 2) % 3) * nb : nullptr;
-    a.hits_cur = r.book + (2 + t % 3) * nb, a.hits_clear = r.book + (2 + (t + 1) % 3) * nb;
-#pragma unroll 1
-    for (int b = 0; b < blocks; ++b) {
-      world_step_block<H, TANH>(a, b, blockIdx.x, lds4);
-      __syncthreads();  // the staging area is free again
+  for (uint32_t finished = 0;; finished = 1u) {
+    if (tid == 0) {
+      __threadfence();  // (release) what every wave wrote, which has arrived at the die's cache
+      if (finished) atomicAdd(done, 1u);
+      const uint32_t mine = atomicAdd(taken, 1u);
+      const uint32_t before = mine / blocks * blocks;
+      while (mine < total && __hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < before)
+        __builtin_amdgcn_s_sleep(4);
+      __threadfence();  // (acquire) what the phases before wrote, on whatever die; this compute unit's cache is every wave's
+      *s_ticket = mine;
     }
+    __syncthreads();
+    const uint32_t ticket = __builtin_amdgcn_readfirstlane(*s_ticket);
+    __syncthreads();  // the staging area is free
+    if (ticket >= total) return;
+    const int phase = static_cast<int>(ticket / blocks), block = static_cast<int>(ticket % blocks);
+    const int first = block * kStepThreads + tid, stride = static_cast<int>(blocks) * kStepThreads;
+    if (phase == 0) {
+      for (int i = world0 * a.pop + first; i < world1 * a.pop; i += stride) {
+        const u32x4 w = philox4x32_10(static_cast<uint32_t>(i % a.pop), static_cast<uint32_t>(i / a.pop), a.gen, kTagAgent, a.key0, a.key1);
+        r.pos[0][i] = make_float2(unit_open(w.x), unit_open(w.y));
+        a.vel_out[i] = make_float2(0.f, 0.f);
+        a.reward[i] = 0;
+      }
+      for (int k = 0; k < 5; ++k)
+        for (int i = world0 * a.c.n_items + first; i < world1 * a.c.n_items; i += stride) r.book[k * nb + i] = 0u;
+    } else if (phase <= r.steps) {
+      const int t = phase - 1;
+      a.pos_in = r.pos[t & 1], a.pos_out = r.pos[(t + 1) & 1];
+      a.counts_in = r.book + (t & 1) * nb, a.counts_out = r.book + ((t + 1) & 1) * nb;
+      a.hits_prev = t > 0 ? r.book + (2 + (t + 2) % 3) * nb : nullptr;
+      a.hits_cur = r.book + (2 + t % 3) * nb, a.hits_clear = r.book + (2 + (t + 1) % 3) * nb;
+      world_step_block<H, TANH>(a, block, four, lds4);
+    } else {
+      for (int i = world0 * a.c.n_items + first; i < world1 * a.c.n_items; i += stride)
+        r.counts_out[i] = r.book[(r.steps & 1) * nb + i] + r.book[(2 + (r.steps - 1) % 3) * nb + i];
+    }
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __syncthreads();
   }
-  __threadfence();
-  __syncthreads();
-  if (r.counts_out)
-    for (int i = world0 * a.c.n_items + threadIdx.x; i < world1 * a.c.n_items; i += kStepThreads)
-      r.counts_out[i] = r.book[(r.steps & 1) * nb + i] + r.book[(2 + (r.steps - 1) % 3) * nb + i];
 }
 
 // ---- single-agent form: every member alone in its own copy of each world ---------------------------------
@@ -1329,8 +1361,8 @@ struct ResetArgs {
   // of the launch with waits, or null: positions of odd steps (a step number no reader waits for first), touches and flags
   unsigned long long* odd;
   unsigned long long* hand;
-  uint32_t* flag;
-  int n_hand;
+  uint32_t* flag;  // and the second run's tickets behind them
+  int n_hand, n_flag;
 };
 
 __global__ __launch_bounds__(256) void world_reset_kernel(ResetArgs a) {
@@ -1346,7 +1378,7 @@ __global__ __launch_bounds__(256) void world_reset_kernel(ResetArgs a) {
   }
   if (i < 5 * a.worlds * a.n_items) a.book[i] = 0u;
   if (i < a.n_hand) a.hand[i] = 0ull;
-  if (a.flag && i < a.worlds) a.flag[i] = 0u;
+  if (i < a.n_flag) a.flag[i] = 0u;
 }
 
 // fitness[a] = mean over the worlds of the summed reward (an exact integer sum, one division).
@@ -1364,9 +1396,9 @@ __global__ __launch_bounds__(256) void world_fill_kernel(uint32_t* dst, int n, u
 }
 
 // How each world was played (ForageForm::told), from the flags of the launch with waits.
-__global__ __launch_bounds__(256) void world_told_kernel(const uint32_t* flag, int worlds, uint32_t* told) {
+__global__ __launch_bounds__(256) void world_told_kernel(const uint32_t* flag, int per_launch, int worlds, uint32_t* told) {
   const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i < worlds) told[i] = 1u + flag[i];
+  if (i < worlds) told[i] = 1u + flag[i % per_launch];
 }
 
 // counts_out = counts + hits (the book after the last step), for the state hook.
@@ -1424,6 +1456,11 @@ static bool one_launch_pays(int H, int pop, int worlds, int steps, int per_launc
   return static_cast<float>(steps) * (1.05f * per_step - launches * (c.step + c.step_agent * scanned)) > 8.f + 3.5f * launches;
 }
 
+// A flag per world of a launch (at most all worlds), and the second run's two tickets per four worlds.
+static size_t flag_words(int worlds) {
+  return static_cast<size_t>(worlds) + 2 * static_cast<size_t>((worlds + kWorldsPerBlock - 1) / kWorldsPerBlock);
+}
+
 static Layout carve(int pop, int worlds, int n_items) {
   const size_t agents = static_cast<size_t>(pop) * worlds;
   auto up = [](size_t n) { return (n + 255) & ~size_t(255); };
@@ -1441,7 +1478,7 @@ static Layout carve(int pop, int worlds, int n_items) {
   // loses its room asks for the whole built-in scratch.
   const size_t groups = std::min(static_cast<size_t>(kMaxResident), static_cast<size_t>(resident_groups(pop, 64)) * worlds);
   l.hand = o, l.flag = o + up(2 * groups * most_chunks(n_items) * sizeof(unsigned long long));
-  l.bytes = l.flag + up(static_cast<size_t>(worlds) * sizeof(uint32_t));
+  l.bytes = l.flag + up(flag_words(worlds) * sizeof(uint32_t));
   l.room = o > EVO_STATIC_SCRATCH_BYTES || l.bytes <= EVO_STATIC_SCRATCH_BYTES;
   if (!l.room) l.bytes = EVO_STATIC_SCRATCH_BYTES;
   return l;
@@ -1528,6 +1565,9 @@ size_t forage_workspace_bytes(int pop, int worlds, const float* cp) {
 }
 
 // ---- the whole episode in one launch: host side ----
+// A wait for workgroups that are not on the chip lasts about as long as playing the worlds again does (1 ms, and 20 us a
+// step), so that at worst an episode takes twice that; the longest wait between workgroups that run is some 10 us.
+constexpr uint64_t kWaitTicks = 100000, kWaitTicksPerStep = 2000;  // of 10 ns
 // Launches with waits follow one another: two at a time could each hold a part of the chip and wait for the rest of it.
 struct ResidentTurn {
   std::mutex m;
@@ -1561,7 +1601,7 @@ static int launch_rerun_acts(const StepArgs& a, const RerunArgs& r, size_t lds, 
     const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kMaxLdsBytes));
     EVO_REQUIRE(e == hipSuccess, EVO_ERR_HIP, "forage: raising the LDS limit of the second run failed: %s", hipGetErrorString(e));
   }
-  const dim3 grid((a.worlds + kWorldsPerBlock - 1) / kWorldsPerBlock);
+  const dim3 grid((a.worlds + kWorldsPerBlock - 1) / kWorldsPerBlock * r.crew);
   if (all_tanh) hipLaunchKernelGGL((world_rerun_kernel<H, true>), grid, dim3(kStepThreads), lds, s, a, r);
   else hipLaunchKernelGGL((world_rerun_kernel<H, false>), grid, dim3(kStepThreads), lds, s, a, r);
   return check_launch("world_rerun_kernel");
@@ -1627,14 +1667,14 @@ int launch_forage(const MlpShape& sh, const float* params, int pop, int worlds, 
   ra.pop = pop, ra.worlds = worlds, ra.n_items = c.n_items;
   ra.key0 = static_cast<uint32_t>(seed), ra.key1 = static_cast<uint32_t>(seed >> 32), ra.gen = gen, ra.gen_dev = gen_dev;
   ra.pos = pos[0], ra.vel = vel, ra.reward = reward, ra.book = book;
-  ra.odd = nullptr, ra.hand = nullptr, ra.flag = nullptr, ra.n_hand = 0;
+  ra.odd = nullptr, ra.hand = nullptr, ra.flag = nullptr, ra.n_hand = 0, ra.n_flag = 0;
   const int chunks = item_chunks(c.n_food, c.n_items);
   if (turn) {
     ra.odd = reinterpret_cast<unsigned long long*>(pos[1]);
     ra.hand = reinterpret_cast<unsigned long long*>(base + l.hand), ra.n_hand = static_cast<int>(2 * touch_words(pop, H, chunks) * per_launch);
-    ra.flag = reinterpret_cast<uint32_t*>(base + l.flag);
+    ra.flag = reinterpret_cast<uint32_t*>(base + l.flag), ra.n_flag = static_cast<int>(flag_words(worlds));
   }
-  const int n_reset = static_cast<int>(std::max({static_cast<size_t>(worlds) * pop, 5 * nb, static_cast<size_t>(ra.n_hand)}));
+  const int n_reset = static_cast<int>(std::max({static_cast<size_t>(worlds) * pop, 5 * nb, static_cast<size_t>(ra.n_hand), static_cast<size_t>(ra.n_flag)}));
   hipLaunchKernelGGL(world_reset_kernel, dim3((n_reset + 255) / 256), dim3(256), 0, s, ra);
   rc = check_launch("world_reset_kernel");
   if (rc) return rc;
@@ -1654,7 +1694,7 @@ int launch_forage(const MlpShape& sh, const float* params, int pop, int worlds, 
     b.per_lane = pad_to((pop + 63) / 64, 2);
     b.lane_magic = static_cast<uint32_t>(((1ull << 32) + b.per_lane - 1) / b.per_lane);
     b.even = reinterpret_cast<unsigned long long*>(pos[0]), b.odd = reinterpret_cast<unsigned long long*>(pos[1]);
-    b.hand = ra.hand, b.groups = groups, b.flag = ra.flag, b.wait_ticks = form.wait_ticks;
+    b.hand = ra.hand, b.groups = groups, b.wait_ticks = form.wait_ticks == kForageWait ? kWaitTicks + kWaitTicksPerStep * static_cast<uint64_t>(steps) : form.wait_ticks;
     b.fail_main = form.fail_main, b.fail_items = form.fail_items, b.fail_groups = form.fail_groups;
     b.reward = reward, b.pos_out = pos[steps & 1], b.vel_out = vel, b.counts_out = counts_out;
     const int stride = (b.per_lane >> 1) & 1 ? b.per_lane : b.per_lane + 2;
@@ -1668,7 +1708,7 @@ int launch_forage(const MlpShape& sh, const float* params, int pop, int worlds, 
       EVO_REQUIRE(e == hipSuccess, EVO_ERR_HIP, "forage: waiting for the launch before failed: %s", hipGetErrorString(e));
       b.per_launch = per_launch;
       for (int w = 0; w < worlds; w += per_launch) {
-        b.world0 = w, b.tag0 = static_cast<uint32_t>(w / per_launch) * (static_cast<uint32_t>(steps) + 1u);
+        b.world0 = w, b.flag = ra.flag - w, b.tag0 = static_cast<uint32_t>(w / per_launch) * (static_cast<uint32_t>(steps) + 1u);
         rc = launch_resident(H, b, std::min(per_launch, worlds - w), lds, s);
         if (rc) return rc;
       }
@@ -1677,7 +1717,9 @@ int launch_forage(const MlpShape& sh, const float* params, int pop, int worlds, 
       turn->used = true;
     }
     RerunArgs r;
-    r.flag = ra.flag, r.steps = steps, r.pos[0] = pos[0], r.pos[1] = pos[1], r.book = book, r.counts_out = counts_out;
+    const int fours = (worlds + kWorldsPerBlock - 1) / kWorldsPerBlock, blocks = (pop + kAgentsPerBlock - 1) / kAgentsPerBlock;
+    r.tickets = ra.flag + worlds, r.crew = std::max(1, std::min(blocks, kMaxResident / fours));
+    r.flag = ra.flag, r.per_launch = per_launch, r.steps = steps, r.pos[0] = pos[0], r.pos[1] = pos[1], r.book = book, r.counts_out = counts_out;
     rc = launch_rerun(H, a, r, step_lds_bytes(pop, c.n_food, c.n_items), s);
     if (rc) return rc;
   }
@@ -1690,7 +1732,7 @@ int launch_forage(const MlpShape& sh, const float* params, int pop, int worlds, 
     if (rc) return rc;
   }
   if (form.told) {
-    if (turn) hipLaunchKernelGGL(world_told_kernel, dim3((worlds + 255) / 256), dim3(256), 0, s, ra.flag, worlds, form.told);
+    if (turn) hipLaunchKernelGGL(world_told_kernel, dim3((worlds + 255) / 256), dim3(256), 0, s, ra.flag, per_launch, worlds, form.told);
     else hipLaunchKernelGGL(world_fill_kernel, dim3((worlds + 255) / 256), dim3(256), 0, s, form.told, worlds, 0u);
     rc = check_launch("world_told_kernel");
     if (rc) return rc;

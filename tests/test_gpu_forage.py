@@ -307,6 +307,45 @@ def test_a_rollout_takes_the_form_that_is_faster(evo, pop, worlds, H, steps, one
     assert all(torch.equal(own[k], other[k]) for k in own)
 
 
+def _ms(run):
+    best = float("inf")
+    for _ in range(3):
+        start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        start.record()
+        run()
+        end.record()
+        end.synchronize()
+        best = min(best, start.elapsed_time(end))
+    return best
+
+
+def test_an_episode_that_is_given_up_does_not_collapse(evo):
+    """Where other work holds the chip, worlds are played again by as many workgroups as there are, not by one for four
+    worlds: 8 times the episode here, and 220 with one for four."""
+    pop, worlds, steps = 1024, 8, 100
+    w = dict(forage.WORLD_DEFAULT, radius=0.0625)
+    pd = evo.make_policy_desc(evo.EVO_POLICY_MLP, (8, 32, 32, 2), (1, 1, 1))
+    params = dev(_random_policies(pop, (8, 32, 32, 2), 0.5, 3))
+    td = _task(evo, w, worlds, pop, pd)
+    one = _ms(lambda: _state(evo, td, pd, params, pop, worlds, 48, steps, form=1))
+    again = _ms(lambda: _state(evo, td, pd, params, pop, worlds, 48, steps, 0))
+    assert again < 20 * one, (again, one)
+
+
+def test_later_launches_of_an_episode_that_is_given_up_do_not_wait(evo):
+    """128 launches of 32 worlds: the first one's wait ends in vain after 0.2 ms, and the others leave at once (each waiting
+    0.2 ms of its own, they took 26 ms)."""
+    pop, worlds, steps = 64, 4096, 2
+    w = dict(forage.WORLD_DEFAULT, radius=0.0625)
+    pd = evo.make_policy_desc(evo.EVO_POLICY_MLP, (8, 64, 64, 2), (1, 1, 1))
+    params = dev(_random_policies(pop, (8, 64, 64, 2), 0.5, 3))
+    td = _task(evo, w, worlds, pop, pd)
+    want = _state(evo, td, pd, params, pop, worlds, 48, steps, form=2, expect=0)
+    got = _state(evo, td, pd, params, pop, worlds, 48, steps, form=1, expect=2, fail_step=1, fail_items=0)
+    assert all(torch.equal(want[k], got[k]) for k in want)
+    assert _ms(lambda: _state(evo, td, pd, params, pop, worlds, 48, steps, form=1, fail_step=1, fail_items=0)) < 13
+
+
 def test_one_launch_episodes_on_two_streams(evo):
     """Each launch fills the chip: they take turns, whatever stream they are on, and no world is given up."""
     w = dict(forage.WORLD_DEFAULT, radius=0.0625)
