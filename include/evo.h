@@ -302,9 +302,11 @@ typedef struct {
 size_t rollout_workspace_bytes(const task_desc* td, const policy_desc* pd, int32_t pop);
 
 /* Evaluate every member: fitness_dev[pop] as defined above.  `steps` is the episode length
- * for CARTPOLE and FORAGE (FORAGE enqueues steps + 2 kernels and keeps the worlds' state in
+ * for CARTPOLE and FORAGE (FORAGE keeps the worlds' state in
  * work_dev, so two roll-outs that share a workspace must not overlap; the same holds for the
- * ConvNet, whose converted batch sits there) and must be 1 for the single-step tasks.
+ * ConvNet, whose converted batch sits there) and must be 1 for the single-step tasks.  FORAGE enqueues steps + 2
+ * kernels, or, for an episode in one launch, three and a launch per batch of worlds that fits the chip; its first such
+ * call on a GPU creates an event, which orders these launches of several streams.
  * Errors: EVO_ERR_ARG, EVO_ERR_UNSUPPORTED, EVO_ERR_HIP. */
 int rollout(const task_desc* td, const policy_desc* pd, const void* params_dev, int32_t pop, int32_t steps,
             float* fitness_dev, void* stream);
@@ -336,7 +338,7 @@ int pgpe_generation(pgpe_state* st, uint64_t seed, int32_t pop, const task_desc*
 /* rollout for callers that cannot allocate device memory (code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc): the same evaluation, by the same kernels, as rollout, but the
  * workspace is a fixed array inside the library's device image (EVO_STATIC_SCRATCH_BYTES per GPU, held until
- * the process ends) instead of td->work_dev, which is ignored.  Calls no allocating routine.  A task whose
+ * the process ends) instead of td->work_dev, which is ignored.  Calls no allocating routine and creates nothing.  A task whose
  * rollout_workspace_bytes() exceeds the array is refused with EVO_ERR_UNSUPPORTED before anything is
  * launched.  Every call on a GPU shares that GPU's array (each kernel writes what it later reads; nothing has to
  * start at zero): two calls that overlap on one GPU, on different streams or threads, race.

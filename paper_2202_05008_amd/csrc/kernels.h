@@ -95,6 +95,7 @@ struct ForageForm {
   int force = 0;  // 1: in one launch wherever that can run, 2: a launch per step, 0: as measured to be faster
   uint64_t wait_ticks = kForageWait;
   int fail_main = 0x7fffffff, fail_items = 0x7fffffff, fail_groups = 0;  // the one launch: see ResidentArgs
+  bool create = true;  // may create the device's event, which orders the one launches of several streams
   uint32_t* told = nullptr;  // [worlds]: 0 played step by step, 1 in the one launch, 2 given up there and played again
 };
 // `work` holds forage_workspace_bytes(...) bytes.  The state outputs (positions and velocities

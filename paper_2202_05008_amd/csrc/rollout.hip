@@ -212,7 +212,7 @@ static int forage_impl(const task_desc* td, const policy_desc* pd, const void* p
 
 static int rollout_impl(const task_desc* td, const policy_desc* pd, const void* params_dev, int32_t pop,
                         int32_t steps, float* fitness_dev, float* ret_dev, float* final_dev, float* trace_dev,
-                        void* stream) {
+                        void* stream, bool create = true) {
   int rc = check_task(td);
   if (rc) return rc;
   EVO_REQUIRE(params_dev != nullptr, EVO_ERR_ARG, "rollout: null device pointer");
@@ -233,7 +233,9 @@ static int rollout_impl(const task_desc* td, const policy_desc* pd, const void* 
   }
   if (td->kind == EVO_TASK_FORAGE || td->kind == EVO_TASK_FORAGE_SOLO) {
     EVO_REQUIRE(fitness_dev != nullptr, EVO_ERR_ARG, "rollout: fitness_dev is null");
-    return forage_impl(td, pd, params_dev, pop, steps, fitness_dev, nullptr, nullptr, nullptr, nullptr, stream);
+    ForageForm form;
+    form.create = create;
+    return forage_impl(td, pd, params_dev, pop, steps, fitness_dev, nullptr, nullptr, nullptr, nullptr, stream, form);
   }
   if (td->kind == EVO_TASK_SEQ2SEQ) {
     EVO_REQUIRE(fitness_dev != nullptr, EVO_ERR_ARG, "rollout: fitness_dev is null");
@@ -446,7 +448,7 @@ extern "C" int rollout_static_scratch(const task_desc* td, const policy_desc* pd
   rc = static_scratch(&ptr);
   if (rc) return rc;
   local.work_dev = need ? ptr : nullptr;
-  return rollout_impl(&local, pd, params_dev, pop, steps, fitness_dev, nullptr, nullptr, nullptr, stream);
+  return rollout_impl(&local, pd, params_dev, pop, steps, fitness_dev, nullptr, nullptr, nullptr, stream, false);
 }
 
 extern "C" int evo_rollout_details(const task_desc* td, const policy_desc* pd, const void* params_dev, int32_t pop,

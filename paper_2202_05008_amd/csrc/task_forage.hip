@@ -1615,8 +1615,9 @@ static int launch_rerun(int H, const StepArgs& a, const RerunArgs& r, size_t lds
 }
 
 // May this call take the launch with waits?  Not into a recorded graph (its replays would not take their turn), and
-// only with a compute unit per workgroup.  The turn of the device, or null.
-static ResidentTurn* resident_turn(int workgroups, hipStream_t s) {
+// only with a compute unit per workgroup.  The turn of the device, or null.  A caller that may not create anything takes the
+// launch without an event as long as there is none; another stream's launch that it meets then costs both a second run.
+static ResidentTurn* resident_turn(int workgroups, bool create, hipStream_t s) {
   static ResidentTurn turns[64];
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(s, &capture) != hipSuccess) {
@@ -1629,7 +1630,7 @@ static ResidentTurn* resident_turn(int workgroups, hipStream_t s) {
     return nullptr;
   ResidentTurn* turn = &turns[device];
   std::lock_guard<std::mutex> lock(turn->m);
-  if (!turn->done && hipEventCreateWithFlags(&turn->done, hipEventDisableTiming) != hipSuccess) {
+  if (create && !turn->done && hipEventCreateWithFlags(&turn->done, hipEventDisableTiming) != hipSuccess) {
     turn->done = nullptr;
     (void)hipGetLastError();
     return nullptr;
@@ -1661,7 +1662,7 @@ int launch_forage(const MlpShape& sh, const float* params, int pop, int worlds, 
   ResidentTurn* turn = nullptr;
   if (form.force != 2 && tame && l.room && per_launch > 0 && (form.force == 1 || one_launch_pays(H, pop, worlds, steps, per_launch)) &&
       static_cast<uint64_t>((worlds + per_launch - 1) / per_launch) * (static_cast<uint64_t>(steps) + 1) < (1ull << 32))
-    turn = resident_turn(groups * per_launch, s);
+    turn = resident_turn(groups * per_launch, form.create, s);
 
   ResetArgs ra;
   ra.pop = pop, ra.worlds = worlds, ra.n_items = c.n_items;
@@ -1712,9 +1713,11 @@ int launch_forage(const MlpShape& sh, const float* params, int pop, int worlds, 
         rc = launch_resident(H, b, std::min(per_launch, worlds - w), lds, s);
         if (rc) return rc;
       }
-      e = hipEventRecord(turn->done, s);
-      EVO_REQUIRE(e == hipSuccess, EVO_ERR_HIP, "forage: recording the launch failed: %s", hipGetErrorString(e));
-      turn->used = true;
+      if (turn->done) {
+        e = hipEventRecord(turn->done, s);
+        EVO_REQUIRE(e == hipSuccess, EVO_ERR_HIP, "forage: recording the launch failed: %s", hipGetErrorString(e));
+        turn->used = true;
+      }
     }
     RerunArgs r;
     const int fours = (worlds + kWorldsPerBlock - 1) / kWorldsPerBlock, blocks = (pop + kAgentsPerBlock - 1) / kAgentsPerBlock;

@@ -71,3 +71,58 @@ def test_static_scratch_refuses_what_does_not_fit(evo):
     with pytest.raises(evo.EvoError) as e:
         evo.rollout_static_scratch(td, None, fake, pop, 1, torch.zeros(pop, device="cuda"))
     assert e.value.code == -3 and "built-in scratch" in str(e.value)
+
+
+_COUNTS = r"""
+static int (*real)(void**, unsigned);
+static int count;
+void set_real(void* f) { real = (int (*)(void**, unsigned))f; }
+int events_created(void) { return count; }
+int hipEventCreateWithFlags(void** event, unsigned flags) { ++count; return real(event, flags); }
+"""
+_PROGRAM = r"""
+import ctypes, sys
+stub = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)      # before anything that brings the runtime's own
+import torch
+import paper_2202_05008_amd as evo
+evo.make_policy_desc(evo.EVO_POLICY_MLP, (8, 32, 32, 2), (1, 1, 1))
+from paper_2202_05008_amd import _lib
+_lib.load()
+paths = {l.split()[-1] for l in open("/proc/self/maps") if "libamdhip64" in l}
+assert len(paths) == 1, paths
+real = ctypes.CDLL(paths.pop()).hipEventCreateWithFlags
+stub.set_real(ctypes.cast(real, ctypes.c_void_p))
+pop, worlds, steps = 64, 8, 40
+pd = evo.make_policy_desc(evo.EVO_POLICY_MLP, (8, 32, 32, 2), (1, 1, 1))
+params = torch.randn(pop, evo.policy_param_count(pd), device="cuda")
+cp = (0.0625, 0.015625, 0.875, 0.25, 0.0625, 24, 24)
+task = dict(n_rollouts=worlds, reset_seed=3, cp=cp)
+td = evo.make_task_desc(evo.EVO_TASK_FORAGE, **task)
+work = torch.empty(evo.rollout_workspace_bytes(td, pd, pop), dtype=torch.uint8, device="cuda")
+got, again, want = (torch.full((pop,), float("nan"), device="cuda") for _ in range(3))
+torch.cuda.synchronize()
+before = stub.events_created()
+evo.rollout_static_scratch(td, pd, params, pop, steps, got)
+assert stub.events_created() == before, "the entry point that allocates nothing created an event"
+evo.rollout(evo.make_task_desc(evo.EVO_TASK_FORAGE, work=work, **task), pd, params, pop, steps, want)
+assert stub.events_created() == before + 1, "rollout orders its one launches by an event"
+evo.rollout_static_scratch(td, pd, params, pop, steps, again)
+assert stub.events_created() == before + 1
+torch.cuda.synchronize()
+assert torch.isfinite(want).all() and torch.equal(got, want) and torch.equal(again, want)
+print("created nothing")
+"""
+
+
+def test_static_scratch_creates_no_event(tmp_path):
+    """A forage episode in one launch: the event that orders such launches is rollout's to create.  In a process of its
+    own, where the runtime's routine is counted and nothing has run before."""
+    import os
+    import subprocess
+    import sys
+    (tmp_path / "counts.c").write_text(_COUNTS)
+    stub = str(tmp_path / "libcounts.so")
+    subprocess.run(["gcc", "-shared", "-fPIC", "-o", stub, str(tmp_path / "counts.c")], check=True)
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", _PROGRAM, stub], capture_output=True, text=True, timeout=100, cwd=root)
+    assert r.returncode == 0 and "created nothing" in r.stdout, (r.stdout, r.stderr)
