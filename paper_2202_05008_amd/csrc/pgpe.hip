@@ -568,8 +568,10 @@ __device__ __forceinline__ void tell_block(TellArgs a, int block, PAIRS pairs, f
       a.mu[c] += vel;
     } else {
       a.v[c] = g_mu;  // ClipUp needs |g_mu| over all of P first: the gradient waits in v
-      const double vel = a.m[c], g = g_mu;
-      sq = fmaf(g_mu, g_mu, sq), gg = fma(g, g, gg), vv = fma(vel, vel, vv), vg = fma(vel, g, vg);
+      if (a.norm_part) {
+        const double vel = a.m[c], g = g_mu;
+        sq = fmaf(g_mu, g_mu, sq), gg = fma(g, g, gg), vv = fma(vel, vel, vv), vg = fma(vel, g, vg);
+      }
     }
     if (SRULE == 0) {
       const float lim = a.max_change * sg;
