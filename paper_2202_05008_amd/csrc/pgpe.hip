@@ -818,12 +818,15 @@ __global__ __launch_bounds__(256) void clipup_step_kernel(float* __restrict__ mu
 #pragma unroll
   for (int k = 0; k < 4; ++k) red[k][tid] = acc[k];
   __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (tid < s)
+  {  // a wave adds up one of the four, in a tree of halves
+    double* x = red[tid >> 6];
+    const int lane = tid & 63;
+    double sum = (x[lane] + x[lane + 128]) + (x[lane + 64] + x[lane + 192]);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) red[k][tid] += red[k][tid + s];
-    __syncthreads();
+    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+    if (lane == 0) x[0] = sum;
   }
+  __syncthreads();
   const double gg = red[0][0], vv = red[1][0], vg = red[2][0], n2 = red[3][0];
   const float scale = n2 > 0.0 ? static_cast<float>(static_cast<double>(step) / sqrt(n2)) : 0.f;
   const double m = momentum, sc = scale;
