@@ -445,8 +445,7 @@ struct TellArgs {
   int P, nquads, N, KS;
   uint32_t gen, key0, key1;
   const uint32_t* gen_dev;  // when set: t is read here and the bias corrections are formed in the kernel
-  float* norm_part;        // ClipUp: [kGradNormParts] partial sums of g_mu^2, one per workgroup, or null
-  double* norm_sums;       // behind them: [3][norm_parts] the same in fp64, of vel^2 and of vel g_mu
+  float* norm_part;        // ClipUp: [kGradNormParts] partial sums of g_mu^2, one per workgroup, or null; see norm_sums
   int norm_parts;
   float inv_n, lr_mu, lr_sigma, max_change, beta1, beta2, eps, bc1, bc2, momentum;
 };
@@ -458,6 +457,9 @@ __device__ __forceinline__ float adam_step(float x, float g, float& m, float& v,
   const float v_hat = v * a.bc2;
   return x + lr * m_hat / (sqrtf(v_hat) + a.eps);
 }
+
+// Behind them: [3][norm_parts] the same in fp64, of vel^2 and of vel g_mu.
+__host__ __device__ inline double* norm_sums(float* norm_part) { return reinterpret_cast<double*>(norm_part + kGradNormParts); }
 
 // Thread (q, ks): parameter quad q, pairs ks, ks+KS, ks+2KS, ...  The KS partial sums of a
 // quad are added in increasing ks by one thread, so the result does not depend on timing.
@@ -595,7 +597,7 @@ __device__ __forceinline__ void tell_block(TellArgs a, int block, PAIRS pairs, f
       double sum = (x[0] + x[64]) + (x[128] + x[192]);
 #pragma unroll
       for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
-      if (lane == 0) a.norm_sums[wave * a.norm_parts + block] = sum;
+      if (lane == 0) norm_sums(a.norm_part)[wave * a.norm_parts + block] = sum;
     }
   }
 }
@@ -1037,7 +1039,6 @@ static TellArgs tell_args(const pgpe_state* st, const float* fitness, float* gmu
   *blocks_out = static_cast<unsigned>((a.nquads + QPB - 1) / QPB);
   // the words of the one-launch generation, which ClipUp never runs as, take the partial sums
   a.norm_part = c.optimizer == EVO_OPT_CLIPUP && *blocks_out <= kGradNormParts ? reinterpret_cast<float*>(ws.gen + 64) : nullptr;
-  a.norm_sums = reinterpret_cast<double*>(ws.gen + 64 + kGradNormParts);
   a.norm_parts = static_cast<int>(*blocks_out);
   return a;
 }
@@ -1091,7 +1092,7 @@ static int run_tell(pgpe_state* st, const float* fitness, float* gmu, float* gsg
   const int grid = (P + 1023) / 1024 < kNormBlocks ? (P + 1023) / 1024 : kNormBlocks;  // four parameters per thread
   if (a.norm_part) {
     hipLaunchKernelGGL(clipup_step_kernel, dim3(grid), dim3(256), 0, s, st->mu, st->m, st->v, P, c.momentum, c.lr_mu, c.max_speed,
-                       a.norm_part, a.norm_sums, a.norm_parts);
+                       a.norm_part, norm_sums(a.norm_part), a.norm_parts);
     return check_launch("clipup_step_kernel");
   }
   hipLaunchKernelGGL(sqnorm_kernel, dim3(kNormBlocks), dim3(256), 0, s, st->v, P, ws.norm);
