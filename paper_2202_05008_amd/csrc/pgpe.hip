@@ -420,6 +420,25 @@ __device__ __forceinline__ void small_pairs(const float* fitness, int pop, int s
   __syncthreads();
 }
 
+// wave_sum's moves and order in fp64 (as shuffles through LDS 0.3 us a sum).
+template <typename MOVE>
+__device__ __forceinline__ double moved(double v, MOVE move) {
+  return __hiloint2double(move(__double2hiint(v)), move(__double2loint(v)));
+}
+__device__ __forceinline__ double wave_sum(double v) {
+  const unsigned lo = __double2loint(v), hi = __double2hiint(v);
+  const auto l32 = __builtin_amdgcn_permlane32_swap(lo, lo, false, false), h32 = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+  v = __hiloint2double(h32[0], l32[0]) + __hiloint2double(h32[1], l32[1]);
+  const unsigned lo16 = __double2loint(v), hi16 = __double2hiint(v);
+  const auto l = __builtin_amdgcn_permlane16_swap(lo16, lo16, false, false), h = __builtin_amdgcn_permlane16_swap(hi16, hi16, false, false);
+  v = __hiloint2double(h[0], l[0]) + __hiloint2double(h[1], l[1]);
+  v += moved(v, [](int x) { return __builtin_amdgcn_update_dpp(0, x, 0x128, 0xf, 0xf, false); });  // row_ror:8
+  v += moved(v, [](int x) { return __builtin_amdgcn_update_dpp(0, x, 0x124, 0xf, 0xf, false); });  // row_ror:4
+  v += moved(v, [](int x) { return __builtin_amdgcn_update_dpp(0, x, 0x4e, 0xf, 0xf, false); });   // quad_perm 2,3,0,1
+  v += moved(v, [](int x) { return __builtin_amdgcn_update_dpp(0, x, 0xb1, 0xf, 0xf, false); });   // quad_perm 1,0,3,2
+  return v;
+}
+
 // Sum of the 256 per-thread values of a workgroup, fixed order; valid in every thread.  scratch: 4 floats of LDS.
 __device__ __forceinline__ float block_sum256(float v, float* scratch) {
   v = wave_sum(v);
@@ -594,9 +613,7 @@ __device__ __forceinline__ void tell_block(TellArgs a, int block, PAIRS pairs, f
     const int wave = tid >> 6, lane = tid & 63;
     if (wave < 3) {
       const double* x = all + 256 * wave + lane;
-      double sum = (x[0] + x[64]) + (x[128] + x[192]);
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+      const double sum = wave_sum((x[0] + x[64]) + (x[128] + x[192]));
       if (lane == 0) norm_sums(a.norm_part)[wave * a.norm_parts + block] = sum;
     }
   }
@@ -823,9 +840,7 @@ __global__ __launch_bounds__(256) void clipup_step_kernel(float* __restrict__ mu
   {  // a wave adds up one of the four, in a tree of halves
     double* x = red[tid >> 6];
     const int lane = tid & 63;
-    double sum = (x[lane] + x[lane + 128]) + (x[lane + 64] + x[lane + 192]);
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+    const double sum = wave_sum((x[lane] + x[lane + 128]) + (x[lane + 64] + x[lane + 192]));
     if (lane == 0) x[0] = sum;
   }
   __syncthreads();
