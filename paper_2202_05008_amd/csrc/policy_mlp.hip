@@ -1045,9 +1045,12 @@ __global__ __launch_bounds__(512, 4) void mlp_f32_units_kernel(MlpArgs a, int gr
 //     and 18, 60-5 514 of 64 10.3 and 7.4
 //   enough samples that set-up and latency drop out: 16-32-4 2048 of 500 (6.6e8 products) 100 and 61, 600 of 1024 (3.9e8)
 //     47 and 52 with the loss
-// The vector form: parameters through LDS up to 16 KB of them (more would leave room for fewer workgroups); a tiny network
-// on a thousand workgroups and more by one wave each (3-4, 1000 of 300 samples: 9.8 us with four waves and 7.9 with one; 16
-// of 512: 3.0 and 3.4).
+// The vector form: parameters through LDS up to 16 KB of them (more would leave room for fewer workgroups).  A tiny network
+// (fewer than 16 inputs, outputs of w <= 16) on 600 + 15 w^2 workgroups and more by one wave each: no waves without a neuron
+// and barriers among none, but more LDS per wave and longer chains.  us with four waves and one: 3-4, 1000 of 300 samples 7.3
+// and 5.8, 16 of 512 3.0 and 3.4; 1-7, 518 of 858 13.5 and 8.0; 4-8-4, 2318 of 668 with a loss 47 and 32; 1-28, 1530 of 244
+// 20.8 and 26.9; 1-15, 582 of 114 5.0 and 5.7.  Over 5551 networks of one to three layers on 512 to 16384 workgroups the
+// rule costs 1.1 % against the better of the two.
 constexpr int kStagedParams = 4096;
 enum MlpForm { FORM_VECTOR, FORM_SPLIT, FORM_F32 };
 static MlpForm mlp_form(const MlpShape& sh, int pop, int B) {
@@ -1178,7 +1181,9 @@ int launch_mlp_f32(const MlpShape& sh, const float* params, const float* obs, in
   auto by_size = [&](auto loss_c) -> int {
     constexpr int L = decltype(loss_c)::value;
     if (!staged) return launch(mlp_f32_kernel<L, false, 4>, 256);
-    const bool lone = sh.dims[0] < 16 && sh.P < (sh.n_layers == 1 ? 80 : 30) && static_cast<int64_t>(pop) * a.tiles >= 1024;
+    int widest = 0;  // of the layers' outputs
+    for (int l = 1; l <= sh.n_layers; ++l) widest = std::max(widest, sh.dims[l]);
+    const bool lone = sh.dims[0] < 16 && widest <= 16 && static_cast<int64_t>(pop) * a.tiles >= 600 + 15 * widest * widest;
     return lone ? launch(mlp_f32_kernel<L, true, 1>, 64) : launch(mlp_f32_kernel<L, true, 4>, 256);
   };
   if (loss == LOSS_NONE) return by_size(std::integral_constant<int, LOSS_NONE>());

@@ -167,6 +167,35 @@ def test_mlp_f32_vector_form_groups_and_staging(evo, dims, pop, B):
         assert_close(got[some], opolicy.mlp_forward(params[some], obs if shared else obs[some], dims, acts), 1e-5, "outputs")
 
 
+# One wave per tile of samples from 600 + 15 w^2 workgroups on, w <= 16 the widest output and fewer than 16 inputs; four
+# below, and for the first that is wider: the same bits, with the remainders of groups of four and eight neurons.
+@pytest.mark.parametrize("dims", [(1, 2), (15, 4), (5, 8), (2, 9), (3, 12, 5), (7, 5, 16), (4, 4, 4, 4), (14, 13), (1, 17)])
+@pytest.mark.parametrize("B", [5, 70])
+def test_mlp_f32_one_wave_and_four_give_the_same_bits(evo, dims, B):
+    acts = (1,) * (len(dims) - 2) + (0,)
+    wgs = 600 + 15 * max(dims[1:]) ** 2
+    pop = -(-wgs // -(-B // 64))
+    few = (pop - 1) // 2                                     # both below, and two tiles by one workgroup with a loss
+    params = gen.random_params(33, pop, mlp_param_count(dims), 0.4)
+    pd = evo.make_policy_desc(evo.EVO_POLICY_MLP, dims, acts)
+    obs = np.random.default_rng(34).standard_normal((B, dims[0])).astype(np.float32)
+    y = (np.arange(B) % dims[-1]).astype(np.int32)
+    out, fit = {}, {}
+    for n in (pop, few):
+        out[n] = torch.full((n, B, dims[-1]), np.nan, dtype=torch.float32, device="cuda")
+        evo.pop_forward(pd, dev(params[:n]), dev(obs), 0, out[n], n, B)
+        fit[n] = torch.full((n,), np.nan, dtype=torch.float32, device="cuda")
+        task = dict(B=B, obs=dev(obs), target=dev(y))
+        work = torch.empty(max(16, evo.rollout_workspace_bytes(evo.make_task_desc(evo.EVO_TASK_CLASSIFY, **task), pd, n)),
+                           dtype=torch.uint8, device="cuda")
+        evo.rollout(evo.make_task_desc(evo.EVO_TASK_CLASSIFY, work=work, **task), pd, dev(params[:n]), n, 1, fit[n])
+    assert torch.equal(out[pop][:few], out[few]) and torch.equal(fit[pop][:few], fit[few])
+    some = sorted({0, few, pop - 1})
+    want = opolicy.mlp_forward(params[some], obs, dims, acts)
+    assert_close(host(out[pop])[some], want, 1e-5, "outputs")
+    assert_close(host(fit[pop])[some], otasks.classify_fitness(want, y), 1e-5, "fitness")
+
+
 def test_mlp_f32_more_workgroups_than_one_grid_dimension_takes(evo):
     """65528 members of 131200 samples on the fp32 matrix form are 2^32 threads and more; the members' fitness is that of
     a few of them evaluated by themselves."""
