@@ -465,7 +465,6 @@ struct TellArgs {
   uint32_t gen, key0, key1;
   const uint32_t* gen_dev;  // when set: t is read here and the bias corrections are formed in the kernel
   float* norm_part;        // ClipUp: [kGradNormParts] partial sums of g_mu^2, one per workgroup, or null; see norm_sums
-  int norm_parts;
   float inv_n, lr_mu, lr_sigma, max_change, beta1, beta2, eps, bc1, bc2, momentum;
 };
 
@@ -477,7 +476,7 @@ __device__ __forceinline__ float adam_step(float x, float g, float& m, float& v,
   return x + lr * m_hat / (sqrtf(v_hat) + a.eps);
 }
 
-// Behind them: [3][norm_parts] the same in fp64, of vel^2 and of vel g_mu.
+// Behind them: [3][kGradNormParts] the same in fp64, of vel^2 and of vel g_mu.
 __host__ __device__ inline double* norm_sums(float* norm_part) { return reinterpret_cast<double*>(norm_part + kGradNormParts); }
 
 // Thread (q, ks): parameter quad q, pairs ks, ks+KS, ks+2KS, ...  The KS partial sums of a
@@ -614,7 +613,7 @@ __device__ __forceinline__ void tell_block(TellArgs a, int block, PAIRS pairs, f
     if (wave < 3) {
       const double* x = all + 256 * wave + lane;
       const double sum = wave_sum((x[0] + x[64]) + (x[128] + x[192]));
-      if (lane == 0) norm_sums(a.norm_part)[wave * a.norm_parts + block] = sum;
+      if (lane == 0) norm_sums(a.norm_part)[wave * kGradNormParts + block] = sum;
     }
   }
 }
@@ -832,7 +831,7 @@ __global__ __launch_bounds__(256) void clipup_step_kernel(float* __restrict__ mu
   for (int i = tid; i < n; i += 256) {
     acc[3] += static_cast<double>(part[i]);
 #pragma unroll
-    for (int k = 0; k < 3; ++k) acc[k] += sums[k * n + i];
+    for (int k = 0; k < 3; ++k) acc[k] += sums[k * kGradNormParts + i];
   }
 #pragma unroll
   for (int k = 0; k < 4; ++k) red[k][tid] = acc[k];
@@ -1054,7 +1053,6 @@ static TellArgs tell_args(const pgpe_state* st, const float* fitness, float* gmu
   *blocks_out = static_cast<unsigned>((a.nquads + QPB - 1) / QPB);
   // the words of the one-launch generation, which ClipUp never runs as, take the partial sums
   a.norm_part = c.optimizer == EVO_OPT_CLIPUP && *blocks_out <= kGradNormParts ? reinterpret_cast<float*>(ws.gen + 64) : nullptr;
-  a.norm_parts = static_cast<int>(*blocks_out);
   return a;
 }
 
@@ -1107,7 +1105,7 @@ static int run_tell(pgpe_state* st, const float* fitness, float* gmu, float* gsg
   const int grid = (P + 1023) / 1024 < kNormBlocks ? (P + 1023) / 1024 : kNormBlocks;  // four parameters per thread
   if (a.norm_part) {
     hipLaunchKernelGGL(clipup_step_kernel, dim3(grid), dim3(256), 0, s, st->mu, st->m, st->v, P, c.momentum, c.lr_mu, c.max_speed,
-                       a.norm_part, norm_sums(a.norm_part), a.norm_parts);
+                       a.norm_part, norm_sums(a.norm_part), static_cast<int>(blocks));
     return check_launch("clipup_step_kernel");
   }
   hipLaunchKernelGGL(sqnorm_kernel, dim3(kNormBlocks), dim3(256), 0, s, st->v, P, ws.norm);
