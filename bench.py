@@ -36,15 +36,15 @@ PEAK_ALU_F32_TF = 157.3        # fp32 vector (256 CU x 4 SIMD x 32 lanes x 2.4 G
 # box FETCH_SIZE x 2.0, WRITE_SIZE x 1.0).  Sources: the summaries under profiles/.  Counters cannot be
 # read from inside the run, so `traffic` is what the profile of this same command measured, not this run.
 MEASURED_TRAFFIC_BYTES = {
-    "cfg1": 2924945,       # profiles/mlp_f32_kernel_cfg1.md
+    "cfg1": 1595392,       # profiles/mlp_f32_kernel_cfg1.md
     "cfg2": 37831063,      # profiles/convnet_kernel_cfg2.md (algorithmic 12.5 MB: the batch, as 4 KB of fp16 planes per
                            # image, is re-fetched per L2)
     "cfg3": 19116032,      # profiles/cartpole_kernel_cfg3.md
     "cfg4": 807197617,     # profiles/mlp_bf16_stream_kernel_cfg4.md
     "cfg5": 4305387571,    # profiles/ask_sphere_tell_kernels_cfg5.md (ask)
     "seq2seq": 890661888,  # profiles/lstm_seq2seq_kernel_seq2seq.md (algorithmic 598 MB: the rest is register spill traffic)
-    "forage": 325433344,   # profiles/world_resident_kernel_forage.md (positions handed over and polled in each of 500 steps)
-    "forage_solo": 5979136,  # profiles/world_solo_kernel_forage_solo.md (the weights, read once; the rest stays on chip)
+    "forage": 324677632,   # profiles/world_resident_kernel_forage.md (positions handed over and polled in each of 500 steps)
+    "forage_solo": 5982208,  # profiles/world_solo_kernel_forage_solo.md (the weights, read once; the rest stays on chip)
 }
 
 
@@ -60,9 +60,9 @@ BOUND_DETAIL = {
     "cfg4": "HBM weight stream: 64 flop per weight byte (profiles/mlp_bf16_stream_kernel_cfg4.md)",
     "cfg5": "HBM write of the population in ask (profiles/ask_sphere_tell_kernels_cfg5.md)",
     "seq2seq": "instruction issue: VALU busy 44 % + MFMA busy 37 %, 29 % of wave time waiting (profiles/lstm_seq2seq_kernel_seq2seq.md)",
-    "forage": "vector-instruction issue plus one hand-over between workgroups per step: vector ALU 81 % busy, polling included "
+    "forage": "vector-instruction issue plus one hand-over between workgroups per step: vector ALU 85 % busy, polling included "
               "(profiles/world_resident_kernel_forage.md)",
-    "forage_solo": "vector-instruction issue along the step chain: vector ALU 82 % busy (profiles/world_solo_kernel_forage_solo.md)",
+    "forage_solo": "vector-instruction issue along the step chain: vector ALU 81 % busy (profiles/world_solo_kernel_forage_solo.md)",
 }
 
 DEFAULT_STEPS = {"cfg1": 200, "cfg2": 50, "cfg3": 20, "cfg4": 50, "cfg5": 20, "seq2seq": 20, "forage": 20, "forage_solo": 50}

@@ -543,7 +543,7 @@ __global__ __launch_bounds__(kStepThreads) void world_step_kernel(StepArgs a) {
 
 // ---- the whole episode of shared worlds in one launch -----------------------------------------------------
 // A launch per step takes 9.1 us (1024 agents, 8 worlds, H = 32), of which the gap, the reloading of the weights and the
-// staging of four worlds are two thirds; this kernel's step takes 3.6 us, and 2.4 us where a world is small.  The agents
+// staging of four worlds are two thirds; this kernel's step takes 3.4 us, and 2.7 us where a world is small.  The agents
 // stay where they are: a workgroup owns agents of ONE world for all steps, weights, state
 // and reward in registers, and what a step has to hand over goes through memory as its own flag: an agent's position is
 // one 8-byte word, x and y with the step's number modulo four in the two top bits of x (a coordinate lies in [0, 1], so
@@ -560,7 +560,7 @@ __global__ __launch_bounds__(kStepThreads) void world_step_kernel(StepArgs a) {
 // up afterwards among the candidates of the lane that holds the minimum).  Policy: sixteen lanes per agent for H <= 32;
 // for H = 64 a wave per agent, since sixteen lanes would need 303 registers each for the weights.
 // The order of every sum is world_step_kernel's, so the trajectories are its trajectories bit for bit.
-// What a step consists of (cycles of a main wave, 8600 in all at 1024 agents): waiting for the positions 2000 + 900 (the
+// What a step consists of (cycles of a main wave at 1024 agents, 8600 in all when it was measured and a step took 3.6 us): waiting for the positions 2000 + 900 (the
 // slowest workgroup), scan 2100 (at the issue rate of two main waves and an item wave per SIMD), look-up 500, waiting for
 // the items 900, policy 950, motion and touches 1300 (a dependent chain at one instruction per 6 to 7 cycles).  With the
 // items and touches in the main waves and one helper wave a step took 9600.
@@ -1431,7 +1431,7 @@ static int resident_worlds(int pop, int worlds, int H) { return std::min(worlds,
 // workgroups (8 agents x 4 worlds) as it has.  So a launch per step is better for a few steps, for many worlds of a few
 // agents, and, as a workgroup of the one launch has only 8 agents there, for many workgroups at H = 64.
 // Microseconds per step, a launch per step / this way, 24 + 24 items:
-//   H = 32: 64 x 8 worlds 7.0 / 3.0, 1024 x 1 7.3 / 3.7, 1024 x 8 9.3 / 3.6, 4800 x 1 51 / 8.7, 64 x 512 24 / 12, 1024 x 64 60 / 29,
+//   H = 32: 64 x 8 worlds 7.0 / 2.9, 1024 x 1 7.3 / 3.7, 1024 x 8 9.1 / 3.4, 4800 x 1 51 / 8.7, 64 x 512 24 / 12, 1024 x 64 60 / 29,
 //           8 x 512 6.9 / 5.6, 8 x 1024 6.9 / 10.8, 8 x 4096 24 / 43, 16 x 4096 47 / 43, 32 x 4096 92 / 45
 //   H = 16: 8 x 4096 13 / 40, 32 x 4096 46 / 40, 256 x 1024 89 / 89
 //   H = 64: 64 x 8 13.4 / 3.4, 1024 x 2 11.6 / 4.0, 600 x 6 15.3 / 8.4, 1024 x 8 17.0 / 16.6, 8 x 4096 51 / 48, 512 x 64 55 / 65, 1024 x 64 120 / 135
