@@ -560,7 +560,8 @@ __global__ __launch_bounds__(kStepThreads) void world_step_kernel(StepArgs a) {
 // up afterwards among the candidates of the lane that holds the minimum).  Policy: sixteen lanes per agent for H <= 32;
 // for H = 64 a wave per agent, since sixteen lanes would need 303 registers each for the weights.
 // The order of every sum is world_step_kernel's, so the trajectories are its trajectories bit for bit.
-// What a step consists of (cycles of a main wave at 1024 agents, 8600 in all when it was measured and a step took 3.6 us): waiting for the positions 2000 + 900 (the
+// What a step consists of (cycles of a main wave at 1024 agents, 8600 in all when it was measured and a step took 3.6 us):
+// waiting for the positions 2000 + 900 (the
 // slowest workgroup), scan 2100 (at the issue rate of two main waves and an item wave per SIMD), look-up 500, waiting for
 // the items 900, policy 950, motion and touches 1300 (a dependent chain at one instruction per 6 to 7 cycles).  With the
 // items and touches in the main waves and one helper wave a step took 9600.
@@ -1660,7 +1661,8 @@ int launch_forage(const MlpShape& sh, const float* params, int pop, int worlds, 
   const int H = sh.dims[1], groups = resident_groups(pop, H), per_launch = resident_worlds(pop, worlds, H);
   const bool tame = std::isfinite(cp[0]) && std::isfinite(cp[1]) && std::isfinite(cp[2]) && std::isfinite(cp[3]);
   ResidentTurn* turn = nullptr;
-  if (form.force != 2 && tame && l.room && per_launch > 0 && (form.force == 1 || one_launch_pays(H, pop, worlds, steps, per_launch)) &&
+  if (form.force != 2 && tame && l.room && per_launch > 0 &&
+      (form.force == 1 || one_launch_pays(H, pop, worlds, steps, per_launch)) &&
       static_cast<uint64_t>((worlds + per_launch - 1) / per_launch) * (static_cast<uint64_t>(steps) + 1) < (1ull << 32))
     turn = resident_turn(groups * per_launch, form.create, s);
 
